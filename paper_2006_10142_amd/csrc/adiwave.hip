@@ -148,6 +148,25 @@ bool launch_x(const XPlan& p, int grid, const XArgs<T>& a, hipStream_t st)
     return false;
 }
 
+// entry pivots of every row: one 8-node segment per thread, the narrowest group of
+// threads that covers the row
+template <typename T, int TR>
+void launch_xpivots1(const T* r, T* qin, T* qin2, int nx, int ny, int nseg, hipStream_t st)
+{
+    constexpr int NT = TR >= 256 ? TR : 256, G = NT / TR;
+    hipLaunchKernelGGL((k_xpivots<T, TR>), dim3((ny + G - 1) / G), dim3(NT), 0, st, r, qin, qin2, nx, ny, nseg);
+}
+
+template <typename T>
+void launch_xpivots(const T* r, T* qin, T* qin2, int nx, int ny, int nseg, hipStream_t st)
+{
+    if (nseg <= 64) launch_xpivots1<T, 64>(r, qin, qin2, nx, ny, nseg, st);
+    else if (nseg <= 128) launch_xpivots1<T, 128>(r, qin, qin2, nx, ny, nseg, st);
+    else if (nseg <= 256) launch_xpivots1<T, 256>(r, qin, qin2, nx, ny, nseg, st);
+    else if (nseg <= 512) launch_xpivots1<T, 512>(r, qin, qin2, nx, ny, nseg, st);
+    else launch_xpivots1<T, 1024>(r, qin, qin2, nx, ny, nseg, st);
+}
+
 template <typename T, int P>
 bool launch_yscan_sk(int sk, int grid, const YArgs<T>& a, hipStream_t st)
 {
@@ -647,14 +666,9 @@ adi_status set_coef(adi_wave_s* w, const void* field, double scalar, int squared
                        static_cast<const T*>(field), (T)scalar, squared, (T)s,
                        static_cast<T*>(w->r), n);
     ADI_LAUNCHED("coef");
-    hipLaunchKernelGGL((k_xpivots<T>), dim3((w->ny + 255) / 256), dim3(256), 0, w->stream,
-                       static_cast<const T*>(w->r), static_cast<T*>(w->qin), w->nx, w->ny, w->nseg);
+    launch_xpivots<T>(static_cast<const T*>(w->r), static_cast<T*>(w->qin), static_cast<T*>(w->qin2), w->nx, w->ny,
+                      w->nseg, w->stream);
     ADI_LAUNCHED("x_pivots");
-    if (w->qin2) {
-        hipLaunchKernelGGL((k_xpivots<T, 2>), dim3((w->ny + 255) / 256), dim3(256), 0, w->stream,
-                           static_cast<const T*>(w->r), static_cast<T*>(w->qin2), w->nx, w->ny, (w->nx + 1) / 2);
-        ADI_LAUNCHED("x_pivots (2-node lanes)");
-    }
     if (measure)
         if (adi_status s = measure_rmax<T>(w)) return s;
     return static_planes<T>(w);

@@ -270,26 +270,6 @@ struct XArgs {
 constexpr int kSeg = 8;   // nodes per x-line segment (one segment per thread)
 constexpr int kPB = 16;   // column block width of the y-chunk summary planes
 
-// pivot entering every segment of SEG nodes of every row (SEG = kSeg: the x-sweep's
-// segments; 2: the lanes of the FP64 one-pass strips): one thread per row, sequential
-template <typename T, int SEG = kSeg>
-__global__ void __launch_bounds__(256) k_xpivots(const T* __restrict__ r, T* __restrict__ qin,
-                                                 int nx, int ny, int nseg)
-{
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= ny) return;
-    const T* rr = r + (size_t)j * nx;
-    T* qo = qin + (size_t)j * nseg;
-    T q = T(0);
-    for (int s = 0; s < nseg; ++s) {
-        qo[s] = q;
-        for (int e = 0; e < SEG; ++e) {
-            const int i = SEG * s + e;
-            if (i < nx) (void)pivot_step<T>(rr[i], q);
-        }
-    }
-}
-
 // ---------------------------------------------------------- buffer I/O ----
 // Rows are read and written through buffer resources whose size is the row's
 // byte length (0 for a row outside the grid): the hardware range check returns
@@ -318,9 +298,10 @@ typedef double f64x2 __attribute__((ext_vector_type(2)));
 // (whole vectors are bit-cast: a bit cast of a single vector element is not
 // compiled correctly by this toolchain)
 
-// 8 consecutive values at byte offset voff with 16-byte accesses.  The row is
-// 16-byte aligned and its byte length a multiple of 16, so every access is
-// wholly inside or wholly outside the range.
+// 8 consecutive values at byte offset voff with 16-byte accesses, which need only
+// 4-byte alignment.  The range check works dword by dword: of an access that crosses
+// the row's end the values past it read as 0 (or are not stored), the others are
+// transferred, so rows of any length and alignment take it.
 template <typename T>
 __device__ __forceinline__ void bload8(rsrc_t rs, int voff, T (&v)[kSeg])
 {
@@ -378,6 +359,79 @@ __device__ __forceinline__ T bload1(rsrc_t rs, int voff)
         return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, 0, 0));
     else
         return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, voff, 0, 0));
+}
+
+// Pivots of a whole line in parallel.  Over a run of nodes the entry pivot q maps to
+//     q_out = al + be q / (1 - ga q),
+// al the run's last pivot started from 0, be = (prod q_e)^2 and ga = sum_e (prod_{i<e}
+// q_i)(prod_{i<=e} q_i) of the same pivots: al, be, ga lie in [0, 1), so neither a
+// map nor a composition of two can overflow or cancel (1 - ga al > 0 for any r).
+struct PivotMap {
+    double al, be, ga;
+};
+// the run `b` after the run `a`
+__device__ __forceinline__ PivotMap then(const PivotMap& a, const PivotMap& b)
+{
+    const double m = nr_rcp(1.0 - b.ga * a.al);
+    return {b.al + b.be * (a.al * m), a.be * b.be * (m * m), a.ga + a.be * (b.ga * m)};
+}
+__device__ __forceinline__ double pivot_after(const PivotMap& a, double q) { return a.al + a.be * (q * nr_rcp(1.0 - a.ga * q)); }
+
+// pivot entering every 8-node segment of every row (qin: the x-sweep's segments), and,
+// with qin2, every 2-node segment (the lanes of the FP64 one-pass strips): TR threads
+// per row, one segment each.  The segments' maps are formed and scanned in FP64 (prefix
+// over the wavefront, then the wavefronts' totals in order), so the pivots are those
+// of a sequential sweep up to their own rounding.
+// Latency-bound: one thread per row, walking it node by node, took 160 us at 1024^2
+// (FP32) and 350 + 536 us (both planes) at 2048^2 (FP64); the parallel form takes 4.6 and 15 us.
+template <typename T, int TR>
+__global__ void __launch_bounds__(TR >= 256 ? TR : 256)
+    k_xpivots(const T* __restrict__ r, T* __restrict__ qin, T* __restrict__ qin2, int nx, int ny, int nseg)
+{
+    constexpr int NW = TR / 64, G = (TR >= 256 ? TR : 256) / TR;
+    __shared__ PivotMap tot[G][NW];
+    const int g = threadIdx.x / TR, t = threadIdx.x - g * TR;
+    const int lane = t & 63, wv = t >> 6;
+    const int j = blockIdx.x * G + g;
+    const bool act = j < ny && t < nseg;
+    T rv[kSeg];
+    bload8<T>(buf(r + (size_t)(j < ny ? j : 0) * nx, j < ny ? nx * (int)sizeof(T) : 0), t * kSeg * (int)sizeof(T), rv);
+    double rr[kSeg];
+#pragma unroll
+    for (int e = 0; e < kSeg; ++e) rr[e] = (double)rv[e];   // 0 past the row's end
+    PivotMap m{0.0, 1.0, 0.0};
+    {
+        double q = 0.0, pi = 1.0, ga = 0.0;
+#pragma unroll
+        for (int e = 0; e < kSeg; ++e) {
+            (void)pivot_step<double>(rr[e], q);
+            const double p = pi * q;
+            ga = fma_rn(pi, p, ga);
+            pi = p;
+        }
+        if (act) m = {q, pi * pi, ga};
+    }
+#pragma unroll
+    for (int s = 1; s < 64; s <<= 1) {
+        const PivotMap o{__shfl_up(m.al, s), __shfl_up(m.be, s), __shfl_up(m.ga, s)};
+        if (lane >= s) m = then(o, m);
+    }
+    if (lane == 63) tot[g][wv] = m;
+    __syncthreads();
+    double q = 0.0;                        // entering this wavefront
+    for (int k = 0; k < wv; ++k) q = pivot_after(tot[g][k], q);
+    const PivotMap before{__shfl_up(m.al, 1), __shfl_up(m.be, 1), __shfl_up(m.ga, 1)};
+    if (lane > 0) q = pivot_after(before, q);
+    if (!act) return;
+    qin[(size_t)j * nseg + t] = (T)q;
+    if (qin2) {
+        const int n2 = (nx + 1) / 2;
+#pragma unroll
+        for (int e = 0; e < kSeg; ++e) {
+            if (e % 2 == 0 && t * kSeg + e < nx) qin2[(size_t)j * n2 + t * (kSeg / 2) + e / 2] = (T)q;
+            (void)pivot_step<double>(rr[e], q);
+        }
+    }
 }
 
 // One row of x-lines solved on chip by a line group of TR threads (kSeg nodes each,

@@ -1,0 +1,61 @@
+"""GPU line kernels at the sizes where their splits change, against the FP64 oracle.
+
+One step from u_prev = 2 u_curr, whose result is the ADI increment itself, on random
+coefficients.  Tolerances: the factors I - beta K L of a line are diagonally dominant
+with condition number at most 1 + 4 r, so a backward-stable solve of both factors is
+off by a few eps (1 + 4 r_max) relative; with r_max = 4.5, 1e-13 in FP64 and 2e-5 in
+FP32 leave a factor of ten over 2 * 19 eps.
+"""
+import numpy as np
+import pytest
+
+from tests.conftest import rel_l2
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+TOL = {"f64": 1e-13, "f32": 2e-5}
+
+
+@pytest.fixture(scope="module")
+def adw():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2006_10142_amd as m
+    m._lib.load()
+    return m
+
+
+def increment(adw, oracle_lib, dtype, nx, ny, rmax, smin=1.0, one_pass=None):
+    """(relative error of one step's increment, the handle's info)."""
+    nt, tt = (np.float32, torch.float32) if dtype == "f32" else (np.float64, torch.float64)
+    rng = np.random.default_rng(nx * 31 + ny)
+    h = 1.0 / (max(nx, ny) + 1)
+    dt = np.sqrt(2 * rmax) * h / 3.0
+    c = rng.uniform(smin, 3.0, (ny, nx)).astype(nt)
+    uc = rng.standard_normal((ny, nx)).astype(nt)
+    up = (2 * uc.astype(np.float64)).astype(nt)
+    src = np.array([(ny - 1) * nx + nx - 1, 0, (ny // 2) * nx + nx // 3], np.int32)
+    amp = (np.array([[1.0, -0.5, 2.0]]) / (h * h)).astype(nt)
+    f = np.bincount(src, weights=amp[0].astype(np.float64), minlength=nx * ny).reshape(ny, nx)
+    ref = oracle_lib.step_parts(c.astype(np.float64) ** 2, up, uc, h, dt, f=f)["d"]
+    wave = adw.Wave(nx, ny, h, dt, c=torch.from_numpy(c).cuda(), dtype=tt)
+    if one_pass is not None:
+        wave.set_tuning(fused_step=one_pass)
+    a, b = wave.step(torch.from_numpy(up).cuda(), torch.from_numpy(uc).cuda(), 1,
+                     src_idx=torch.from_numpy(src).cuda(), src_amp=torch.from_numpy(amp).cuda())
+    torch.cuda.synchronize()
+    info = wave.info()
+    wave.close()
+    return rel_l2(b.cpu().numpy(), ref), info
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("nx", [1, 7, 9, 511, 513, 1025, 2049, 4095, 4097, 8192])
+def test_entry_pivots_of_long_rows(adw, oracle_lib, dtype, nx):
+    """Rows around the widths where the pivot kernel's thread group changes (512 x 2^k)
+    and its last segment is partial; r up to 4.5, where the pivots are remembered over
+    many segments."""
+    print(f"entry pivots {dtype} nx={nx}", flush=True)
+    err, _ = increment(adw, oracle_lib, dtype, nx, 5, 4.5)
+    assert err <= TOL[dtype]
