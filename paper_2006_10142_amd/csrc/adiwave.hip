@@ -379,8 +379,6 @@ XArgs<T> make_x(const adi_wave_s* w, const void* u, const adi_source* f, int k, 
     a.nseg = w->nseg;
     a.rows_per_strip = w->xp.fuse ? w->xp.frs : w->xp.rs;
     a.xcd = a.rows_per_strip <= kXcdStripRows;
-    a.vec = ((size_t)w->nx * sizeof(T)) % 16 == 0 && aligned16(u) && aligned16(w->r) &&
-            aligned16(w->w);
     a.sum = static_cast<T*>(w->sum);
     a.K = w->K;
     a.M = w->M;

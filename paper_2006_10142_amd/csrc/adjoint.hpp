@@ -212,7 +212,7 @@ struct XUShared {
     int src_n;                   // count, or -1 when the strip holds more than kStripSrc
 };
 
-template <typename T, int TR, bool VEC>
+template <typename T, int TR>
 __device__ __forceinline__ void xsolve_update_strip(const XArgs<T>& X, const AdjArgs<T>& A, const int strip,
                                                     const int t, XUShared<T, TR>& sh)
 {
@@ -231,18 +231,10 @@ __device__ __forceinline__ void xsolve_update_strip(const XArgs<T>& X, const Adj
     const long long npts = (long long)nx * ny;
     auto seg = [&](const T* base, int row, T (&v)[E]) {      // this lane's nodes of a row, 0 outside
         const bool in = row >= 0 && row < ny;
-        if constexpr (VEC) {
-            bload8<T>(buf(base + (size_t)(in ? row : 0) * nx, in ? row_bytes : 0), voff, v);
-        } else if (act && in) {
-            gload8<T>(base + (size_t)row * nx, i0, nx, v);
-        } else {
-#pragma unroll
-            for (int e = 0; e < E; ++e) v[e] = T(0);
-        }
+        bload8<T>(buf(base + (size_t)(in ? row : 0) * nx, in ? row_bytes : 0), voff, v);
     };
     auto put = [&](T* base, int row, const T (&v)[E]) {
-        if constexpr (VEC) bstore8<T>(buf(base + (size_t)row * nx, row_bytes), voff, v);
-        else if (act) gstore8<T>(base + (size_t)row * nx, i0, nx, v);
+        bstore8<T>(buf(base + (size_t)row * nx, row_bytes), voff, v);
     };
     auto one = [&](const T* base, int row, int col) -> T {   // a single value, 0 outside
         return (act && row >= 0 && row < ny && col >= 0 && col < nx) ? base[(size_t)row * nx + col] : T(0);
@@ -425,8 +417,7 @@ __global__ void __launch_bounds__(TR >= 256 ? TR : 256) k_xsolve_update(XArgs<T>
     const int strips = (X.ny + X.rows_per_strip - 1) / X.rows_per_strip;
     if (blk * G >= strips) return;
     const int g = __builtin_amdgcn_readfirstlane(threadIdx.x / TR);
-    if (X.vec) xsolve_update_strip<T, TR, true>(X, A, blk * G + g, threadIdx.x - g * TR, sh[g]);
-    else xsolve_update_strip<T, TR, false>(X, A, blk * G + g, threadIdx.x - g * TR, sh[g]);
+    xsolve_update_strip<T, TR>(X, A, blk * G + g, threadIdx.x - g * TR, sh[g]);
 }
 
 // The transposed y-lines of one reverse step, z = A_y^{-1} (r lambda), on windows
@@ -628,7 +619,6 @@ adi_status queue_xsolve(adi_wave_s* w, const void* rhs, void* out)
     a.w = static_cast<T*>(out);
     a.rows_per_strip = w->xp.rs;
     a.xcd = a.rows_per_strip <= kXcdStripRows;
-    a.vec = a.vec && aligned16(out);
     const int g = x_groups_per_wg(w->xp.tr);
     const int grid = xsweep_grid(w->ny, w->xp.rs, g);
     switch (w->xp.tr) {
@@ -651,9 +641,6 @@ bool queue_xsolve_update(adi_wave_s* w, const void* z, const AdjArgs<T>& ua)
     XArgs<T> a = make_x<T>(w, z, nullptr, 0, T(1));
     a.rows_per_strip = w->xp.rs;
     a.xcd = a.rows_per_strip <= kXcdStripRows;
-    a.vec = ((size_t)w->nx * sizeof(T)) % 16 == 0 && aligned16(z) && aligned16(w->r) && aligned16(ua.uk) &&
-            aligned16(ua.up) && aligned16(ua.um) && aligned16(ua.lam1) && aligned16(ua.lam2) &&
-            aligned16(ua.grad);
     const int grid = xsweep_grid(w->ny, w->xp.rs, x_groups_per_wg(w->xp.tr));
     switch (w->xp.tr) {
         case 64: hipLaunchKernelGGL((k_xsolve_update<T, 64>), dim3(grid), dim3(256), 0, w->stream, a, ua); return true;

@@ -17,7 +17,7 @@ constexpr int kBatchStripRows = 1024;   // longest strip segment of a batched si
 
 template <typename T>
 struct SimDesc {
-    int nx, ny, nseg, K, nxp, vec;
+    int nx, ny, nseg, K, nxp;
     int f_wt, f_tx, f_tiles;   // one-pass tiles (see fused.hpp)
     int f4_wt, f4_tx, f4_tiles;   // one-pass tiles with four nodes per lane (fused4.hpp)
     int s_wt, s_tx, s_hs, s_tiles;   // one-pass column strips (fusedr.hpp): width, strips, segment rows
@@ -144,7 +144,6 @@ __global__ void __launch_bounds__(TR >= 256 ? TR : 256) k_xsweep_batch(BatchArgs
             A.nx = S.nx;
             A.ny = S.ny;
             A.nseg = S.nseg;
-            A.vec = S.vec;
             A.sum = S.sum;
             A.K = S.K;
             A.nxp = S.nxp;
@@ -294,13 +293,9 @@ void fill_desc(adi_batch_s* b)
         if (!b->s_wt.empty()) {
             d[s].s_wt = b->s_wt[s]; d[s].s_tx = b->s_tx[s]; d[s].s_hs = b->s_hs[s]; d[s].s_tiles = b->s_tiles[s];
         }
-        d[s].vec = ((size_t)w.nx * sizeof(T)) % 16 == 0;
         d[s].r = (T*)w.r; d[s].w = (T*)w.w; d[s].qin = (T*)w.qin; d[s].sum = (T*)w.sum; d[s].X = (T*)w.X;
         d[s].lev[0] = b->bound ? (T*)b->lev0[s] : nullptr;
         d[s].lev[1] = b->bound ? (T*)b->lev1[s] : nullptr;
-        if (b->bound)
-            d[s].vec = d[s].vec && aligned16(b->lev0[s]) && aligned16(b->lev1[s]) && aligned16(w.r) &&
-                       aligned16(w.w);
     }
 }
 
