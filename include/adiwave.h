@@ -348,7 +348,8 @@ typedef struct {
     int y_fused;              /* 1: y-chunk elimination fused into the x-sweep */
     int y_chunk_rows;         /* y-lines are split in chunks of this many rows */
     int y_chunks;             /* number of chunks per y-line */
-    int kernels_per_step;     /* launches queued per ADI step */
+    int kernels_per_step;     /* launches queued per ADI step (exact step: 2 with whole columns
+                                 in one launch, 3 or 4 with the chunked y-solve) */
     size_t workspace_bytes;   /* device bytes owned by the handle */
     int fused_step;           /* 1: adi_wave_step runs the one-pass step */
     int fused_allowed;        /* 1: the one-pass step's truncation bound holds (FP32:
@@ -380,7 +381,9 @@ adi_status adi_wave_get_info(adi_wave_t w, adi_wave_info* info);
 typedef struct {
     int x_threads_per_line;   /* 64, 128, 256 or 1024, with 8 * threads >= nx */
     int x_rows_per_strip;     /* >= 1 (unfused plans; a fused strip is one y-chunk) */
-    int y_fused;              /* 1 = fuse the y-chunk elimination into the x-sweep, 2 = separate */
+    int y_fused;              /* 1 = fuse the y-chunk elimination into the x-sweep, 2 = separate
+                                 (either, like y_chunk_rows, takes the chunked y-solve instead
+                                 of the whole-column one of short columns) */
     int y_chunk_rows;         /* 16 or 32 */
     int fused_step;           /* 1 = one-pass step when allowed (else ADI_EUNSUPPORTED),
                                  2 = exact two-pass step, 0 = keep */

@@ -16,6 +16,7 @@
 #include "fused.hpp"
 #include "fused4.hpp"
 #include "fusedr.hpp"
+#include "ycol.hpp"
 #include "cr.hpp"
 #include "tridiag_part.hpp"
 
@@ -200,6 +201,69 @@ bool launch_ysolve(int M, dim3 grid, const YArgs<T>& a, hipStream_t st)
     return false;
 }
 
+// whole-column y-lines (ycol.hpp): rows per thread, the fewest of 2 .. 32 whose 64
+// segments cover ny; 0: the chunked y-solve.  Columns of more than 1024 rows (32 a
+// thread, one workgroup a compute unit) stay with it on grids above 2^23 nodes, where
+// both are bound by bytes and its many small workgroups hide the loads better (step of
+// 8192 x 2048: FP32 121 us chunked, 129 whole; FP64 259, 291); at or below, whole
+// columns win (4096 x 2048: FP32 76, 62; FP64 141, 138; 2048 x 1100 FP32 30.4, 22.0).
+int choose_ycol(int nx, int ny, adi_dtype dt)
+{
+    const long long n = (long long)nx * ny;
+    if (n * (long long)esize(dt) > kFuOOB || (ny > kYcP * 16 && n > (1LL << 23))) return 0;
+    for (int s = 2; s <= 32; s *= 2)
+        if (kYcP * s >= ny) return s;
+    return 0;
+}
+
+// threads of a block of CB columns: whole wavefronts holding ceil(ny / S) segments
+int ycol_threads(int ny, int S, int CB) { return (CB * ((ny + S - 1) / S) + 63) / 64 * 64; }
+
+template <typename T, int CB>
+bool launch_ycol_s(int S, const YArgs<T>& a, hipStream_t st)
+{
+    constexpr bool kTop = CB < 16 || sizeof(T) == 4;      // 32-row segments fit the registers
+    const int blocks = (a.nx + CB - 1) / CB;
+    const dim3 grid((blocks + 7) / 8 * 8), blk(ycol_threads(a.ny, S, CB));
+    switch (S) {
+        case 2: hipLaunchKernelGGL((k_ycol<T, 2, CB>), grid, blk, 0, st, a); return true;
+        case 4: hipLaunchKernelGGL((k_ycol<T, 4, CB>), grid, blk, 0, st, a); return true;
+        case 8: hipLaunchKernelGGL((k_ycol<T, 8, CB>), grid, blk, 0, st, a); return true;
+        case 16: hipLaunchKernelGGL((k_ycol<T, 16, CB>), grid, blk, 0, st, a); return true;
+        case 32:
+            if constexpr (kTop) { hipLaunchKernelGGL((k_ycol<T, 32, CB>), grid, blk, 0, st, a); return true; }
+            return false;
+    }
+    return false;
+}
+
+// Columns per workgroup: 16 where that leaves a workgroup for each of 256 compute units
+// (FP32 8192 x 1024: 54 us a step, 64 with 8 columns, 90 with 4; not for FP64 segments
+// of 32 rows, whose registers allow 512 threads), else 8 where that does (FP32: from
+// 128 workgroups on; 1501 x 997: 17.6 us, 18.9 with 16, 21.2 with 4), else 4 (1024^2
+// FP64: 20.1 us, 21.6 with 8; 500 x 2040 FP32 19.9, 22.2 with 8).
+template <typename T>
+bool launch_ycol(int S, const YArgs<T>& a, hipStream_t st)
+{
+    if (a.nx > 16 * 255 && (sizeof(T) == 4 || S <= 16)) return launch_ycol_s<T, 16>(S, a, st);
+    if (a.nx > 8 * (sizeof(T) == 4 ? 127 : 255)) return launch_ycol_s<T, 8>(S, a, st);
+    return launch_ycol_s<T, 4>(S, a, st);
+}
+
+template <typename T>
+bool launch_ycol_pivots(int S, const T* r, T* qy, int nx, int ny, hipStream_t st)
+{
+    const dim3 grid((nx + kYpCB - 1) / kYpCB), blk(ycol_threads(ny, S, kYpCB));
+    switch (S) {
+        case 2: hipLaunchKernelGGL((k_ycol_pivots<T, 2>), grid, blk, 0, st, r, qy, nx, ny); return true;
+        case 4: hipLaunchKernelGGL((k_ycol_pivots<T, 4>), grid, blk, 0, st, r, qy, nx, ny); return true;
+        case 8: hipLaunchKernelGGL((k_ycol_pivots<T, 8>), grid, blk, 0, st, r, qy, nx, ny); return true;
+        case 16: hipLaunchKernelGGL((k_ycol_pivots<T, 16>), grid, blk, 0, st, r, qy, nx, ny); return true;
+        case 32: hipLaunchKernelGGL((k_ycol_pivots<T, 32>), grid, blk, 0, st, r, qy, nx, ny); return true;
+    }
+    return false;
+}
+
 template <typename T, int S, int TR>
 void launch_tri1(long long batch, const TriArgs<T>& a, hipStream_t st)
 {
@@ -251,6 +315,9 @@ struct adi_wave_s {
     void* X = nullptr;     // K * nx
     void* qin = nullptr;   // ny * nseg entry pivots of the x-line segments
     void* qin2 = nullptr;  // FP64: ny * ceil(nx / 2) entry pivots of every 2-node lane (one-pass strips)
+    void* qy = nullptr;    // qy_n = ceil(ny / ycs) * nx entry pivots of the y-line segments (ycol.hpp)
+    size_t qy_n = 0;
+    int ycs = 0;           // rows per thread of the whole-column y-solve; 0: the chunked y-solve
     int nseg = 0;
     int nxp = 0;           // nx rounded up to the summary-plane column block
     size_t w_cap = 0;      // elements of w (also create-time scratch of 5*K*nx)
@@ -300,10 +367,11 @@ void free_ws(adi_wave_s* w)
     if (w->X) (void)hipFree(w->X);
     if (w->qin) (void)hipFree(w->qin);
     if (w->qin2) (void)hipFree(w->qin2);
+    if (w->qy) (void)hipFree(w->qy);
     if (w->cr_abc) (void)hipFree(w->cr_abc);
     if (w->r_prev) (void)hipFree(w->r_prev);
     if (w->rho_buf) (void)hipFree(w->rho_buf);
-    w->r = w->w = w->sum = w->X = w->qin = w->qin2 = w->cr_abc = w->r_prev = w->rho_buf = nullptr;
+    w->r = w->w = w->sum = w->X = w->qin = w->qin2 = w->qy = w->cr_abc = w->r_prev = w->rho_buf = nullptr;
 }
 
 adi_status alloc_chunks(adi_wave_s* w)
@@ -335,7 +403,8 @@ adi_status alloc_chunks(adi_wave_s* w)
         return fail(ADI_ENOMEM, "hipMalloc of y-chunk workspace failed");
     }
     w->bytes = ((size_t)w->nx * w->ny + w->w_cap + (size_t)w->ny * w->nseg + nsum + nX +
-                (w->qin2 ? (size_t)w->ny * ((w->nx + 1) / 2) : 0)) * es;
+                (w->qin2 ? (size_t)w->ny * ((w->nx + 1) / 2) : 0) +
+                w->qy_n) * es;
     return ADI_OK;
 }
 
@@ -408,6 +477,7 @@ YArgs<T> make_y(const adi_wave_s* w, const void* u, const void* v, void* out, T 
     a.K = w->K;
     a.nxp = w->nxp;
     a.tmp = static_cast<T*>(w->w);
+    a.qy = static_cast<const T*>(w->qy);
     a.sum = static_cast<T*>(w->sum);
     a.X = static_cast<T*>(w->X);
     a.u = static_cast<const T*>(u);
@@ -423,9 +493,44 @@ int x_grid(const adi_wave_s* w)
     return xsweep_grid(w->ny, w->xp.fuse ? w->xp.frs : w->xp.rs, x_groups_per_wg(w->xp.tr));
 }
 
-// Queue one solve: x-sweep of `u` (with sources f at step k) then the y-chain
+// Queue the y-lines and the update: whole columns in one launch where they fit
+// (ycol.hpp), else the chunk reduction (unless the x-sweep did it: `reduced`), the
+// interface systems and the chunk solve.  `ev` (optional): ev[1] .. ev[3] receive the
+// ends of the three.
+template <typename T>
+adi_status queue_y(adi_wave_s* w, const YArgs<T>& ya, bool reduced, hipEvent_t* ev)
+{
+    hipStream_t st = w->stream;
+    if (w->ycs) {
+        if (ev) {
+            ADI_HIP(hipEventRecord(ev[1], st));
+            ADI_HIP(hipEventRecord(ev[2], st));
+        }
+        if (!launch_ycol<T>(w->ycs, ya, st)) return fail(ADI_EUNSUPPORTED, "no column kernel for this plan");
+        ADI_LAUNCHED("y_solve_update");
+        if (ev) ADI_HIP(hipEventRecord(ev[3], st));
+        return ADI_OK;
+    }
+    const dim3 yg((w->nx + 255) / 256, w->K);
+    if (!reduced) {
+        hipLaunchKernelGGL((k_yreduce<T>), yg, dim3(256), 0, st, ya);
+        ADI_LAUNCHED("y_reduce");
+    }
+    if (ev) ADI_HIP(hipEventRecord(ev[1], st));
+    if (!launch_yscan<T>(w->yq, w->nx, ya, st))
+        return fail(ADI_EUNSUPPORTED, "no y-interface kernel for this configuration");
+    ADI_LAUNCHED("y_scan");
+    if (ev) ADI_HIP(hipEventRecord(ev[2], st));
+    if (!launch_ysolve<T>(w->M, yg, ya, st))
+        return fail(ADI_EUNSUPPORTED, "no y-solve kernel for this chunk size");
+    ADI_LAUNCHED("y_solve_update");
+    if (ev) ADI_HIP(hipEventRecord(ev[3], st));
+    return ADI_OK;
+}
+
+// Queue one solve: x-sweep of `u` (with sources f at step k) then the y-lines
 // writing out = alpha*u + beta*v + d.  `ev` (optional) receives 5 events
-// bracketing the 4 launches.
+// bracketing the launches (x-sweep, y reduction, y interfaces, y solve).
 template <typename T>
 adi_status queue_solve(adi_wave_s* w, const void* u, const void* v, void* out, T alpha, T beta,
                        const adi_source* f, int k, T rho_scale, hipEvent_t* ev)
@@ -437,22 +542,7 @@ adi_status queue_solve(adi_wave_s* w, const void* u, const void* v, void* out, T
         return fail(ADI_EUNSUPPORTED, "no x-sweep kernel for this configuration");
     ADI_LAUNCHED("x_sweep_rhs");
     if (ev) ADI_HIP(hipEventRecord(ev[1], st));
-    YArgs<T> ya = make_y<T>(w, u, v, out, alpha, beta);
-    const dim3 yg((w->nx + 255) / 256, w->K);
-    if (!w->xp.fuse) {
-        hipLaunchKernelGGL((k_yreduce<T>), yg, dim3(256), 0, st, ya);
-        ADI_LAUNCHED("y_reduce");
-    }
-    if (ev) ADI_HIP(hipEventRecord(ev[2], st));
-    if (!launch_yscan<T>(w->yq, w->nx, ya, st))
-        return fail(ADI_EUNSUPPORTED, "no y-interface kernel for this configuration");
-    ADI_LAUNCHED("y_scan");
-    if (ev) ADI_HIP(hipEventRecord(ev[3], st));
-    if (!launch_ysolve<T>(w->M, yg, ya, st))
-        return fail(ADI_EUNSUPPORTED, "no y-solve kernel for this chunk size");
-    ADI_LAUNCHED("y_solve_update");
-    if (ev) ADI_HIP(hipEventRecord(ev[4], st));
-    return ADI_OK;
+    return queue_y<T>(w, make_y<T>(w, u, v, out, alpha, beta), w->xp.fuse != 0, ev ? ev + 1 : nullptr);
 }
 
 // The interface-system coefficients of the y-chunks depend on r only: built
@@ -669,6 +759,12 @@ adi_status set_coef(adi_wave_s* w, const void* field, double scalar, int squared
     ADI_LAUNCHED("x_pivots");
     if (measure)
         if (adi_status s = measure_rmax<T>(w)) return s;
+    if (w->ycs) {
+        if (!launch_ycol_pivots<T>(w->ycs, static_cast<const T*>(w->r), static_cast<T*>(w->qy), w->nx, w->ny, w->stream))
+            return fail(ADI_EUNSUPPORTED, "no column pivot kernel for this plan");
+        ADI_LAUNCHED("y_pivots");
+        return ADI_OK;
+    }
     return static_planes<T>(w);
 }
 
@@ -901,8 +997,11 @@ adi_status adi_wave_create(adi_wave_t* out, int nx, int ny, double h, double dt,
     const size_t es = esize(dtype);
     const size_t npts = (size_t)nx * ny;
     w->nseg = (nx + kSeg - 1) / kSeg;
+    if (!xp.fuse) w->ycs = choose_ycol(nx, ny, dtype);
+    if (w->ycs) w->qy_n = (size_t)((ny + w->ycs - 1) / w->ycs) * nx;
     if (hipMalloc(&w->r, npts * es) != hipSuccess ||
         hipMalloc(&w->qin, (size_t)ny * w->nseg * es) != hipSuccess ||
+        (w->ycs && hipMalloc(&w->qy, w->qy_n * es) != hipSuccess) ||
         (dtype == ADI_F64 && hipMalloc(&w->qin2, (size_t)ny * ((nx + 1) / 2) * es) != hipSuccess)) {
         (void)hipGetLastError();
         free_ws(w);
@@ -988,7 +1087,7 @@ adi_status adi_wave_get_info(adi_wave_t w, adi_wave_info* info)
     info->y_chunk_rows = w->M;
     info->y_chunks = w->K;
     info->kernels_per_step = w->cr ? 1 + 2 * cr_levels(w->nx) + 2 * cr_levels(w->ny)
-                                   : w->fstep ? 1 : (w->xp.fuse ? 3 : 4);
+                                   : w->fstep ? 1 : w->ycs ? 2 : (w->xp.fuse ? 3 : 4);
     info->workspace_bytes = w->bytes;
     info->fused_step = w->fstep;
     info->fused_allowed = w->fused_ok;
@@ -1065,13 +1164,17 @@ adi_status adi_wave_set_tuning(adi_wave_t w, const adi_tuning* t)
     if (t->line_solver > 0) w->cr = t->line_solver == 2 ? 1 : 0;
     if (xp.fuse && (M != w->M || !w->xp.fuse)) xp.frs = fused_rows(M);
     w->xp = xp;
+    // a y plan set by the caller is one of the chunked solve
+    const bool M_changed = M != w->M;
+    const bool chunked = w->ycs && (t->y_fused > 0 || t->y_chunk_rows > 0);
+    if (chunked) w->ycs = 0;
     if (M != w->M) {
         if (hipStreamSynchronize(w->stream) != hipSuccess)
             return fail(ADI_EHIP, "stream synchronise failed");
         w->M = M;
         if (adi_status s = alloc_chunks(w)) return s;
-        return w->dtype == ADI_F32 ? static_planes<float>(w) : static_planes<double>(w);
     }
+    if (chunked || M_changed) return w->dtype == ADI_F32 ? static_planes<float>(w) : static_planes<double>(w);
     return ADI_OK;
 }
 
@@ -1140,7 +1243,7 @@ adi_status adi_wave_profile(adi_wave_t w, void** u_prev, void** u_curr, const ad
             static const char* kFusedX = "x_sweep_rhs_y_reduce";
             int n = 0;
             for (int q = 0; q < 4; ++q) {
-                if (q == 1 && w->xp.fuse) continue;
+                if ((q == 1 && w->xp.fuse) || ((q == 1 || q == 2) && w->ycs)) continue;
                 ms_per_kernel[n] = acc[q] / nsteps;
                 if (names) names[n] = (q == 0 && w->xp.fuse) ? kFusedX : kNames[q];
                 ++n;

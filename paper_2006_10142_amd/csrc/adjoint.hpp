@@ -657,16 +657,7 @@ adi_status queue_ysolve_scaled(adi_wave_s* w, const void* rhs, void* out)
     YArgs<T> ya = make_y<T>(w, nullptr, nullptr, out, T(0), T(0));
     ya.w = static_cast<const T*>(rhs);
     ya.rhs_times_r = 1;
-    const dim3 yg((w->nx + 255) / 256, w->K);
-    hipLaunchKernelGGL((k_yreduce<T>), yg, dim3(256), 0, w->stream, ya);
-    ADI_LAUNCHED("y_reduce (adjoint)");
-    if (!launch_yscan<T>(w->yq, w->nx, ya, w->stream))
-        return fail(ADI_EUNSUPPORTED, "no y-interface kernel for this configuration");
-    ADI_LAUNCHED("y_scan (adjoint)");
-    if (!launch_ysolve<T>(w->M, yg, ya, w->stream))
-        return fail(ADI_EUNSUPPORTED, "no y-solve kernel for this chunk size");
-    ADI_LAUNCHED("y_solve (adjoint)");
-    return ADI_OK;
+    return queue_y<T>(w, ya, false, nullptr);
 }
 
 adi_source src_at(const adi_source* f, int step0, size_t es)

@@ -78,16 +78,7 @@ adi_status do_step_tdc(adi_wave_s* w, void** u_prev, void** u_curr, const void* 
         ADI_LAUNCHED("sources");
     }
     if (adi_status st = queue_xsolve<T>(w, w->rho_buf, w->w)) return st;
-    YArgs<T> ya = make_y<T>(w, *u_curr, *u_prev, *u_prev, T(2), T(-1));
-    const dim3 yg((w->nx + 255) / 256, w->K);
-    hipLaunchKernelGGL((k_yreduce<T>), yg, dim3(256), 0, w->stream, ya);
-    ADI_LAUNCHED("y_reduce");
-    if (!launch_yscan<T>(w->yq, w->nx, ya, w->stream))
-        return fail(ADI_EUNSUPPORTED, "no y-interface kernel for this configuration");
-    ADI_LAUNCHED("y_scan");
-    if (!launch_ysolve<T>(w->M, yg, ya, w->stream))
-        return fail(ADI_EUNSUPPORTED, "no y-solve kernel for this chunk size");
-    ADI_LAUNCHED("y_solve_update");
+    if (adi_status st = queue_y<T>(w, make_y<T>(w, *u_curr, *u_prev, *u_prev, T(2), T(-1)), false, nullptr)) return st;
     if (rec && rec->count > 0) {
         hipLaunchKernelGGL((k_record<T>), dim3((rec->count + 255) / 256), dim3(256), 0, w->stream,
                            static_cast<const T*>(*u_prev), rec->idx, static_cast<T*>(rec->traces), rec->count, n);

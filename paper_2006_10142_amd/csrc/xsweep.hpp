@@ -672,10 +672,11 @@ __device__ __forceinline__ void xsweep_strip(const XArgs<T>& A, const int strip,
         const int j = j0 + it;
         const bool live = j < ny;
         // prefetch
-        load_u(live ? j + 2 : -1, u2);
+        const bool more = live && it + 1 < RS;           // the strip's last row needs no next one
+        load_u(more ? j + 2 : -1, u2);
         // (FP64 line groups of 1024 threads request row j+1 of r after the scans
         // instead, where fewer registers are live: see kUmLds)
-        if constexpr (!kUmLds<T, TR>) load_rq(live ? j + 1 : -1, rn, qn);
+        if constexpr (!kUmLds<T, TR>) load_rq(more ? j + 1 : -1, rn, qn);
         // edges of row j+1 (resident since the previous row) for the next row's stencil;
         // the other parity buffer is read below, and row j-1's readers passed a barrier
         if (live && j + 1 < ny) put_halo(j + 1, u1);
@@ -738,7 +739,7 @@ __device__ __forceinline__ void xsweep_strip(const XArgs<T>& A, const int strip,
 
         T wout[E];
         xline_row<T, TR>(rho, rc, qc, L, act, lane, wv, j & 1, sh.totf, sh.totb, [&]() {
-            if constexpr (kUmLds<T, TR>) load_rq(live ? j + 1 : -1, rn, qn);
+            if constexpr (kUmLds<T, TR>) load_rq(more ? j + 1 : -1, rn, qn);
         }, wout);
         bstore8<T>(buf(A.w + (size_t)(live ? j : 0) * nx, live ? row_bytes : 0), voff, wout);
 

@@ -69,3 +69,15 @@ def test_rows_of_any_length(adw, oracle_lib, dtype, nx, ny):
     print(f"rows of any length {dtype} {nx}x{ny}", flush=True)
     err, info = increment(adw, oracle_lib, dtype, nx, ny, 4.5)
     assert info["fused_step"] == 0 and err <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("nx,ny", [(3, 128), (17, 129), (9, 255), (5, 257), (1017, 30), (1016, 513), (2041, 66),
+                                   (4081, 40), (4080, 9), (4, 1023), (33, 1025), (7, 2048), (6, 2049), (4200, 1030)])
+def test_whole_columns(adw, oracle_lib, dtype, nx, ny):
+    """Columns around the lengths where the rows a thread holds double (64 x 2^k), and
+    widths around those where the columns of a workgroup change, ragged last blocks
+    included; 2049 rows take the chunked solve."""
+    print(f"whole columns {dtype} {nx}x{ny}", flush=True)
+    err, info = increment(adw, oracle_lib, dtype, nx, ny, 4.5, one_pass=False)
+    assert info["kernels_per_step"] == (2 if ny <= 2048 else 4) and err <= TOL[dtype]
