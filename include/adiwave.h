@@ -189,8 +189,9 @@ adi_status adi_adjoint_backward(adi_wave_t w, unsigned long long record, const a
  * values (count values, already divided by h^2); rec: traces of u^{n+1} (count
  * values).  kappa_next becomes the handle's coefficient (its pivots and chunk
  * planes are rebuilt on the stream); the one-pass step stays off until the next
- * adi_wave_set_kappa, which measures the coefficient again.  Uses the exact
- * two-pass kernels; the first call allocates two nx*ny fields of workspace. */
+ * adi_wave_set_kappa, which measures the coefficient again.  Exact line solves in
+ * both directions; grids of more than 2048 columns, and those whose y-lines take the
+ * chunked solve, allocate two nx*ny fields of workspace in the first call. */
 adi_status adi_wave_step_tdc(adi_wave_t w, void** u_prev, void** u_curr, const void* kappa_prev,
                              const void* kappa_next, const adi_source* f, const adi_receivers* rec);
 

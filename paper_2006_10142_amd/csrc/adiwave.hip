@@ -219,19 +219,19 @@ int choose_ycol(int nx, int ny, adi_dtype dt)
 // threads of a block of CB columns: whole wavefronts holding ceil(ny / S) segments
 int ycol_threads(int ny, int S, int CB) { return (CB * ((ny + S - 1) / S) + 63) / 64 * 64; }
 
-template <typename T, int CB>
+template <typename T, int CB, bool DYN>
 bool launch_ycol_s(int S, const YArgs<T>& a, hipStream_t st)
 {
     constexpr bool kTop = CB < 16 || sizeof(T) == 4;      // 32-row segments fit the registers
     const int blocks = (a.nx + CB - 1) / CB;
     const dim3 grid((blocks + 7) / 8 * 8), blk(ycol_threads(a.ny, S, CB));
     switch (S) {
-        case 2: hipLaunchKernelGGL((k_ycol<T, 2, CB>), grid, blk, 0, st, a); return true;
-        case 4: hipLaunchKernelGGL((k_ycol<T, 4, CB>), grid, blk, 0, st, a); return true;
-        case 8: hipLaunchKernelGGL((k_ycol<T, 8, CB>), grid, blk, 0, st, a); return true;
-        case 16: hipLaunchKernelGGL((k_ycol<T, 16, CB>), grid, blk, 0, st, a); return true;
+        case 2: hipLaunchKernelGGL((k_ycol<T, 2, CB, DYN>), grid, blk, 0, st, a); return true;
+        case 4: hipLaunchKernelGGL((k_ycol<T, 4, CB, DYN>), grid, blk, 0, st, a); return true;
+        case 8: hipLaunchKernelGGL((k_ycol<T, 8, CB, DYN>), grid, blk, 0, st, a); return true;
+        case 16: hipLaunchKernelGGL((k_ycol<T, 16, CB, DYN>), grid, blk, 0, st, a); return true;
         case 32:
-            if constexpr (kTop) { hipLaunchKernelGGL((k_ycol<T, 32, CB>), grid, blk, 0, st, a); return true; }
+            if constexpr (kTop) { hipLaunchKernelGGL((k_ycol<T, 32, CB, DYN>), grid, blk, 0, st, a); return true; }
             return false;
     }
     return false;
@@ -242,12 +242,13 @@ bool launch_ycol_s(int S, const YArgs<T>& a, hipStream_t st)
 // of 32 rows, whose registers allow 512 threads), else 8 where that does (FP32: from
 // 128 workgroups on; 1501 x 997: 17.6 us, 18.9 with 16, 21.2 with 4), else 4 (1024^2
 // FP64: 20.1 us, 21.6 with 8; 500 x 2040 FP32 19.9, 22.2 with 8).
-template <typename T>
+template <typename T, bool DYN = false>
 bool launch_ycol(int S, const YArgs<T>& a, hipStream_t st)
 {
-    if (a.nx > 16 * 255 && (sizeof(T) == 4 || S <= 16)) return launch_ycol_s<T, 16>(S, a, st);
-    if (a.nx > 8 * (sizeof(T) == 4 ? 127 : 255)) return launch_ycol_s<T, 8>(S, a, st);
-    return launch_ycol_s<T, 4>(S, a, st);
+    if constexpr (!DYN)                 // (the time-dependent step comes here with at most 2048 columns)
+        if (a.nx > 16 * 255 && (sizeof(T) == 4 || S <= 16)) return launch_ycol_s<T, 16, DYN>(S, a, st);
+    if (a.nx > 8 * (sizeof(T) == 4 ? 127 : 255)) return launch_ycol_s<T, 8, DYN>(S, a, st);
+    return launch_ycol_s<T, 4, DYN>(S, a, st);
 }
 
 template <typename T>
@@ -477,7 +478,7 @@ YArgs<T> make_y(const adi_wave_s* w, const void* u, const void* v, void* out, T 
     a.K = w->K;
     a.nxp = w->nxp;
     a.tmp = static_cast<T*>(w->w);
-    a.qy = static_cast<const T*>(w->qy);
+    a.qy = static_cast<T*>(w->qy);
     a.sum = static_cast<T*>(w->sum);
     a.X = static_cast<T*>(w->X);
     a.u = static_cast<const T*>(u);

@@ -351,16 +351,59 @@ __device__ __forceinline__ T bload1(rsrc_t rs, int voff)
 // al the run's last pivot started from 0, be = (prod q_e)^2 and ga = sum_e (prod_{i<e}
 // q_i)(prod_{i<=e} q_i) of the same pivots: al, be, ga lie in [0, 1), so neither a
 // map nor a composition of two can overflow or cancel (1 - ga al > 0 for any r).
+template <typename M>
 struct PivotMap {
-    double al, be, ga;
+    M al, be, ga;
 };
 // the run `b` after the run `a`
-__device__ __forceinline__ PivotMap then(const PivotMap& a, const PivotMap& b)
+template <typename M>
+__device__ __forceinline__ PivotMap<M> then(const PivotMap<M>& a, const PivotMap<M>& b)
 {
-    const double m = nr_rcp(1.0 - b.ga * a.al);
+    const M m = nr_rcp(M(1) - b.ga * a.al);
     return {b.al + b.be * (a.al * m), a.be * b.be * (m * m), a.ga + a.be * (b.ga * m)};
 }
-__device__ __forceinline__ double pivot_after(const PivotMap& a, double q) { return a.al + a.be * (q * nr_rcp(1.0 - a.ga * q)); }
+template <typename M>
+__device__ __forceinline__ M pivot_after(const PivotMap<M>& a, M q)
+{
+    return a.al + a.be * (q * nr_rcp(M(1) - a.ga * q));
+}
+// the map of the run of nodes r[0 .. N), and of every run of lanes 0 .. l of a wavefront
+template <typename M, int N>
+__device__ __forceinline__ PivotMap<M> pivot_map(const M (&r)[N])
+{
+    M q = M(0), pi = M(1), ga = M(0);
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        (void)pivot_step<M>(r[e], q);
+        const M p = pi * q;
+        ga = fma_rn(pi, p, ga);
+        pi = p;
+    }
+    return {q, pi * pi, ga};
+}
+template <typename M>
+__device__ __forceinline__ PivotMap<M> pivot_scan(PivotMap<M> m, int lane)
+{
+#pragma unroll
+    for (int s = 1; s < 64; s <<= 1) {
+        const PivotMap<M> o{__shfl_up(m.al, s), __shfl_up(m.be, s), __shfl_up(m.ga, s)};
+        if (lane >= s) m = then(o, m);
+    }
+    return m;
+}
+// pivot entering this thread's segment of a line of NW wavefronts (m: the segment's
+// map); tot: the wavefronts' totals, one per wavefront of the line.  Synchronises.
+template <typename M, int NW>
+__device__ __forceinline__ M entry_pivot(PivotMap<M> m, PivotMap<M> (&tot)[NW], int lane, int wv)
+{
+    m = pivot_scan(m, lane);
+    if (lane == 63) tot[wv] = m;
+    __syncthreads();
+    M q = M(0);                            // entering this wavefront
+    for (int k = 0; k < wv; ++k) q = pivot_after(tot[k], q);
+    const PivotMap<M> before{__shfl_up(m.al, 1), __shfl_up(m.be, 1), __shfl_up(m.ga, 1)};
+    return lane > 0 ? pivot_after(before, q) : q;
+}
 
 // pivot entering every 8-node segment of every row (qin: the x-sweep's segments), and,
 // with qin2, every 2-node segment (the lanes of the FP64 one-pass strips): TR threads
@@ -374,9 +417,8 @@ __global__ void __launch_bounds__(TR >= 256 ? TR : 256)
     k_xpivots(const T* __restrict__ r, T* __restrict__ qin, T* __restrict__ qin2, int nx, int ny, int nseg)
 {
     constexpr int NW = TR / 64, G = (TR >= 256 ? TR : 256) / TR;
-    __shared__ PivotMap tot[G][NW];
+    __shared__ PivotMap<double> tot[G][NW];
     const int g = threadIdx.x / TR, t = threadIdx.x - g * TR;
-    const int lane = t & 63, wv = t >> 6;
     const int j = blockIdx.x * G + g;
     const bool act = j < ny && t < nseg;
     T rv[kSeg];
@@ -384,29 +426,9 @@ __global__ void __launch_bounds__(TR >= 256 ? TR : 256)
     double rr[kSeg];
 #pragma unroll
     for (int e = 0; e < kSeg; ++e) rr[e] = (double)rv[e];   // 0 past the row's end
-    PivotMap m{0.0, 1.0, 0.0};
-    {
-        double q = 0.0, pi = 1.0, ga = 0.0;
-#pragma unroll
-        for (int e = 0; e < kSeg; ++e) {
-            (void)pivot_step<double>(rr[e], q);
-            const double p = pi * q;
-            ga = fma_rn(pi, p, ga);
-            pi = p;
-        }
-        if (act) m = {q, pi * pi, ga};
-    }
-#pragma unroll
-    for (int s = 1; s < 64; s <<= 1) {
-        const PivotMap o{__shfl_up(m.al, s), __shfl_up(m.be, s), __shfl_up(m.ga, s)};
-        if (lane >= s) m = then(o, m);
-    }
-    if (lane == 63) tot[g][wv] = m;
-    __syncthreads();
-    double q = 0.0;                        // entering this wavefront
-    for (int k = 0; k < wv; ++k) q = pivot_after(tot[g][k], q);
-    const PivotMap before{__shfl_up(m.al, 1), __shfl_up(m.be, 1), __shfl_up(m.ga, 1)};
-    if (lane > 0) q = pivot_after(before, q);
+    PivotMap<double> m{0.0, 1.0, 0.0};
+    if (act) m = pivot_map(rr);
+    double q = entry_pivot(m, tot[g], t & 63, t >> 6);
     if (!act) return;
     qin[(size_t)j * nseg + t] = (T)q;
     if (qin2) {

@@ -55,13 +55,9 @@ __global__ void __launch_bounds__(kYcP * kYpCB) k_ycol_pivots(const T* __restric
     sh.m[2][p][col] = ga;
     __syncthreads();
     for (int c = wv; c < CB; c += nw) {
-        PivotMap m{0.0, 1.0, 0.0};
+        PivotMap<double> m{0.0, 1.0, 0.0};
         if (lane < P) m = {sh.m[0][lane][c], sh.m[1][lane][c], sh.m[2][lane][c]};
-#pragma unroll
-        for (int s = 1; s < 64; s <<= 1) {
-            const PivotMap o{__shfl_up(m.al, s), __shfl_up(m.be, s), __shfl_up(m.ga, s)};
-            if (lane >= s) m = then(o, m);
-        }
+        m = pivot_scan(m, lane);
         if (lane + 1 < P) sh.m[0][lane + 1][c] = m.al;   // al: the run's last pivot from 0
         if (lane == 0) sh.m[0][0][c] = 0.0;
     }
@@ -69,7 +65,9 @@ __global__ void __launch_bounds__(kYcP * kYpCB) k_ycol_pivots(const T* __restric
     if (i < nx && p * S < ny) qy[(size_t)p * nx + i] = (T)sh.m[0][p][col];
 }
 
-template <typename T, int S, int CB>
+// DYN: r is new (the time-dependent step): the entry pivots are formed here and kept in
+// A.qy, and the receivers of the new level are recorded.
+template <typename T, int S, int CB, bool DYN = false>
 __global__ void __launch_bounds__(kYcP * CB) k_ycol(YArgs<T> A)
 {
     constexpr int ES = (int)sizeof(T);
@@ -94,7 +92,10 @@ __global__ void __launch_bounds__(kYcP * CB) k_ycol(YArgs<T> A)
         q[k] = fr_load1<T, 0>(rr, off + k * rowb, 0);
         g[k] = fr_load1<T, 0>(rw, off + k * rowb, 0);
     }
-    T qq = fr_load1<T, 0>(buf(A.qy, (ny + S - 1) / S * rowb), i < nx ? (p * nx + i) * ES : kFuOOB, 0);
+    const rsrc_t rq = buf(A.qy, (ny + S - 1) / S * rowb);
+    const int qoff = i < nx ? (p * nx + i) * ES : kFuOOB;
+    T qq = T(0);
+    if constexpr (!DYN) qq = fr_load1<T, 0>(rq, qoff, 0);
     T uu[PRE ? S : 1], vv[PRE ? S : 1];
     if constexpr (PRE) {
 #pragma unroll
@@ -102,6 +103,23 @@ __global__ void __launch_bounds__(kYcP * CB) k_ycol(YArgs<T> A)
             uu[k] = fr_load1<T, 0>(ru, off + k * rowb, 0);
             vv[k] = fr_load1<T, 0>(rv, off + k * rowb, 0);
         }
+    }
+    if constexpr (DYN) {
+        const PivotMap<T> own = pivot_map(q);
+        sh.m[0][p][col] = own.al;
+        sh.m[1][p][col] = own.be;
+        sh.m[2][p][col] = own.ga;
+        __syncthreads();
+        for (int c = wv; c < CB; c += nw) {
+            PivotMap<T> m{T(0), T(1), T(0)};
+            if (lane < P) m = {sh.m[0][lane][c], sh.m[1][lane][c], sh.m[2][lane][c]};
+            m = pivot_scan(m, lane);
+            if (lane < P) sh.m[3][lane][c] = m.al;          // the run's last pivot from 0
+        }
+        __syncthreads();
+        if (p > 0) qq = sh.m[3][p - 1][col];
+        fr_store1<T, 0>(qq, rq, qoff, 0);
+        __syncthreads();                                    // m[0 .. 3] are written again
     }
     const bool sc = A.rhs_times_r != 0;
     {
@@ -168,6 +186,18 @@ __global__ void __launch_bounds__(kYcP * CB) k_ycol(YArgs<T> A)
             for (int k = S - 1; k >= 0; --k) {
                 x = fma_rn(q[k], x, g[k]);
                 fr_store1<T, 0>(fma_rn(A.beta, vv[k], A.alpha * uu[k]) + x, ro, off + k * rowb, 0);
+            }
+        }
+    }
+    if constexpr (DYN) {
+        if (A.nrec > 0) {
+            __syncthreads();                                // the block's columns are written
+            for (int k = t; k < A.nrec; k += blockDim.x) {
+                const int id = A.rec_idx[k];
+                const bool in = id >= 0 && id < nx * ny;
+                const int c = in ? id % nx - blk * CB : -1;
+                if (c >= 0 && c < CB) A.rec_out[k] = A.out[id];
+                else if (!in && blk == 0) A.rec_out[k] = T(NAN);
             }
         }
     }

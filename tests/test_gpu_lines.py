@@ -81,3 +81,39 @@ def test_whole_columns(adw, oracle_lib, dtype, nx, ny):
     print(f"whole columns {dtype} {nx}x{ny}", flush=True)
     err, info = increment(adw, oracle_lib, dtype, nx, ny, 4.5, one_pass=False)
     assert info["kernels_per_step"] == (2 if ny <= 2048 else 4) and err <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("nx,ny", [(1, 1), (9, 5), (64, 130), (511, 20), (513, 66), (1031, 17), (2048, 9), (2049, 9),
+                                   (12, 1030), (5, 2049)])
+def test_time_dependent_step(adw, oracle_lib, dtype, nx, ny):
+    """One step with a changing coefficient at r up to 4.5 (more sources than a strip
+    stages, receivers on the first and last nodes and outside the grid), then one plain
+    step on the coefficient it left; rows of more than 2048 nodes and columns of more
+    than 2048 rows take the separate launches."""
+    print(f"time-dependent step {dtype} {nx}x{ny}", flush=True)
+    nt = np.float32 if dtype == "f32" else np.float64
+    rng = np.random.default_rng(nx + 7 * ny)
+    n, h = nx * ny, 1.0 / (max(nx, ny) + 1)
+    dt = 3.0 * h                                        # r = dt^2 kappa / (2 h^2), kappa in [0.1, 1]
+    ka, kb = (rng.uniform(0.1, 1.0, (ny, nx)).astype(nt) for _ in range(2))
+    up, uc = (rng.standard_normal((ny, nx)).astype(nt) for _ in range(2))
+    src = rng.integers(0, n, 40).astype(np.int32)
+    amp = (rng.standard_normal(40) / (h * h)).astype(nt)
+    f = np.bincount(src, weights=amp.astype(np.float64), minlength=n).reshape(ny, nx)
+    rec = np.array([0, n - 1, n // 2, -1, n, n - 1], np.int32)
+    u1 = oracle_lib.step_tdc(ka, kb, up, uc, h, dt, f=f)
+    u2 = oracle_lib.run(kb.astype(np.float64), uc, u1, h, dt, 1)[1]
+
+    def cu(a):
+        return torch.from_numpy(a).cuda()
+    wave = adw.Wave(nx, ny, h, dt, kappa=1.0, dtype=torch.float32 if dtype == "f32" else torch.float64)
+    tr = cu(np.zeros(rec.size, nt))
+    a, b = wave.step_tdc(cu(up), cu(uc), cu(ka), cu(kb), src_idx=cu(src), src_amp=cu(amp), rec_idx=cu(rec), traces=tr)
+    got1 = b.cpu().numpy()
+    a, b = wave.step(a, b, 1)
+    got2, tr = b.cpu().numpy(), tr.cpu().numpy()
+    wave.close()
+    assert rel_l2(got1, u1) <= TOL[dtype] and rel_l2(got2, u2) <= TOL[dtype]
+    inside = [0, 1, 2, 5]
+    assert np.array_equal(tr[inside], got1.ravel()[rec[inside]]) and np.isnan(tr[[3, 4]]).all()
