@@ -58,7 +58,7 @@ struct XPlan { int tr, rs, fuse, frs; };   // frs: rows of a fused strip (whole 
 // x-sweep: smallest line group whose 8 * tr nodes cover nx
 bool choose_x(int nx, adi_dtype, XPlan& p)
 {
-    static const int cand[] = {64, 128, 256, 1024};
+    static const int cand[] = {64, 128, 256, 512, 1024};
     for (int tr : cand)
         if (8LL * tr >= nx) { p.tr = tr; return true; }
     return false;
@@ -74,6 +74,7 @@ bool fuse_fits(int tr, adi_dtype dt)
         case 64: return 4 * sizeof(XShared<T, 64, true>);
         case 128: return 2 * sizeof(XShared<T, 128, true>);
         case 256: return sizeof(XShared<T, 256, true>);
+        case 512: return sizeof(XShared<T, 512, true>);
         case 1024: return sizeof(XShared<T, 1024, true>);
         default: return SIZE_MAX;
         }
@@ -130,7 +131,7 @@ template <typename T, int TR>
 bool launch_x_f(bool fuse, int grid, const XArgs<T>& a, hipStream_t st)
 {
     if (fuse) {
-        if constexpr (sizeof(T) == 8 && TR > 256) return false;
+        if constexpr (sizeof(T) == 8 && TR > 512) return false;
         else { launch_x1<T, TR, true>(grid, a, st); return true; }
     }
     launch_x1<T, TR, false>(grid, a, st);
@@ -144,6 +145,7 @@ bool launch_x(const XPlan& p, int grid, const XArgs<T>& a, hipStream_t st)
         case 64: return launch_x_f<T, 64>(p.fuse != 0, grid, a, st);
         case 128: return launch_x_f<T, 128>(p.fuse != 0, grid, a, st);
         case 256: return launch_x_f<T, 256>(p.fuse != 0, grid, a, st);
+        case 512: return launch_x_f<T, 512>(p.fuse != 0, grid, a, st);
         case 1024: return launch_x_f<T, 1024>(p.fuse != 0, grid, a, st);
     }
     return false;
@@ -1111,7 +1113,7 @@ adi_status adi_wave_set_tuning(adi_wave_t w, const adi_tuning* t)
     if (t->x_rows_per_strip > 0) xp.rs = t->x_rows_per_strip;
     if (t->y_fused == 1) xp.fuse = 1;
     if (t->y_fused == 2) xp.fuse = 0;
-    if (xp.tr != 64 && xp.tr != 128 && xp.tr != 256 && xp.tr != 1024)
+    if (t->x_threads_per_line > 0 && xp.tr != 64 && xp.tr != 128 && xp.tr != 256 && xp.tr != 1024)
         return fail(ADI_EINVAL, "x_threads_per_line must be 64, 128, 256 or 1024");
     if (8LL * xp.tr < w->nx) return fail(ADI_EINVAL, "8 * x_threads_per_line must cover nx");
     if (xp.fuse && !fuse_fits(xp.tr, w->dtype))

@@ -625,6 +625,7 @@ adi_status queue_xsolve(adi_wave_s* w, const void* rhs, void* out)
         case 64: launch_xsolve1<T, 64>(grid, a, w->stream); break;
         case 128: launch_xsolve1<T, 128>(grid, a, w->stream); break;
         case 256: launch_xsolve1<T, 256>(grid, a, w->stream); break;
+        case 512: launch_xsolve1<T, 512>(grid, a, w->stream); break;
         case 1024: launch_xsolve1<T, 1024>(grid, a, w->stream); break;
         default: return fail(ADI_EUNSUPPORTED, "no x-solve kernel for this plan");
     }

@@ -471,6 +471,7 @@ adi_status adi_batch_create(adi_batch_t* out, int count, const int* nx, const in
     }
     XPlan xp{};
     if (!choose_x(max_nx, dtype, xp)) return fail(ADI_EUNSUPPORTED, "nx > 8192");
+    if (xp.tr == 512) xp.tr = 1024;   // the batch kernels come with 64, 128, 256 and 1024
     if (!batch_fits(xp.tr, dtype))
         return fail(ADI_EUNSUPPORTED, "the widest grid does not fit the batched x-sweep in LDS");
 
