@@ -142,10 +142,11 @@ adi_status adi_wave_destroy(adi_wave_t w);
  *   lambda^k = g^k + 2 lambda^{k+1} - lambda^{k+2} + dt^2 Lap(kappa mu),
  * with d^k = u^{k+1} - 2u^k + u^{k-1} and w^k = A_y d^k formed from the levels.
  * The initial levels are treated as independent of kappa.  Where the forward
- * run takes the one-pass step, the reverse pass works on the exact step's levels
- * recomputed from its checkpoints (the two steps differ by at most the one-pass
- * bound, half an ulp per step), so the gradient then depends on
- * checkpoint_every only at that level; after exact steps it does not at all. */
+ * run takes the one-pass step, the reverse pass works on that run's levels in the
+ * last two segments and on the exact step's levels, recomputed from the
+ * checkpoints, before them (the two steps differ by at most the one-pass bound,
+ * half an ulp per step), so the gradient then depends on checkpoint_every only
+ * at that level; after exact steps it does not at all. */
 
 /* Forward run of nsteps steps from (u_prev, u_curr) (not modified) with
  * sources and receivers exactly as adi_wave_step (the handle's step: the
@@ -169,10 +170,11 @@ adi_status adi_adjoint_forward(adi_wave_t w, const void* u_prev, const void* u_c
  * grad_kappa: device nx*ny, overwritten with dJ/dkappa.
  * grad_amp: device nsteps x f->count, overwritten with dJ/d(source value),
  * or NULL.  Each segment between checkpoints is recomputed once, with the
- * exact two-pass step, on a second stream the library creates for the handle,
- * overlapping the reverse pass of the segment after it (allocates
- * 2 * checkpoint_every fields and a copy of the y-chunk planes on first use or
- * growth); the call returns with all its work ordered on the handle's stream. */
+ * exact two-pass step (the last two with the forward run's step, unless that run
+ * could leave their levels in the storage below), on a second stream the library
+ * creates for the handle, overlapping the reverse pass of the segment after it
+ * (allocates 2 * checkpoint_every fields and a copy of the y-chunk planes on first
+ * use or growth); the call returns with all its work ordered on the handle's stream. */
 adi_status adi_adjoint_backward(adi_wave_t w, unsigned long long record, const adi_source* f,
                                 const adi_receivers* rec, const void* grad_traces,
                                 void* grad_kappa, void* grad_amp);

@@ -772,11 +772,12 @@ adi_status set_coef(adi_wave_s* w, const void* field, double scalar, int squared
 }
 
 template <typename T>
-FArgsT<T> make_fargs(const adi_wave_s* w, const void* u_curr, void* u_prev, const adi_source* f, int k)
+FArgsT<T> make_fargs(const adi_wave_s* w, const void* u_curr, const void* u_prev, void* out, const adi_source* f, int k)
 {
     FArgsT<T> a{};
     a.uc = static_cast<const T*>(u_curr);
-    a.up = static_cast<T*>(u_prev);
+    a.up = static_cast<T*>(const_cast<void*>(u_prev));
+    a.out = static_cast<T*>(out);
     a.r = static_cast<const T*>(w->r);
     a.qin = static_cast<const T*>(w->qin);
     a.nx = w->nx;
@@ -786,7 +787,6 @@ FArgsT<T> make_fargs(const adi_wave_s* w, const void* u_curr, void* u_prev, cons
     a.tiles_x = w->f_tx;
     a.wide = w->f_wide;
     a.tiles = w->f_tiles;
-    a.xcd_map = 1;
     a.tau2 = (T)(w->dt * w->dt);
     if (f && f->count > 0) {
         a.nsrc = f->count;
@@ -800,22 +800,30 @@ FArgsT<T> make_fargs(const adi_wave_s* w, const void* u_curr, void* u_prev, cons
     return a;
 }
 
-adi_status queue_fused(adi_wave_s* w, const void* u_curr, void* u_prev, const adi_source* f, int k)
+// out: u_prev (in place) or another 16-byte aligned buffer
+adi_status queue_fused(adi_wave_s* w, const void* u_curr, const void* u_prev, void* out, const adi_source* f, int k)
 {
+    const bool keep = out != u_prev;
     if (w->dtype == ADI_F64) {
-        FArgsT<double> a = make_fargs<double>(w, u_curr, u_prev, f, k);
+        FArgsT<double> a = make_fargs<double>(w, u_curr, u_prev, out, f, k);
         a.qin = static_cast<const double*>(w->qin2);   // entry pivot of every 2-node lane
-        hipLaunchKernelGGL(k_fusedr<double>, dim3(w->f_grid), dim3(kFrThreads64), 0, w->stream, a);
+        const dim3 g(w->f_grid), b(kFrThreads64);
+        if (keep) hipLaunchKernelGGL((k_fusedr<double, true>), g, b, 0, w->stream, a);
+        else hipLaunchKernelGGL((k_fusedr<double>), g, b, 0, w->stream, a);
         ADI_LAUNCHED("fused_step");
         return ADI_OK;
     }
-    const FArgs a = make_fargs<float>(w, u_curr, u_prev, f, k);
-    if (w->f_hs > 0)
-        hipLaunchKernelGGL(k_fusedr<float>, dim3(w->f_grid), dim3(kFrThreads), 0, w->stream, a);
-    else if (w->f_lane == 4)
-        hipLaunchKernelGGL(k_fused4, dim3(w->f_grid), dim3(1024), 0, w->stream, a);
-    else
-        hipLaunchKernelGGL(k_fused, dim3(w->f_grid), dim3(1024), 0, w->stream, a);
+    const FArgs a = make_fargs<float>(w, u_curr, u_prev, out, f, k);
+    const dim3 g(w->f_grid);
+    if (w->f_hs > 0) {
+        if (keep) hipLaunchKernelGGL((k_fusedr<float, true>), g, dim3(kFrThreads), 0, w->stream, a);
+        else hipLaunchKernelGGL((k_fusedr<float>), g, dim3(kFrThreads), 0, w->stream, a);
+    } else if (w->f_lane == 4) {
+        hipLaunchKernelGGL(k_fused4, g, dim3(1024), 0, w->stream, a);
+    } else {
+        if (keep) hipLaunchKernelGGL(k_fused<true>, g, dim3(1024), 0, w->stream, a);
+        else hipLaunchKernelGGL(k_fused<>, g, dim3(1024), 0, w->stream, a);
+    }
     ADI_LAUNCHED("fused_step");
     return ADI_OK;
 }
@@ -891,12 +899,14 @@ adi_status queue_cr_step(adi_wave_s* w, const void* u, const void* v, void* out,
 // without cyclic reduction; kStepExact = the exact two-pass step
 enum { kStepDefault = 0, kStepNoCr = 1, kStepExact = 2 };
 
+// keep (may be NULL): u^{n+1} of step k goes to keep + k fields instead of over
+// u^{n-1}, and the pointers move there (not with cyclic reduction).
 template <typename T>
 adi_status do_step(adi_wave_s* w, void** u_prev, void** u_curr, const adi_source* f,
-                   const adi_receivers* rec, int nsteps, int kind = kStepDefault)
+                   const adi_receivers* rec, int nsteps, int kind = kStepDefault, T* keep = nullptr)
 {
     const bool cr = kind == kStepDefault && w->cr;
-    const bool fused = !cr && kind != kStepExact && w->fstep && aligned16(*u_prev) && aligned16(*u_curr);
+    const bool fused = !cr && kind != kStepExact && w->fstep && aligned16(*u_prev) && aligned16(*u_curr) && aligned16(keep);
     const bool recs = rec && rec->count > 0;
     auto record = [&](int k, const void* level) -> adi_status {
         hipLaunchKernelGGL((k_record<T>), dim3((rec->count + 255) / 256), dim3(256), 0, w->stream,
@@ -913,16 +923,18 @@ adi_status do_step(adi_wave_s* w, void** u_prev, void** u_curr, const adi_source
             w->tap_idx = rec->idx;
             w->tap_out = static_cast<T*>(rec->traces) + (size_t)(k - 1) * rec->count;
         }
+        void* out = keep ? keep + (size_t)k * w->nx * w->ny : *u_prev;
         adi_status s = cr      ? queue_cr_step<T>(w, *u_curr, *u_prev, *u_prev, T(2), T(-1), f, k, T(1))
-                       : fused ? queue_fused(w, *u_curr, *u_prev, f, k)
-                               : queue_solve<T>(w, *u_curr, *u_prev, *u_prev, T(2), T(-1), f, k, T(1), nullptr);
+                       : fused ? queue_fused(w, *u_curr, *u_prev, out, f, k)
+                               : queue_solve<T>(w, *u_curr, *u_prev, out, T(2), T(-1), f, k, T(1), nullptr);
         w->tap_n = 0;
         w->tap_idx = nullptr;
         w->tap_out = nullptr;
         if (s != ADI_OK) return s;
         if (recs && cr)
             if (adi_status s2 = record(k, *u_prev)) return s2;
-        std::swap(*u_prev, *u_curr);
+        *u_prev = *u_curr;
+        *u_curr = out;
     }
     if (recs && !cr && nsteps > 0) return record(nsteps - 1, *u_curr);
     return ADI_OK;
@@ -1202,7 +1214,7 @@ adi_status adi_wave_profile(adi_wave_t w, void** u_prev, void** u_curr, const ad
         if (fused) {   // one timed range per step (one-pass step, or the whole cyclic-reduction step)
             if (hipEventRecord(e[0], w->stream) != hipSuccess) st = fail(ADI_EHIP, "hipEventRecord failed");
             if (st == ADI_OK)
-                st = !cr ? queue_fused(w, *u_curr, *u_prev, f, k)
+                st = !cr ? queue_fused(w, *u_curr, *u_prev, *u_prev, f, k)
                    : w->dtype == ADI_F32
                        ? queue_cr_step<float>(w, *u_curr, *u_prev, *u_prev, 2.f, -1.f, f, k, 1.f)
                        : queue_cr_step<double>(w, *u_curr, *u_prev, *u_prev, 2.0, -1.0, f, k, 1.0);

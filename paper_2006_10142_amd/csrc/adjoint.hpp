@@ -17,7 +17,8 @@
 // the stored levels as u^{k+1} - 2u^k + u^{k-1}, and w^k as A_y d^k =
 // d^k - r (d^k above + d^k below - 2 d^k) (zero beyond the walls), so that only
 // levels are kept.  Levels are checkpointed every K steps by the forward run,
-// which takes the handle's step (the one-pass step where it is allowed); each
+// which takes the handle's step (the one-pass step where it is allowed) and writes the
+// levels of its last two segments to the segment storage; each earlier
 // segment is recomputed once with the exact two-pass step (its kernels share the
 // device with the reverse pass far better than the one-pass step's, which fill
 // whole compute units), in reverse segment order, on a second stream into one of
@@ -495,6 +496,7 @@ struct adi_adjoint_s {
     void* ck = nullptr;          // 2 * ncheck fields: (u^{k0-1}, u^{k0}) of every segment
     void* seg = nullptr;         // 2 x K fields, one half per segment parity: levels
                                  // u^{k0+1..k0+K}
+    bool kept = false;           // seg holds the forward run's own levels of its last two segments
     void* work = nullptr;        // 6 fields: forward levels (2; during the reverse pass the
                                  // recomputation's x-sweep output), lambda (2), t, z
     void* rmap = nullptr;        // nx*ny + receiver count + ny ints: receiver map of the reverse pass
@@ -640,6 +642,11 @@ adi_status adj_forward(adi_wave_s* w, const void* u_prev, const void* u_curr, co
     char* lev = static_cast<char*>(a->work);
     void* p = lev;
     void* q = lev + F;
+    // The reverse pass starts with the last two segments: where an earlier one has left
+    // its segment storage, this run writes their levels there and they need no
+    // recomputation (at 1024^2 FP32, 18 us a step with nothing to run beside it for the
+    // last one).  Without it the reverse pass runs them again with the same step.
+    a->kept = a->seg_cap >= 2 * (size_t)K * F;
     ADI_HIP(hipMemcpyAsync(p, u_prev, F, hipMemcpyDeviceToDevice, w->stream));
     ADI_HIP(hipMemcpyAsync(q, u_curr, F, hipMemcpyDeviceToDevice, w->stream));
     // the handle's step without cyclic reduction: the one-pass step where it is
@@ -655,7 +662,8 @@ adi_status adj_forward(adi_wave_s* w, const void* u_prev, const void* u_curr, co
             rc = *rec;
             rc.traces = static_cast<char*>(rec->traces) + (size_t)c * K * rec->count * sizeof(T);
         }
-        if (adi_status s = do_step<T>(w, &p, &q, f ? &sc : nullptr, rec ? &rc : nullptr, n, kStepNoCr))
+        T* keep = a->kept && c + 2 >= a->ncheck ? static_cast<T*>(a->seg) + (size_t)K * (c & 1) * w->nx * w->ny : nullptr;
+        if (adi_status s = do_step<T>(w, &p, &q, f ? &sc : nullptr, rec ? &rc : nullptr, n, kStepNoCr, keep))
             return s;
     }
     return ADI_OK;
@@ -747,8 +755,11 @@ adi_status adj_backward(adi_wave_s* w, const adi_source* f, const adi_receivers*
     // recompute segment c on the recomputation stream with the exact two-pass step
     // (the levels are those of the forward run bit for bit when it took that step;
     // after one-pass steps they differ by at most that step's bound, half an ulp per
-    // step)
+    // step).  The last two segments are the forward run's own levels: still in the
+    // storage, or run again with its step (a second reverse pass of the same record)
+    const int last = a->ncheck - 1;
     auto recompute = [&](int c) -> adi_status {
+        if (a->kept && c + 1 >= last) return ADI_OK;
         const int k0 = 1 + c * K;
         const int n = std::min(K, S - c * K);
         hipStream_t s1 = w->stream;
@@ -758,7 +769,12 @@ adi_status adj_backward(adi_wave_s* w, const adi_source* f, const adi_receivers*
         w->X = X2;
         w->w = work;                             // the x-sweep's output (not kept)
         adi_status s = ADI_OK;
-        for (int m = 0; m < n && s == ADI_OK; ++m) {
+        if (c + 1 >= last) {
+            void *p = lev(c, 0), *q = lev(c, 1);
+            adi_source sc = src_at(f, k0 - 1, sizeof(T));
+            s = do_step<T>(w, &p, &q, f ? &sc : nullptr, nullptr, n, kStepNoCr, static_cast<T*>(lev(c, 2)));
+        }
+        for (int m = 0; m < n && s == ADI_OK && c + 1 < last; ++m) {
             adi_source sc = src_at(f, k0 - 1 + m, sizeof(T));
             s = queue_solve<T>(w, lev(c, m + 1), lev(c, m), lev(c, m + 2), T(2), T(-1), f ? &sc : nullptr, 0,
                                T(1), nullptr);
@@ -774,7 +790,6 @@ adi_status adj_backward(adi_wave_s* w, const adi_source* f, const adi_receivers*
     // c + 1 used, once the reverse pass of c + 1 is done with it
     ADI_HIP(hipEventRecord(a->ev_start, w->stream));
     ADI_HIP(hipStreamWaitEvent(a->rs, a->ev_start, 0));
-    const int last = a->ncheck - 1;
     if (adi_status s = recompute(last)) return s;
     ADI_HIP(hipEventRecord(a->ev_rc[last & 1], a->rs));
     for (int c = last; c >= 0; --c) {
@@ -816,6 +831,7 @@ adi_status adj_backward(adi_wave_s* w, const adi_source* f, const adi_receivers*
         }
         ADI_HIP(hipEventRecord(a->ev_rev[c & 1], w->stream));
     }
+    if (last > 1) a->kept = false;       // the storage was used for earlier segments
     return ADI_OK;
 }
 

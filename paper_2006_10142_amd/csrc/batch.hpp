@@ -59,7 +59,7 @@ __global__ void __launch_bounds__(1024) k_fused_batch(FBatchArgs B)
     const SimDesc<float>& S = B.sims[wi.x];
     FArgs A{};
     A.uc = S.lev[B.u_slot];
-    A.up = S.lev[B.out_slot];
+    A.up = A.out = S.lev[B.out_slot];
     A.r = S.r;
     A.qin = S.qin;
     A.nx = __builtin_amdgcn_readfirstlane(S.nx);
@@ -81,7 +81,7 @@ __global__ void __launch_bounds__(1024) k_fused4_batch(FBatchArgs B)
     const SimDesc<float>& S = B.sims[wi.x];
     FArgs A{};
     A.uc = S.lev[B.u_slot];
-    A.up = S.lev[B.out_slot];
+    A.up = A.out = S.lev[B.out_slot];
     A.r = S.r;
     A.qin = S.qin;
     A.nx = __builtin_amdgcn_readfirstlane(S.nx);
@@ -109,7 +109,7 @@ __global__ void __launch_bounds__(Fr<float>::THREADS) k_fusedr_batch(FBatchArgs 
     const SimDesc<float>& S = B.sims[wi.x];
     FArgsT<float> A{};
     A.uc = S.lev[B.u_slot];
-    A.up = S.lev[B.out_slot];
+    A.up = A.out = S.lev[B.out_slot];
     A.r = S.r;
     A.qin = S.qin;
     A.nx = __builtin_amdgcn_readfirstlane(S.nx);

@@ -47,17 +47,18 @@ constexpr int kFuNT = 2;            // buffer cache policy: non-temporal (a last
 constexpr int kFuOOB = 0x40000000;  // byte offset beyond every buffer range used here
                                     // (grids hold at most 2^27 values, 2^29 bytes)
 
+// (120 bytes for FP32: the hidden launch arguments behind it, gridDim among them, start
+// in the second 64-byte line; in a third one their load cost the 2048^2 step 0.2 us)
 template <typename T>
 struct FArgsT {
     const T* uc;         // u^n
-    T* up;               // u^{n-1} in, u^{n+1} out
+    T* up;               // u^{n-1} in, u^{n+1} out (see out)
     const T* r;
     const T* qin;        // full-line entry pivot of every 8-node x-segment
     int nx, ny, nseg;
     int wt;              // output columns per tile (multiple of 8)
     int tiles_x, tiles;  // tiles across, total tiles
     int wide;            // column strips (fusedr.hpp): strips 0..wide-1 are wt wide, the others wt - 8
-    int xcd_map;         // 1: block -> tile map that keeps neighbours on one XCD
     int hs;              // column strips (fusedr.hpp): output rows per strip segment
     T tau2;
     int nsrc;
@@ -66,6 +67,7 @@ struct FArgsT {
     int nrec;            // receivers of the previous step, sampled from uc (see rec_tap)
     const int* rec_idx;
     T* rec_out;
+    T* out;              // u^{n+1} (kernels with KEEP, and the four-node tiles): up, or a buffer of its own
 };
 using FArgs = FArgsT<float>;   // the tile kernels are FP32; the column strips take both
 
@@ -106,6 +108,8 @@ __device__ __forceinline__ float fu_load1_nt(rsrc_t rs, int voff)
 __device__ __forceinline__ int xcd_band(int b) { return (b & 7) * (int)(gridDim.x >> 3) + (b >> 3); }
 
 // one tile of one grid; every thread of the 1024-thread workgroup takes part
+// KEEP: u^{n+1} goes to a buffer of its own, through a buffer resource of its own
+template <bool KEEP = false>
 __device__ __forceinline__ void fused_tile(const FArgs& A, const int tile, FShared& sh)
 {
     const int t = threadIdx.x;
@@ -326,6 +330,7 @@ __device__ __forceinline__ void fused_tile(const FArgs& A, const int tile, FShar
     const int lim = (int)(npts * 4);
     const rsrc_t ruc = buf(A.uc, lim);
     const rsrc_t rup = buf(static_cast<const float*>(A.up), lim);
+    const rsrc_t rout = KEEP ? buf(static_cast<const float*>(A.out), lim) : rup;
     f32x4 cv[kFuUp], pv[kFuUp];
     int uoff[kFuUp];
 #pragma unroll
@@ -346,18 +351,19 @@ __device__ __forceinline__ void fused_tile(const FArgs& A, const int tile, FShar
             const float4 dv = *reinterpret_cast<const float4*>(sh.w + (kFuKy + orow) * wt + 4 * oq);
             const f32x4 o = {fma_rn(2.f, cv[s].x, -pv[s].x) + dv.x, fma_rn(2.f, cv[s].y, -pv[s].y) + dv.y,
                              fma_rn(2.f, cv[s].z, -pv[s].z) + dv.z, fma_rn(2.f, cv[s].w, -pv[s].w) + dv.w};
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, o), rup, uoff[s], 0, kFuNT);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, o), rout, uoff[s], 0, kFuNT);
         }
     }
 }
 
+template <bool KEEP = false>
 __global__ void __launch_bounds__(1024) k_fused(FArgs A)
 {
     __shared__ FShared sh;
     rec_tap<float>(A.uc, A.rec_idx, A.rec_out, A.nrec, (long long)A.nx * A.ny);
-    const int tile = A.xcd_map ? xcd_band(blockIdx.x) : (int)blockIdx.x;
+    const int tile = xcd_band(blockIdx.x);
     if (tile >= A.tiles) return;
-    fused_tile(A, tile, sh);
+    fused_tile<KEEP>(A, tile, sh);
 }
 
 }  // namespace adw

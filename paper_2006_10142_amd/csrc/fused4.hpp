@@ -270,7 +270,7 @@ __device__ __forceinline__ void fused4_tile(const FArgs& A, const int tile, FSha
                                  fma_rn(2.f, keep_u[it][3], -keep_p[it][3]) + dv.w};
                 const bool ok = j >= 0 && j < ny;
                 __builtin_amdgcn_raw_buffer_store_b128(
-                    __builtin_bit_cast(i32x4, o), buf(static_cast<const float*>(A.up) + (size_t)(ok ? j : 0) * nx, ok ? row_bytes : 0),
+                    __builtin_bit_cast(i32x4, o), buf(static_cast<const float*>(A.out) + (size_t)(ok ? j : 0) * nx, ok ? row_bytes : 0),
                     voff, 0, kFuNT);
             }
         }
@@ -281,7 +281,7 @@ __global__ void __launch_bounds__(1024) k_fused4(FArgs A)
 {
     __shared__ FShared4 sh;
     rec_tap<float>(A.uc, A.rec_idx, A.rec_out, A.nrec, (long long)A.nx * A.ny);
-    const int tile = A.xcd_map ? xcd_band(blockIdx.x) : (int)blockIdx.x;
+    const int tile = xcd_band(blockIdx.x);
     if (tile >= A.tiles) return;
     fused4_tile(A, tile, sh);
 }

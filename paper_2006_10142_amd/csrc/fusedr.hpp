@@ -196,7 +196,8 @@ __device__ __forceinline__ void fr_scan_bwd2(T& a, T& b, int lane)
 
 // One strip segment (blk = segment row * tiles_x + strip) of the grid A
 // describes, by the whole workgroup.
-template <typename T>
+// KEEP: u^{n+1} goes to a buffer of its own (see fused_tile)
+template <typename T, bool KEEP = false>
 __device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShared<T>& sh)
 {
     using C = FrCfg<T>;
@@ -432,6 +433,7 @@ __device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShar
     const bool ycol = yt < wt && c0 + yt < nx;
     const int lim = (int)(npts * ES);
     const rsrc_t rup = buf(static_cast<const T*>(A.up), lim);
+    const rsrc_t rout = KEEP ? buf(static_cast<const T*>(A.out), lim) : rup;
     T gcar = T(0), qcar = T(0);                              // forward carries of the column
     T pu[kFrB];                                              // u^{n-1} of the next band's output rows
     // the update operands and results of output row o of band b (row xb - KY + o):
@@ -555,7 +557,7 @@ __device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShar
                     if (o < kFrB && (kFull || out_row(b, o))) {
                         const T v = fma_rn(T(2), uu[e], C::YSPLIT ? -pu[o] : base[o]) + d;
                         const int so = kFull ? so0 + o * rowb : srow(b, o);
-                        fr_store1<T, kFuNT>(v, rup, vcol, so);
+                        fr_store1<T, kFuNT>(v, rout, vcol, so);
                     }
                 }
             }
@@ -628,16 +630,16 @@ __device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShar
     }
 }
 
-template <typename T>
+template <typename T, bool KEEP = false>
 __global__ void __launch_bounds__(Fr<T>::THREADS) k_fusedr(FArgsT<T> A)
 {
     __shared__ FRShared<T> sh;
     rec_tap<T>(A.uc, A.rec_idx, A.rec_out, A.nrec, (long long)A.nx * A.ny);
     // neighbouring strips of a segment row run on one XCD (their halo columns meet
     // in that XCD's L2): the grid is a multiple of 8 and blocks past the tiles exit
-    const int blk = A.xcd_map ? xcd_band(blockIdx.x) : (int)blockIdx.x;
+    const int blk = xcd_band(blockIdx.x);
     if (blk >= A.tiles) return;
-    fusedr_strip<T>(A, blk, sh);
+    fusedr_strip<T, KEEP>(A, blk, sh);
 }
 
 }  // namespace adw

@@ -38,3 +38,30 @@ def test_reverse_step_tiles(adw, oracle_lib, nx, ny, nsrc):
     gk, ga, tr = gpu_grad(adw, c, 5, one_pass=True)
     rk, ra, rtr = oracle_grad(oracle_lib, c)
     assert rel_l2(tr, rtr) <= 1e-5 and rel_l2(gk, rk) <= 1e-5 and rel_l2(ga, ra) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype,one_pass", [("f32", True), ("f32", False), ("f64", True), ("f64", False)])
+@pytest.mark.parametrize("nsteps", [4, 5, 9, 17])
+def test_reverse_pass_repeats(adw, dtype, one_pass, nsteps):
+    """1, 1, 2 and 4 segments of 5 steps: the first run of a handle (no segment storage
+    yet), a second reverse pass of its record, and a later run that leaves its last
+    levels in the storage, all with the same gradient bit for bit."""
+    print(f"reverse pass repeats {dtype} one_pass={one_pass} nsteps={nsteps}", flush=True)
+    c = case(dtype, nx=96, ny=40, nsteps=nsteps, nonzero=True)
+    tt = torch.float32 if dtype == "f32" else torch.float64
+
+    def cu(a):
+        return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    wave = adw.Wave(c["nx"], c["ny"], c["h"], c["dt"], kappa=cu(c["kappa"]), dtype=tt)
+    wave.set_tuning(fused_step=one_pass)
+    kw = dict(src_idx=cu(c["src_idx"]), src_amp=cu(c["amp"]), rec_idx=cu(c["rec_idx"]))
+    got = []
+    for _ in range(2):
+        tr = wave.adjoint_forward(cu(c["up"]), cu(c["uc"]), nsteps, checkpoint_every=5, **kw)
+        for _ in range(2):
+            gk, ga = wave.adjoint_backward(tr, want_amp=True, **kw)
+            got.append((tr.clone(), gk, ga))
+    torch.cuda.synchronize()
+    wave.close()
+    for g in got[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(got[0], g))
