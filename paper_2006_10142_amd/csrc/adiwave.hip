@@ -88,7 +88,7 @@ struct TPlan { int tr, s; };
 bool choose_tri(int n, adi_dtype dt, TPlan& p)
 {
     static const int cand[][2] = {{64, 2}, {64, 4}, {64, 8}, {64, 16}, {256, 8},
-                                  {256, 16}, {1024, 8}, {1024, 16}};
+                                  {256, 16}, {512, 8}, {1024, 8}, {1024, 16}};
     for (auto& c : cand) {
         if (dt == ADI_F64 && c[1] > 8) continue;
         if ((long long)c[0] * c[1] >= n) { p.tr = c[0]; p.s = c[1]; return true; }
@@ -272,8 +272,14 @@ void launch_tri1(long long batch, const TriArgs<T>& a, hipStream_t st)
 {
     constexpr int NT = TR >= 256 ? TR : 256;
     constexpr int G = NT / TR;
-    const long long grid = (batch + G - 1) / G;
-    hipLaunchKernelGGL((k_tridiag_wg<T, S, TR>), dim3((unsigned)grid), dim3(NT), 0, st, a);
+    // (a lane's segment must be read whole before its lines leave the first-level
+    // cache: 64-byte FP64 segments bypassing, 5000 systems of 4000, 206 us, else 161)
+    constexpr bool kShort = S * sizeof(T) <= 32;
+    const dim3 grid((unsigned)((batch + G - 1) / G));
+    if (kShort && tri_streams<T>(a.n, batch))
+        hipLaunchKernelGGL((k_tridiag_wg<T, S, TR, kShort>), grid, dim3(NT), 0, st, a);
+    else
+        hipLaunchKernelGGL((k_tridiag_wg<T, S, TR, false>), grid, dim3(NT), 0, st, a);
 }
 
 template <typename T, int TR>
@@ -296,6 +302,7 @@ bool launch_tri(const TPlan& p, long long batch, const TriArgs<T>& a, hipStream_
     switch (p.tr) {
         case 64: return launch_tri_s<T, 64>(p.s, batch, a, st);
         case 256: return launch_tri_s<T, 256>(p.s, batch, a, st);
+        case 512: return launch_tri_s<T, 512>(p.s, batch, a, st);
         case 1024: return launch_tri_s<T, 1024>(p.s, batch, a, st);
     }
     return false;
@@ -1310,17 +1317,14 @@ adi_status tri_check(adi_dtype dtype, int n, int batch, const void* a, const voi
 adi_status tri_run_wg(adi_dtype dtype, const TPlan& p, int n, int batch, const void* a, const void* b,
                       const void* c, void* d, long long sys_stride, long long elem_stride, hipStream_t st)
 {
-    const size_t es = esize(dtype);
-    const bool vec = aligned16(a) && aligned16(b) && aligned16(c) && aligned16(d) &&
-                     ((size_t)sys_stride * es) % 16 == 0 && ((size_t)p.s * es) % 16 == 0;
     bool ok;
     if (dtype == ADI_F32) {
         TriArgs<float> t{(const float*)a, (const float*)b, (const float*)c, (float*)d, n, batch,
-                         sys_stride, elem_stride, vec};
+                         sys_stride, elem_stride};
         ok = launch_tri<float>(p, batch, t, st);
     } else {
         TriArgs<double> t{(const double*)a, (const double*)b, (const double*)c, (double*)d, n, batch,
-                          sys_stride, elem_stride, vec};
+                          sys_stride, elem_stride};
         ok = launch_tri<double>(p, batch, t, st);
     }
     if (!ok) return fail(ADI_EUNSUPPORTED, "no batched kernel for this size");
@@ -1339,11 +1343,11 @@ adi_status tri_run_part(adi_dtype dtype, int n, int batch, const void* a, const 
 {
     if (dtype == ADI_F32) {
         TriArgs<float> t{(const float*)a, (const float*)b, (const float*)c, (float*)d, n, batch,
-                         sys_stride, elem_stride, 0};
+                         sys_stride, elem_stride};
         launch_tri_part<float>(t, (float*)scr, st);
     } else {
         TriArgs<double> t{(const double*)a, (const double*)b, (const double*)c, (double*)d, n, batch,
-                          sys_stride, elem_stride, 0};
+                          sys_stride, elem_stride};
         launch_tri_part<double>(t, (double*)scr, st);
     }
     ADI_LAUNCHED("tridiag_part");

@@ -36,39 +36,51 @@ template <> struct Vec16<double> {
     __device__ static double2 pack(const double* o) { return make_double2(o[0], o[1]); }
 };
 
-// Load the L <= S nodes of a segment starting at p (zeros beyond L).
-// vec: p is 16-byte aligned for every segment with L == S.
-template <typename T, int S>
-__device__ __forceinline__ void load_seg(const T* __restrict__ p, int L, bool vec, T (&v)[S])
+// The batched line solves read past the caches where their four arrays are far larger
+// than the last-level cache (256 MB); below, what one call or kernel leaves there serves
+// the next (4000 FP32 contiguous systems of 4000, 256 MB: 49 us, 87 bypassing; 4000 of
+// 5000, 320 MB: 75, 81; 4096 of 8192, 537 MB: 128, 113;
+// on other arrays each time 3500 of 8192: 111, 107).
+template <typename T>
+inline bool tri_streams(int n, long long batch) { return 4.0 * sizeof(T) * n * (double)batch > 4.5e8; }
+
+// S consecutive values at byte offset voff of a line, through a buffer resource of the
+// line's length, which needs no 16-byte alignment and drops what lies past the line's
+// end value by value (see bload8).  AUX: the buffer cache policy bits.
+template <typename T, int S, int AUX>
+__device__ __forceinline__ void load_seg(rsrc_t rs, int voff, T (&v)[S])
 {
     using V = Vec16<T>;
-    if constexpr (S % V::N == 0) {
-        if (vec && L == S) {
-            const typename V::type* q = reinterpret_cast<const typename V::type*>(p);
+    if constexpr (S < V::N) {
 #pragma unroll
-            for (int k = 0; k < S / V::N; ++k) V::unpack(q[k], &v[k * V::N]);
-            return;
+        for (int k = 0; k < S; ++k) v[k] = bload1<T>(rs, voff + k * (int)sizeof(T));
+    } else {
+#pragma unroll
+        for (int k = 0; k < S / V::N; ++k) {
+            const auto x = __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 16 * k, 0, AUX);
+            V::unpack(__builtin_bit_cast(typename V::type, x), &v[k * V::N]);
         }
     }
-#pragma unroll
-    for (int k = 0; k < S; ++k) v[k] = (k < L) ? p[k] : T(0);
 }
 
 template <typename T, int S>
-__device__ __forceinline__ void store_seg(T* __restrict__ p, int L, bool vec, const T (&v)[S])
+__device__ __forceinline__ void store_seg(rsrc_t rs, int voff, const T (&v)[S])
 {
     using V = Vec16<T>;
-    if constexpr (S % V::N == 0) {
-        if (vec && L == S) {
-            typename V::type* q = reinterpret_cast<typename V::type*>(p);
+    if constexpr (S < V::N) {
 #pragma unroll
-            for (int k = 0; k < S / V::N; ++k) q[k] = V::pack(&v[k * V::N]);
-            return;
+        for (int k = 0; k < S; ++k) {
+            if constexpr (sizeof(T) == 4) {
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v[k]), rs, voff + 4 * k, 0, 0);
+            } else {
+                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(i32x2, v[k]), rs, voff + 8 * k, 0, 0);
+            }
         }
-    }
+    } else {
 #pragma unroll
-    for (int k = 0; k < S; ++k)
-        if (k < L) p[k] = v[k];
+        for (int k = 0; k < S / V::N; ++k)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, V::pack(&v[k * V::N])), rs, voff + 16 * k, 0, 0);
+    }
 }
 
 // ------------------------------------------------------------- coefficient --
@@ -384,15 +396,17 @@ struct TriArgs {
     const T* a; const T* b; const T* c; T* d;
     int n, batch;
     long long sys_stride, elem_stride;
-    int vec;
 };
 
-// One workgroup (TR threads) per contiguous system, nodes in registers.
-template <typename T, int S, int TR>
+// One workgroup (TR threads) per contiguous system, nodes in registers: everything read
+// and written once.  NT: the reads bypass the caches, for calls whose arrays exceed them
+// (8192 FP32 systems of 8192: 245 us, 5.5 TB/s; 258 without; 222 on the same arrays
+// again).  By buffer accesses of any alignment: 8192 systems of 8191, value by value
+// behind bounds tests, 580 us; so, 245.
+template <typename T, int S, int TR, bool NT>
 __global__ void __launch_bounds__(TR >= 256 ? TR : 256) k_tridiag_wg(TriArgs<T> A)
 {
-    constexpr int NT = TR >= 256 ? TR : 256;
-    constexpr int G = NT / TR;
+    constexpr int G = (TR >= 256 ? TR : 256) / TR;
     __shared__ T lds_all[G * partition_lds_slots<TR>()];
     const int g = threadIdx.x / TR;
     const int t = threadIdx.x - g * TR;
@@ -401,17 +415,17 @@ __global__ void __launch_bounds__(TR >= 256 ? TR : 256) k_tridiag_wg(TriArgs<T> 
     const int lo = t * S;
     const int L = live ? max(0, min(S, A.n - lo)) : 0;
     const int nact = live ? (A.n + S - 1) / S : 0;
-    const long long off = (live ? sys : 0) * A.sys_stride + lo;
-    const bool vec = A.vec != 0;
+    const long long off = (live ? sys : 0) * A.sys_stride;
+    const int bytes = live ? A.n * (int)sizeof(T) : 0, voff = lo * (int)sizeof(T);
     T a[S], b[S], c[S], d[S];
-    load_seg<T, S>(A.a + off, L, vec, a);
-    load_seg<T, S>(A.b + off, L, vec, b);
-    load_seg<T, S>(A.c + off, L, vec, c);
-    load_seg<T, S>(A.d + off, L, vec, d);
+    load_seg<T, S, NT ? 2 : 0>(buf(A.a + off, bytes), voff, a);
+    load_seg<T, S, NT ? 2 : 0>(buf(A.b + off, bytes), voff, b);
+    load_seg<T, S, NT ? 2 : 0>(buf(A.c + off, bytes), voff, c);
+    load_seg<T, S, NT ? 2 : 0>(buf(A.d + off, bytes), voff, d);
 #pragma unroll
     for (int k = 0; k < S; ++k) if (k >= L) b[k] = T(1);
     partition_solve<T, S, TR>(d, CoefABC<T, S>{a, b, c}, L, t, nact, lds_all + g * partition_lds_slots<TR>(), 1);
-    if (L > 0) store_seg<T, S>(A.d + off, L, vec, d);
+    store_seg<T, S>(buf(A.d + off, bytes), voff, d);
 }
 
 // ------------------------------------------------------------------- copy ----

@@ -117,3 +117,45 @@ def test_time_dependent_step(adw, oracle_lib, dtype, nx, ny):
     assert rel_l2(got1, u1) <= TOL[dtype] and rel_l2(got2, u2) <= TOL[dtype]
     inside = [0, 1, 2, 5]
     assert np.array_equal(tr[inside], got1.ravel()[rec[inside]]) and np.isnan(tr[[3, 4]]).all()
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n,batch,pad,shift", [(127, 70, 0, 1), (129, 9, 3, 1), (1023, 5, 1, 3), (2050, 3, 1, 2),
+                                               (4095, 3, 0, 1), (4097, 2, 2, 1), (8191, 2, 0, 3)])
+def test_contiguous_lines_of_any_alignment(adw, oracle_lib, dtype, n, batch, pad, shift):
+    """Contiguous systems that start off 16-byte boundaries and end inside a vector, with
+    gaps between them, around the lengths where the thread group changes."""
+    print(f"contiguous lines {dtype} n={n} batch={batch} pad={pad} shift={shift}", flush=True)
+    nt = np.float32 if dtype == "f32" else np.float64
+    rng = np.random.default_rng(n)
+    size = (batch - 1) * (n + pad) + n
+    a, c, d = (rng.uniform(-1, 1, size).astype(nt) for _ in range(3))
+    b = (np.abs(a) + np.abs(c) + 0.5).astype(nt)
+    ref = oracle_lib.tridiag_batched(a, b, c, d, n, batch, n + pad, 1)
+    A, B, C, D = (torch.from_numpy(np.concatenate([np.zeros(shift, nt), v])).cuda()[shift:] for v in (a, b, c, d))
+    adw.tridiag_solve_batched(A, B, C, D, n, batch, n + pad, 1)
+    got = D.cpu().numpy()
+    assert rel_l2(got, ref) <= (1e-13 if dtype == "f64" else 1e-5)
+    gap = np.ones(size, bool)
+    for s in range(batch):
+        gap[s * (n + pad):s * (n + pad) + n] = False
+    assert np.array_equal(got[gap], d[gap])
+
+
+def test_lines_past_the_caches(adw):
+    """Line solves whose arrays exceed the last-level cache (their kernels read past it):
+    the residual of 3500 systems of 8192 unknowns, contiguous and interleaved."""
+    n, batch = 8192, 3500
+    for sys_stride, elem_stride in ((n, 1), (1, batch)):
+        print(f"lines past the caches {sys_stride} {elem_stride}", flush=True)
+        g = torch.Generator(device="cuda").manual_seed(3)
+        a, c, d0 = (torch.rand(n * batch, device="cuda", generator=g) - 0.5 for _ in range(3))
+        b = a.abs() + c.abs() + 0.5
+        d = d0.clone()
+        adw.tridiag_solve_batched(a, b, c, d, n, batch, sys_stride, elem_stride)
+        shape = (batch, n) if elem_stride == 1 else (n, batch)
+        a, b, c, d0, x = (t.view(shape) if elem_stride == 1 else t.view(shape).t() for t in (a, b, c, d0, d))
+        res = b * x - d0
+        res[:, 1:] += a[:, 1:] * x[:, :-1]
+        res[:, :-1] += c[:, :-1] * x[:, 1:]
+        assert (res.norm() / d0.norm()).item() <= 1e-6
