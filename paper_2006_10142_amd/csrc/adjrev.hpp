@@ -209,12 +209,8 @@ __global__ void __launch_bounds__(64 * kArWaves) k_adjoint_step(AdjArgs<float> A
         }
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            float a = fG[k], b = fQ[k];
-            fu_scan_fwd(a, b);
-            const float gin = dpp<kWaveShr1>(0.f, a);
-            float ba = inwin ? fma_rn(Ev[k], gin, H[k]) : 0.f, bb = inwin ? fQ[k] : 1.f;
-            wave_scan_bwd2(ba, bb, lane);
-            float x = dpp<kWaveShl1>(0.f, ba);
+            const float gin = enter_left<16 / E>(fG[k], fQ[k]);
+            float x = enter_right<16 / E>(inwin ? fma_rn(Ev[k], gin, H[k]) : 0.f, fQ[k]);
 #pragma unroll
             for (int e = E - 1; e >= 0; --e) {
                 x = fma_rn(qe[k][e], x, fma_rn(Qe[k][e], gin, Ge[k][e]));

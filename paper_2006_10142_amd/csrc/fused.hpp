@@ -78,6 +78,41 @@ struct FShared {
     int src_n;             // -1: more than kFuSrc in this tile
 };
 
+// The value entering each lane from the lanes before it (after it), for the truncated
+// x-lines: the maps x -> a + b x of the nearest N lanes only, composed one lane at a time
+// (t <- a + b (t of the neighbour)).  A carry from further away has crossed every pivot
+// of N lanes; with N lanes of 16 nodes or more it is below qs^16 (1.3e-14 at the largest r
+// of the FP32 one-pass step), nothing beside the step's bound of 4 qs^9.  A scan over the
+// whole wavefront takes six levels of two moved values, then readlanes across its rows of
+// 16 lanes; this takes N - 1 multiply-adds and N whole-wavefront shifts, about 40 of the
+// 165 instructions of an x-row with four nodes a lane less: 2048^2 19.6 -> 18.8 us (eight
+// nodes a lane), 8192^2 217.6 -> 213.7 us (strips), 256 simulations of 256^2 to 1024^2 410 -> 401 us, 400 adjoint
+// steps at 1024^2 12.0 -> 11.6 ms; the results did not change in any bit.
+__device__ __forceinline__ float from_left(float x)    // of the lane before; 0 into lane 0
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), kWaveShr1, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float from_right(float x)   // of the lane after; 0 into the last lane
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), kWaveShl1, 0xf, 0xf, true));
+}
+template <int N>
+__device__ __forceinline__ float enter_left(float a, float b)
+{
+    float t = a;
+#pragma unroll
+    for (int k = 1; k < N; ++k) t = fma_rn(b, from_left(t), a);
+    return from_left(t);
+}
+template <int N>
+__device__ __forceinline__ float enter_right(float a, float b)
+{
+    float t = a;
+#pragma unroll
+    for (int k = 1; k < N; ++k) t = fma_rn(b, from_right(t), a);
+    return from_right(t);
+}
+
 // inclusive suffix (lanes l..63) of two-component affine maps over the wavefront
 __device__ __forceinline__ void wave_scan_bwd2(float& a, float& b, int lane)
 {
@@ -246,13 +281,9 @@ __device__ __forceinline__ void fused_tile(const FArgs& A, const int tile, FShar
                 fG = Gv; fQ = Qv; H = h; Ev = ee;
             }
             // forward carries within the window (zero entering lane 0)
-            float a = fG, b = fQ;
-            fu_scan_fwd(a, b);
-            const float gin = dpp<kWaveShr1>(0.f, a);
+            const float gin = enter_left<16 / kSeg>(fG, fQ);
             // backward values within the window (zero leaving the last lane)
-            float ba = inwin ? fma_rn(Ev, gin, H) : 0.f, bb = inwin ? fQ : 1.f;
-            wave_scan_bwd2(ba, bb, lane);
-            const float dbelow = dpp<kWaveShl1>(0.f, ba);
+            const float dbelow = enter_right<16 / kSeg>(inwin ? fma_rn(Ev, gin, H) : 0.f, fQ);
             float wout[kSeg];
             {
                 float x = dbelow;

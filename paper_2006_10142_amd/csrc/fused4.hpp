@@ -200,13 +200,9 @@ __device__ __forceinline__ void fused4_tile(const FArgs& A, const int tile, FSha
                 fG = Gv; fQ = Qv; H = h; Ev = ee;
             }
             // forward carries within the window (zero entering lane 0)
-            float a = fG, b = fQ;
-            fu_scan_fwd(a, b);
-            const float gin = dpp<kWaveShr1>(0.f, a);
+            const float gin = enter_left<16 / kF4Seg>(fG, fQ);
             // backward values within the window (zero leaving the last lane)
-            float ba = inwin ? fma_rn(Ev, gin, H) : 0.f, bb = inwin ? fQ : 1.f;
-            wave_scan_bwd2(ba, bb, lane);
-            const float dbelow = dpp<kWaveShl1>(0.f, ba);
+            const float dbelow = enter_right<16 / kF4Seg>(inwin ? fma_rn(Ev, gin, H) : 0.f, fQ);
             float wout[kF4Seg];
             {
                 float x = dbelow;
