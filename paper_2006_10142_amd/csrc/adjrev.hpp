@@ -176,7 +176,7 @@ __global__ void __launch_bounds__(64 * kArWaves) k_adjoint_step(AdjArgs<float> A
     float zr[2][E], rr[2][E], tr[2][E];
     const int lr0 = kFuKy + 2 * wv;
     {
-        float Ge[2][E], qe[2][E], Qe[2][E], fG[2], fQ[2], H[2], Ev[2];
+        float Ge[2][E], qe[2][E], Qe[2][E];
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const int o4 = (lr0 + k) * nl + (inwin ? lane : 0);
@@ -192,28 +192,30 @@ __global__ void __launch_bounds__(64 * kArWaves) k_adjoint_step(AdjArgs<float> A
 #pragma unroll
             for (int e = 0; e < E; ++e) (void)pivot_step<float>(dpp<kRowShr + 1>(0.f, rr[k][e]), qo);
             if (lane & 1) q = qo;
-            float Gv = 0.f, Qv = 1.f, h = 0.f, ee = 0.f;
+            float Gv = 0.f, Qv = 1.f;
 #pragma unroll
             for (int e = 0; e < E; ++e) {
                 const float m = pivot_step<float>(rr[k][e], q);
-                const float P = Qv;
                 Gv = fma_rn(m, zr[k][e], q * Gv);
                 Qv = q * Qv;
-                h = fma_rn(P, Gv, h);
-                ee = fma_rn(P, Qv, ee);
                 Ge[k][e] = Gv;
                 qe[k][e] = q;
                 Qe[k][e] = Qv;
             }
-            fG[k] = Gv; fQ[k] = Qv; H[k] = h; Ev[k] = ee;
         }
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            const float gin = enter_left<16 / E>(fG[k], fQ[k]);
-            float x = enter_right<16 / E>(inwin ? fma_rn(Ev[k], gin, H[k]) : 0.f, fQ[k]);
+            const float gin = enter_left<16 / E>(Ge[k][E - 1], Qe[k][E - 1]);
+            float first = 0.f;                   // the lane's first value with nothing from below
 #pragma unroll
             for (int e = E - 1; e >= 0; --e) {
-                x = fma_rn(qe[k][e], x, fma_rn(Qe[k][e], gin, Ge[k][e]));
+                Ge[k][e] = fma_rn(Qe[k][e], gin, Ge[k][e]);
+                first = fma_rn(qe[k][e], first, Ge[k][e]);
+            }
+            float x = enter_right<16 / E>(inwin ? first : 0.f, Qe[k][E - 1]);
+#pragma unroll
+            for (int e = E - 1; e >= 0; --e) {
+                x = fma_rn(qe[k][e], x, Ge[k][e]);
                 tr[k][e] = x;
             }
             if (inwin)

@@ -263,33 +263,36 @@ __device__ __forceinline__ void fused_tile(const FArgs& A, const int tile, FShar
             }
             // segment elimination from the full-line entry pivot (zero rows decouple)
             float Ge[kSeg], qe[kSeg], Qe[kSeg];
-            float fG, fQ, H, Ev;
             {
-                float q = qc, Gv = 0.f, Qv = 1.f, h = 0.f, ee = 0.f;
+                float q = qc, Gv = 0.f, Qv = 1.f;
 #pragma unroll
                 for (int e = 0; e < kSeg; ++e) {
                     const float m = pivot_step<float>(rc[e], q);
-                    const float P = Qv;
                     Gv = fma_rn(m, rho[e], q * Gv);
                     Qv = q * Qv;
-                    h = fma_rn(P, Gv, h);
-                    ee = fma_rn(P, Qv, ee);
                     Ge[e] = Gv;
                     qe[e] = q;
                     Qe[e] = Qv;
                 }
-                fG = Gv; fQ = Qv; H = h; Ev = ee;
             }
             // forward carries within the window (zero entering lane 0)
-            const float gin = enter_left<16 / kSeg>(fG, fQ);
+            const float fQ = Qe[kSeg - 1];
+            const float gin = enter_left<16 / kSeg>(Ge[kSeg - 1], fQ);
+            // the lane's first value with nothing from below, then
             // backward values within the window (zero leaving the last lane)
-            const float dbelow = enter_right<16 / kSeg>(inwin ? fma_rn(Ev, gin, H) : 0.f, fQ);
+            float first = 0.f;
+#pragma unroll
+            for (int e = kSeg - 1; e >= 0; --e) {
+                Ge[e] = fma_rn(Qe[e], gin, Ge[e]);
+                first = fma_rn(qe[e], first, Ge[e]);
+            }
+            const float dbelow = enter_right<16 / kSeg>(inwin ? first : 0.f, fQ);
             float wout[kSeg];
             {
                 float x = dbelow;
 #pragma unroll
                 for (int e = kSeg - 1; e >= 0; --e) {
-                    x = fma_rn(qe[e], x, fma_rn(Qe[e], gin, Ge[e]));
+                    x = fma_rn(qe[e], x, Ge[e]);
                     wout[e] = x;
                 }
             }

@@ -182,33 +182,36 @@ __device__ __forceinline__ void fused4_tile(const FArgs& A, const int tile, FSha
             }
             // lane elimination from the entry pivot (zero rows decouple)
             float Ge[kF4Seg], qe[kF4Seg], Qe[kF4Seg];
-            float fG, fQ, H, Ev;
             {
-                float Gv = 0.f, Qv = 1.f, h = 0.f, ee = 0.f;
+                float Gv = 0.f, Qv = 1.f;
 #pragma unroll
                 for (int e = 0; e < kF4Seg; ++e) {
                     const float m = pivot_step<float>(rc[e], q);
-                    const float P = Qv;
                     Gv = fma_rn(m, rho[e], q * Gv);
                     Qv = q * Qv;
-                    h = fma_rn(P, Gv, h);
-                    ee = fma_rn(P, Qv, ee);
                     Ge[e] = Gv;
                     qe[e] = q;
                     Qe[e] = Qv;
                 }
-                fG = Gv; fQ = Qv; H = h; Ev = ee;
             }
             // forward carries within the window (zero entering lane 0)
-            const float gin = enter_left<16 / kF4Seg>(fG, fQ);
+            const float fQ = Qe[kF4Seg - 1];
+            const float gin = enter_left<16 / kF4Seg>(Ge[kF4Seg - 1], fQ);
+            // the lane's first value with nothing from below, then
             // backward values within the window (zero leaving the last lane)
-            const float dbelow = enter_right<16 / kF4Seg>(inwin ? fma_rn(Ev, gin, H) : 0.f, fQ);
+            float first = 0.f;
+#pragma unroll
+            for (int e = kF4Seg - 1; e >= 0; --e) {
+                Ge[e] = fma_rn(Qe[e], gin, Ge[e]);
+                first = fma_rn(qe[e], first, Ge[e]);
+            }
+            const float dbelow = enter_right<16 / kF4Seg>(inwin ? first : 0.f, fQ);
             float wout[kF4Seg];
             {
                 float x = dbelow;
 #pragma unroll
                 for (int e = kF4Seg - 1; e >= 0; --e) {
-                    x = fma_rn(qe[e], x, fma_rn(Qe[e], gin, Ge[e]));
+                    x = fma_rn(qe[e], x, Ge[e]);
                     wout[e] = x;
                 }
             }

@@ -390,46 +390,44 @@ __device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShar
                     for (int it = 0; it < XR; ++it) (void)pivot_step<T>(rb[it][b][e], q[it]);
         }
         // local elimination of each lane's nodes, then the scans across the line
-        T Ge[XR][NPL], qe[XR][NPL], Qe[XR][NPL], fG[XR], fQ[XR], H[XR], Ev[XR];
+        T Ge[XR][NPL], qe[XR][NPL], Qe[XR][NPL];
         {
-            T Gv[XR], Qv[XR], hh[XR], ee[XR];
+            T Gv[XR], Qv[XR];
 #pragma unroll
-            for (int it = 0; it < XR; ++it) { Gv[it] = T(0); Qv[it] = T(1); hh[it] = T(0); ee[it] = T(0); }
+            for (int it = 0; it < XR; ++it) { Gv[it] = T(0); Qv[it] = T(1); }
 #pragma unroll
             for (int e = 0; e < NPL; ++e) {
 #pragma unroll
                 for (int it = 0; it < XR; ++it) {
                     const T m = pivot_step<T>(P.r[it][e], q[it]);
-                    const T Pq = Qv[it];
                     Gv[it] = fma_rn(m, rho[it][e], q[it] * Gv[it]);
                     Qv[it] = q[it] * Qv[it];
-                    hh[it] = fma_rn(Pq, Gv[it], hh[it]);
-                    ee[it] = fma_rn(Pq, Qv[it], ee[it]);
                     Ge[it][e] = Gv[it];
                     qe[it][e] = q[it];
                     Qe[it][e] = Qv[it];
                 }
             }
-#pragma unroll
-            for (int it = 0; it < XR; ++it) { fG[it] = Gv[it]; fQ[it] = Qv[it]; H[it] = hh[it]; Ev[it] = ee[it]; }
         }
-        T gin[XR], below[XR];
-        if constexpr (sizeof(T) == 4) {
+        // the carry entering each lane, the lane's first value with nothing from below,
+        // and from these of the lanes after it the value below each lane
+        T first[XR], below[XR];
 #pragma unroll
-            for (int it = 0; it < XR; ++it) gin[it] = enter_left<16 / NPL>(fG[it], fQ[it]);
+        for (int it = 0; it < XR; ++it) {
+            T gin;
+            if constexpr (sizeof(T) == 4) gin = enter_left<16 / NPL>(Ge[it][NPL - 1], Qe[it][NPL - 1]);
+            else gin = fr_enter_left(Ge[it][NPL - 1], Qe[it][NPL - 1]);
+            T x = T(0);
 #pragma unroll
-            for (int it = 0; it < XR; ++it)
-                below[it] = enter_right<16 / NPL>(inwin ? fma_rn(Ev[it], gin[it], H[it]) : T(0), fQ[it]);
-        } else {
-            T ba[XR], bb[XR];
-#pragma unroll
-            for (int it = 0; it < XR; ++it) {
-                gin[it] = fr_enter_left(fG[it], fQ[it]);
-                ba[it] = inwin ? fma_rn(Ev[it], gin[it], H[it]) : T(0);
-                bb[it] = inwin ? fQ[it] : T(1);
+            for (int e = NPL - 1; e >= 0; --e) {
+                Ge[it][e] = fma_rn(Qe[it][e], gin, Ge[it][e]);
+                x = fma_rn(qe[it][e], x, Ge[it][e]);
             }
+            first[it] = inwin ? x : T(0);
+        }
 #pragma unroll
-            for (int it = 0; it < XR; ++it) below[it] = fr_enter_right(ba[it], bb[it], lane);
+        for (int it = 0; it < XR; ++it) {
+            if constexpr (sizeof(T) == 4) below[it] = enter_right<16 / NPL>(first[it], Qe[it][NPL - 1]);
+            else below[it] = fr_enter_right(first[it], inwin ? Qe[it][NPL - 1] : T(1), lane);
         }
 #pragma unroll
         for (int it = 0; it < XR; ++it) {
@@ -439,7 +437,7 @@ __device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShar
                 T x = dbelow;
 #pragma unroll
                 for (int e = NPL - 1; e >= 0; --e) {
-                    x = fma_rn(qe[it][e], x, fma_rn(Qe[it][e], gin[it], Ge[it][e]));
+                    x = fma_rn(qe[it][e], x, Ge[it][e]);
                     wout[e] = x;
                 }
             }
