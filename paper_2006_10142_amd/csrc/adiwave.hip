@@ -351,6 +351,9 @@ struct adi_wave_s {
     int f_lane_user = 0; // nodes per lane set through adi_wave_set_tuning (0: chosen here)
     int f_hs = 0;        // output rows per column-strip segment (fusedr.hpp); 0: 64-row tiles
     int f_hs_user = 0;   // set through adi_wave_set_tuning: > 0 strips, -2 tiles, 0 chosen here
+    // one-pass step where the other's does not apply (fused_plan_wide): its form and plan
+    int two_pass_user = 0;   // an x or y plan of the exact step was set through adi_wave_set_tuning
+    int fwide = 0, g_wt = 0, g_tx = 0, g_wide = 0, g_hs = 0, g_tiles = 0;
     int f4_wt = 0, f4_tx = 0, f4_tiles = 0;   // widest four-node tiles (used by the batched step)
     // cyclic-reduction baseline (line_solver = 2): coefficient arrays a, b, c
     int cr = 0;
@@ -572,12 +575,12 @@ adi_status static_planes(adi_wave_s* w)
 // One-pass step: the truncation error of a step is at most 4 qs^(K+1) max|w| (see
 // fused.hpp); it is enabled only when that is below half an ulp of the arithmetic:
 // 2^-24 for FP32 (K = 8), 2^-53 for FP64 (K = 16, the FP64 column strips).
-bool fused_bound_holds(double rm, adi_dtype dt)
+bool fused_bound_holds(double rm, adi_dtype dt, int halo = 0)
 {
     if (!(rm >= 0.0) || !std::isfinite(rm)) return false;
     const double qs = rm > 0.0 ? (1.0 + 2.0 * rm - std::sqrt(1.0 + 4.0 * rm)) / (2.0 * rm) : 0.0;
     return dt == ADI_F64 ? 4.0 * std::pow(qs, FrCfg<double>::KY + 1) <= std::ldexp(1.0, -53)
-                         : 4.0 * std::pow(qs, kFuKy + 1) <= std::ldexp(1.0, -24);
+                         : 4.0 * std::pow(qs, (halo ? halo : kFuKy) + 1) <= std::ldexp(1.0, -24);
 }
 
 constexpr int kFuT8a = 16000, kFuT8b = 30;   // eight nodes per lane (fused.hpp)
@@ -657,6 +660,81 @@ void fused_plan_f64(adi_wave_s* w)
     w->f_grid = (w->f_tiles + 7) / 8 * 8;
 }
 
+// Column strips of two widths 8 apart (at most `most` columns) that cover nx, one segment
+// per compute unit: among the strip counts from the fewest to four more, the one whose
+// largest segment has the least x-window work, (widest + 2 kx) * hs, with hs >= hmin.
+bool strip_plan(int nx, int ny, int ncu, int most, int kx, int hmin, int& wt, int& tx, int& wide, int& hs)
+{
+    long long best = -1;
+    const int tx0 = (nx + most - 1) / most;
+    for (int t = tx0; t <= tx0 + 4; ++t) {
+        const int w0 = nx / t / 8 * 8;
+        const int a = (nx - t * w0 + 7) / 8;               // strips one width step wider
+        const int wmax = a > 0 ? w0 + 8 : w0;
+        const int g = ncu / t;
+        if (w0 < 8 || wmax > most || a > t || g <= 0) continue;
+        const int h = (ny + g - 1) / g;
+        if (h < hmin) continue;
+        const long long cost = (long long)(wmax + 2 * kx) * h;
+        if (best < 0 || cost < best) {
+            best = cost;
+            wt = wmax;
+            tx = t;
+            wide = a > 0 ? a : t;
+            hs = h;
+        }
+    }
+    return best >= 0;
+}
+
+// Where the handle's one-pass step (fused_ok) does not apply, adi_wave_step takes two more
+// forms of it (FP32, automatic choice only):
+//   kWideHalo   column strips with 16 halo columns and rows, for larger r: the bound
+//               4 qs^17 max|w| is below half an ulp up to r = 0.81.
+//   kWideTiles  four-node tiles on rows that are no multiple of 16 bytes (every access of
+//               that kernel goes through a row's own descriptor), within the plain bound.
+// Both lie on one line of time that the exact step has to be above.  A pass of either costs
+// a chain of its own, 13 and 10 us, however small the grid; the exact step's two launches
+// are below that until the grid is large, and far above it once its columns are too long
+// for a short chain in the column solve.  us a step, exact -> this:
+//   kWideHalo   1024^2 14.2 -> 16.4, 4096x512 17.6 -> 21.4, 2048x1024 18.4 -> 20.2,
+//               4096x640 19.4 -> 20.6 | 2560x1000 26.4 -> 20.6, 8192x512 31.5 -> 24.2;
+//               512x1152 13.2 -> 16.4 | 1024x1280 19.2 -> 16.4, 1152^2 20.5 -> 16.3;
+//               256x1280 12.3 -> 13.8 | 64x1536 15.4 -> 13.0, 512x3072 22.6 -> 19.3;
+//               3072^2 70 -> 43, 4096^2 101 -> 67, 8192^2 393 -> 249
+//   kWideTiles  449^2 9.7 -> 10.4, 4097x65 10.2 -> 10.7 | 401x801 11.7 -> 10.7;
+//               65x1101 13.9 -> 10.3, 255x2049 19.8 -> 11.0;
+//               1501x997 17.4 -> 10.7, 2049x2047 48 -> 23, 8191^2 450 -> 257
+enum { kWideNone = 0, kWideHalo = 1, kWideTiles = 2 };
+
+// nodes from which the form is faster, by the rows of the grid
+long long wide_nodes(int form, int ny)
+{
+    if (form == kWideTiles) return ny > 1024 ? 1LL << 16 : 300000;
+    return ny >= 1536 ? 1LL << 16 : ny > 1024 ? 1250000 : ny >= 768 ? 2500000 : 3000000;
+}
+
+void fused_plan_wide(adi_wave_s* w)
+{
+    const long long n = (long long)w->nx * w->ny;
+    w->fwide = kWideNone;
+    if (w->dtype != ADI_F32 || w->fused_ok || w->fused_mode != 0 || w->two_pass_user || w->f_ncu <= 0) return;
+    if (w->nx % 4 == 0) {
+        if (n >= wide_nodes(kWideHalo, w->ny) && fused_bound_holds(w->rmax, w->dtype, FrCfg<float, 1>::KY) &&
+            strip_plan(w->nx, w->ny, w->f_ncu, Fr<float, 1>::S, FrCfg<float, 1>::KX, 1, w->g_wt, w->g_tx, w->g_wide, w->g_hs)) {
+            w->fwide = kWideHalo;
+            w->g_tiles = w->g_tx * ((w->ny + w->g_hs - 1) / w->g_hs);
+        }
+    } else if (n >= wide_nodes(kWideTiles, w->ny) && fused_bound_holds(w->rmax, w->dtype)) {
+        long long c = 0;
+        w->fwide = kWideTiles;
+        w->g_wt = fused_width(w->nx, w->ny, w->f_ncu, kF4Wmax, kFuT4a, kFuT4b, &c);
+        w->g_tx = w->g_wide = (w->nx + w->g_wt - 1) / w->g_wt;
+        w->g_hs = 0;
+        w->g_tiles = w->g_tx * ((w->ny + kFuHt - 1) / kFuHt);
+    }
+}
+
 void fused_plan(adi_wave_s* w)
 {
     const bool f64 = w->dtype == ADI_F64;
@@ -687,9 +765,9 @@ void fused_plan(adi_wave_s* w)
     // columns) that cover nx, and g = ncu / tx segments of hs rows per strip, one per
     // compute unit.  Among the strip counts from the fewest, the one whose largest
     // segment has the least x-window work ((widest + 16 halo columns) * hs) is taken,
-    // automatically when every segment then has at least kFrHmin rows (measured faster
-    // than the tiles from 4096^2 to 8192^2); or set through adi_wave_set_tuning (one
-    // width).
+    // automatically (strip_plan) when every segment then has at least kFrHmin rows
+    // (measured faster than the tiles from 4096^2 to 8192^2); or set through
+    // adi_wave_set_tuning (one width).
     w->f_hs = 0;
     long long c = 0;
     const int wt4 = fused_width(w->nx, w->ny, 0, kF4Wmax, kFuT4a, kFuT4b, &c);
@@ -697,23 +775,9 @@ void fused_plan(adi_wave_s* w)
     int swt = w->f_wt_user > 0 ? std::min(w->f_wt_user, kF4Wmax) : wt4;
     int stx = (w->nx + swt - 1) / swt, swide = stx;
     if (w->f_hs_user == 0 && w->f_ncu > 0 && w->f_wt_user == 0 && w->f_lane_user == 0) {
-        long long best = -1;
-        for (int tx = (w->nx + kF4Wmax - 1) / kF4Wmax; tx <= (w->nx + kF4Wmax - 1) / kF4Wmax + 4; ++tx) {
-            const int w0 = w->nx / tx / 8 * 8;
-            const int a = (w->nx - tx * w0 + 7) / 8;           // strips one width step wider
-            const int wmax = a > 0 ? w0 + 8 : w0;
-            const int g = w->f_ncu / tx;
-            if (w0 < 8 || wmax > kF4Wmax || a > tx || g <= 0) continue;
-            const int h = (w->ny + g - 1) / g;
-            if (h < kFrHmin) continue;
-            const long long cost = (long long)(wmax + 2 * kFuKx) * h;
-            if (best < 0 || cost < best) {
-                best = cost;
-                hs = h;
-                swt = wmax;
-                stx = tx;
-                swide = a > 0 ? a : tx;
-            }
+        int p_wt, p_tx, p_wide, p_hs;
+        if (strip_plan(w->nx, w->ny, w->f_ncu, kF4Wmax, kFuKx, kFrHmin, p_wt, p_tx, p_wide, p_hs)) {
+            swt = p_wt; stx = p_tx; swide = p_wide; hs = p_hs;
         }
     }
     if (hs > 0) {
@@ -725,6 +789,7 @@ void fused_plan(adi_wave_s* w)
         w->f_tiles = w->f_tx * ((w->ny + hs - 1) / hs);
         w->f_grid = (w->f_tiles + 7) / 8 * 8;   // a multiple of 8 for the XCD-aware block map
     }
+    fused_plan_wide(w);
 }
 
 // largest r of an FP32 handle (synchronises the stream); X is free scratch here
@@ -820,7 +885,21 @@ adi_status queue_fused(adi_wave_s* w, const void* u_curr, const void* u_prev, vo
         ADI_LAUNCHED("fused_step");
         return ADI_OK;
     }
-    const FArgs a = make_fargs<float>(w, u_curr, u_prev, out, f, k);
+    FArgs a = make_fargs<float>(w, u_curr, u_prev, out, f, k);
+    if (w->fwide) {
+        a.wt = w->g_wt;
+        a.tiles_x = w->g_tx;
+        a.wide = w->g_wide;
+        a.hs = w->g_hs;
+        a.tiles = w->g_tiles;
+        const dim3 g((w->g_tiles + 7) / 8 * 8);
+        if (w->fwide == kWideHalo)
+            hipLaunchKernelGGL((k_fusedr<float, false, 1>), g, dim3(Fr<float, 1>::THREADS), 0, w->stream, a);
+        else
+            hipLaunchKernelGGL(k_fused4, g, dim3(1024), 0, w->stream, a);
+        ADI_LAUNCHED("fused_step");
+        return ADI_OK;
+    }
     const dim3 g(w->f_grid);
     if (w->f_hs > 0) {
         if (keep) hipLaunchKernelGGL((k_fusedr<float, true>), g, dim3(kFrThreads), 0, w->stream, a);
@@ -913,7 +992,8 @@ adi_status do_step(adi_wave_s* w, void** u_prev, void** u_curr, const adi_source
                    const adi_receivers* rec, int nsteps, int kind = kStepDefault, T* keep = nullptr)
 {
     const bool cr = kind == kStepDefault && w->cr;
-    const bool fused = !cr && kind != kStepExact && w->fstep && aligned16(*u_prev) && aligned16(*u_curr) && aligned16(keep);
+    const bool one_pass = kind != kStepExact && (w->fstep || (w->fwide && kind == kStepDefault));
+    const bool fused = !cr && one_pass && aligned16(*u_prev) && aligned16(*u_curr) && aligned16(keep);
     const bool recs = rec && rec->count > 0;
     auto record = [&](int k, const void* level) -> adi_status {
         hipLaunchKernelGGL((k_record<T>), dim3((rec->count + 255) / 256), dim3(256), 0, w->stream,
@@ -1109,7 +1189,7 @@ adi_status adi_wave_get_info(adi_wave_t w, adi_wave_info* info)
     info->y_chunk_rows = w->M;
     info->y_chunks = w->K;
     info->kernels_per_step = w->cr ? 1 + 2 * cr_levels(w->nx) + 2 * cr_levels(w->ny)
-                                   : w->fstep ? 1 : w->ycs ? 2 : (w->xp.fuse ? 3 : 4);
+                                   : w->fstep || w->fwide ? 1 : w->ycs ? 2 : (w->xp.fuse ? 3 : 4);
     info->workspace_bytes = w->bytes;
     info->fused_step = w->fstep;
     info->fused_allowed = w->fused_ok;
@@ -1165,13 +1245,15 @@ adi_status adi_wave_set_tuning(adi_wave_t w, const adi_tuning* t)
         return fail(ADI_EINVAL, "column strips take four nodes per lane");
     if (t->fused_segment_rows > 0 && wt_req > kF4Wmax)
         return fail(ADI_EINVAL, "column strips are at most 240 columns wide");
+    const bool two_pass = t->x_threads_per_line > 0 || t->x_rows_per_strip > 0 || t->y_fused > 0 || t->y_chunk_rows > 0;
+    if (two_pass) w->two_pass_user = 1;
     if (t->fused_step > 0) w->fused_mode = t->fused_step;
     if (t->fused_segment_rows) w->f_hs_user = t->fused_segment_rows == -1 ? 0 : t->fused_segment_rows;
     if (t->fused_tile_cols > 0) w->f_wt_user = t->fused_tile_cols;
     if (t->fused_tile_cols == -1) w->f_wt_user = 0;
     if (t->fused_lane_nodes) w->f_lane_user = t->fused_lane_nodes > 0 ? t->fused_lane_nodes : 0;
     if (t->fused_step > 0 || t->fused_tile_cols > 0 || t->fused_tile_cols == -1 || t->fused_lane_nodes ||
-        t->fused_segment_rows)
+        t->fused_segment_rows || two_pass)
         fused_plan(w);
     if (t->line_solver < 0 || t->line_solver > 2) return fail(ADI_EINVAL, "line_solver must be 0, 1 or 2");
     if (t->line_solver == 2 && !w->cr_abc) {
@@ -1215,7 +1297,7 @@ adi_status adi_wave_profile(adi_wave_t w, void** u_prev, void** u_curr, const ad
     for (auto& e : ev)
         if (hipEventCreate(&e) != hipSuccess) { st = fail(ADI_EHIP, "hipEventCreate failed"); break; }
     const bool cr = w->cr != 0;
-    const bool fused = cr || (w->fstep && aligned16(*u_prev) && aligned16(*u_curr));
+    const bool fused = cr || ((w->fstep || w->fwide) && aligned16(*u_prev) && aligned16(*u_curr));
     for (int k = 0; k < nsteps && st == ADI_OK; ++k) {
         hipEvent_t* e = &ev[(size_t)k * 5];
         if (fused) {   // one timed range per step (one-pass step, or the whole cyclic-reduction step)

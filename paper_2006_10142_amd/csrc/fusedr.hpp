@@ -8,7 +8,8 @@
 // output rows, and walks down it in bands of B x-rows; band k holds the x-rows
 // [r0 - KY + Bk, r0 - KY + B + Bk).  (FP32: B = 24, NPL = 4 nodes per lane,
 // KX = KY = 8 halo columns and rows, S = 240; FP64: B = 24, NPL = 2, KX = KY = 16,
-// S = 64.)
+// S = 64; FP32 beyond r = 0.18, up to 0.81, FrCfg<float, 1>: KX = KY = 16, S = 208, and
+// PB = 12, where qs < 0.36 leaves qs^25 < 1e-11 of a start value.)
 //   x-role (XW = 12 wavefronts): XR = B / XW = 2 x-rows each per band, NPL nodes
 //     per lane, on the window [c0 - KX, c0 + Wt + KX) as fused4.hpp, except for the
 //     entry pivots (below); w, r and u^n of the central columns go to rings in LDS.
@@ -55,8 +56,9 @@
 
 namespace adw {
 
-template <typename T> struct FrCfg;
-template <> struct FrCfg<float> {
+// H: 0 = the halo of fused.hpp; 1 (FP32) = 16 columns and rows, for larger r
+template <typename T, int H = 0> struct FrCfg;
+template <> struct FrCfg<float, 0> {
     static constexpr int B = 24;           // x-rows per band
     static constexpr int NPL = kF4Seg;     // nodes per lane (one 16-byte vector)
     static constexpr int KX = kFuKx;       // x-halo columns on each side
@@ -66,8 +68,23 @@ template <> struct FrCfg<float> {
     static constexpr int PB = 6;           // nodes a lane rebuilds its entry pivot over
     static constexpr int KG = 8;           // y-role rows per group of LDS reads
     static constexpr bool YSPLIT = false;  // the y-role's wavefronts share the strip's columns
+    static constexpr int NEAR = 16;        // nodes an x-line carry is composed over
+    static constexpr int SMAX = 64 * NPL;
 };
-template <> struct FrCfg<double> {
+template <> struct FrCfg<float, 1> {
+    static constexpr int B = 24;
+    static constexpr int NPL = kF4Seg;
+    static constexpr int KX = 16;
+    static constexpr int KY = 16;
+    static constexpr int YW = 4;
+    static constexpr int XW = 12;
+    static constexpr int PB = 12;
+    static constexpr int KG = 8;
+    static constexpr bool YSPLIT = false;
+    static constexpr int NEAR = 24;        // nodes an x-line carry is composed over
+    static constexpr int SMAX = 208;       // three rings of 64 rows in 160 KiB
+};
+template <> struct FrCfg<double, 0> {
     static constexpr int B = 24;           // 12 x-role wavefronts of two x-rows
     static constexpr int NPL = 2;
     static constexpr int KX = 16;
@@ -77,13 +94,15 @@ template <> struct FrCfg<double> {
     static constexpr int PB = 8;           // not used: the lanes read their entry pivots
     static constexpr int KG = 8;
     static constexpr bool YSPLIT = true;   // the y-role split by stage, strips of at most 64 columns
+    static constexpr int NEAR = 32;
+    static constexpr int SMAX = 64 * NPL;
 };
 
 constexpr int kFrHmin = 256;               // shortest strip segment the plan picks by itself
 
-template <typename T>
+template <typename T, int H = 0>
 struct Fr {
-    using C = FrCfg<T>;
+    using C = FrCfg<T, H>;
     static constexpr int XR = C::B / C::XW;                    // x-rows per x-role wavefront per band (2)
     static_assert(C::B % C::XW == 0, "every x-role wavefront takes the same number of x-rows");
     // ring rows: the band being solved, the band being eliminated and the look-ahead
@@ -94,7 +113,8 @@ struct Fr {
     static_assert(!C::YSPLIT || C::YW == 2, "a split y-role has one wavefront per stage");
     // ring row stride, widest strip: the x-window's central columns, at most one per
     // y-role thread (240 / 64)
-    static constexpr int S = 64 * C::NPL - 2 * C::KX < 64 * YC ? 64 * C::NPL - 2 * C::KX : 64 * YC;
+    static constexpr int S0 = 64 * C::NPL - 2 * C::KX < 64 * YC ? 64 * C::NPL - 2 * C::KX : 64 * YC;
+    static constexpr int S = S0 < C::SMAX ? S0 : C::SMAX;
     static constexpr int THREADS = 64 * (C::YW + C::XW);       // workgroup size (1024 / 896)
     static constexpr int LB = (C::PB + C::NPL - 1) / C::NPL;   // lanes the pivot rebuild reaches back
     static constexpr int FIRST = LB * C::NPL - C::PB;          // nodes of the furthest of them skipped
@@ -106,11 +126,11 @@ constexpr int kFrS = Fr<float>::S;          // widest FP32 strip (240)
 constexpr int kFrS64 = Fr<double>::S;       // widest FP64 strip (64)
 constexpr int kFrThreads64 = Fr<double>::THREADS;
 
-template <typename T>
+template <typename T, int H = 0>
 struct FRShared {
-    alignas(16) T w[Fr<T>::R * Fr<T>::S];   // w of the x-rows, then g once the y-role has eliminated them
-    alignas(16) T r[Fr<T>::R * Fr<T>::S];   // r of the x-rows, then the y-lines' pivots
-    alignas(16) T u[Fr<T>::R * Fr<T>::S];   // u^n of the x-rows, read again by the update
+    alignas(16) T w[Fr<T, H>::R * Fr<T, H>::S];   // w of the x-rows, then g once the y-role has eliminated them
+    alignas(16) T r[Fr<T, H>::R * Fr<T, H>::S];   // r of the x-rows, then the y-lines' pivots
+    alignas(16) T u[Fr<T, H>::R * Fr<T, H>::S];   // u^n of the x-rows, read again by the update
     T src_add[kFuSrc];
     int src_row[kFuSrc];
     int src_wc[kFuSrc];
@@ -118,16 +138,17 @@ struct FRShared {
 };
 
 static_assert(sizeof(FRShared<float>) <= 160 * 1024, "the FP32 strip ring exceeds the LDS of a workgroup");
+static_assert(sizeof(FRShared<float, 1>) <= 160 * 1024, "the wide-halo strip ring exceeds the LDS of a workgroup");
 static_assert(sizeof(FRShared<double>) <= 160 * 1024, "the FP64 strip ring exceeds the LDS of a workgroup");
 
 // x-role inputs of one band: u^n rows j-1 .. j+XR and r rows j .. j+XR-1 of the
 // wavefront's x-rows, with the window-edge values
-template <typename T>
+template <typename T, int H = 0>
 struct FRIn {
-    T u[Fr<T>::XR + 2][FrCfg<T>::NPL];
-    T e[Fr<T>::XR + 2];
-    T r[Fr<T>::XR][FrCfg<T>::NPL];
-    T q[Fr<T>::XR];      // FP64: the lane's full-line entry pivot of each x-row
+    T u[Fr<T, H>::XR + 2][FrCfg<T>::NPL];
+    T e[Fr<T, H>::XR + 2];
+    T r[Fr<T, H>::XR][FrCfg<T>::NPL];
+    T q[Fr<T, H>::XR];      // FP64: the lane's full-line entry pivot of each x-row
 };
 
 // NPL values of T at byte offset vo + so through a buffer resource (16 bytes)
@@ -217,12 +238,12 @@ __device__ __forceinline__ double fr_enter_right(double a, double b, int lane)
 // One strip segment (blk = segment row * tiles_x + strip) of the grid A
 // describes, by the whole workgroup.
 // KEEP: u^{n+1} goes to a buffer of its own (see fused_tile)
-template <typename T, bool KEEP = false>
-__device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShared<T>& sh)
+template <typename T, bool KEEP = false, int H = 0>
+__device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShared<T, H>& sh)
 {
-    using C = FrCfg<T>;
+    using C = FrCfg<T, H>;
     constexpr int NPL = C::NPL, KX = C::KX, KY = C::KY, KG = C::KG, kFrB = C::B;
-    constexpr int R = Fr<T>::R, S = Fr<T>::S, XR = Fr<T>::XR;
+    constexpr int R = Fr<T, H>::R, S = Fr<T, H>::S, XR = Fr<T, H>::XR;
     constexpr int ES = (int)sizeof(T);
     const int t = threadIdx.x;
     const int lane = t & 63;
@@ -291,20 +312,20 @@ __device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShar
     const int qoff = voff == kFuOOB ? kFuOOB : voff / 2;
     // pieces of band k's inputs: u^n row j-1+i (with its window-edge values), and
     // r row j+i, j = the wavefront's first x-row of band k
-    auto load_u = [&](int k, int i, FRIn<T>& P) {
+    auto load_u = [&](int k, int i, FRIn<T, H>& P) {
         const int jj = xr_lo + kFrB * k + XR * xw - 1 + i;
         const bool ok = row_ok(jj) && k < nb;
         const int so = ok ? jj * row_bytes : 0;
         fr_load_vec<T>(ru_all, ok ? voff : kFuOOB, so, P.u[i]);
         P.e[i] = fr_load1<T, 0>(ru_all, ok ? eoff : kFuOOB, so);
     };
-    auto load_r = [&](int k, int i, FRIn<T>& P) {
+    auto load_r = [&](int k, int i, FRIn<T, H>& P) {
         const int jj = xr_lo + kFrB * k + XR * xw + i;
         const bool ok = row_ok(jj) && k < nb;
         fr_load_vec<T>(rr_all, ok ? voff : kFuOOB, ok ? jj * row_bytes : 0, P.r[i]);
         if constexpr (sizeof(T) == 8) P.q[i] = fr_load1<T, 0>(rq_all, ok ? qoff : kFuOOB, ok ? jj * (row_bytes / 2) : 0);
     };
-    auto load_band = [&](int k, FRIn<T>& P) {
+    auto load_band = [&](int k, FRIn<T, H>& P) {
 #pragma unroll
         for (int i = 0; i < XR + 2; ++i) load_u(k, i, P);
 #pragma unroll
@@ -314,7 +335,7 @@ __device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShar
     // central columns to the ring.  The wavefront's XR rows are independent: each
     // stage below runs for all of them before the next, so that their dependency
     // chains (the pivot recurrences, the scans) interleave.
-    auto x_band = [&](int k, int sb, const FRIn<T>& P) {
+    auto x_band = [&](int k, int sb, const FRIn<T, H>& P) {
         T rho[XR][NPL];
 #pragma unroll
         for (int it = 0; it < XR; ++it) {
@@ -369,7 +390,7 @@ __device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShar
 #pragma unroll
             for (int it = 0; it < XR; ++it) q[it] = P.q[it];
         } else {
-            constexpr int LB = Fr<T>::LB, FIRST = Fr<T>::FIRST;
+            constexpr int LB = Fr<T, H>::LB, FIRST = Fr<T, H>::FIRST;
             T rb[XR][LB][NPL];
 #pragma unroll
             for (int it = 0; it < XR; ++it) {
@@ -414,7 +435,7 @@ __device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShar
 #pragma unroll
         for (int it = 0; it < XR; ++it) {
             T gin;
-            if constexpr (sizeof(T) == 4) gin = enter_left<16 / NPL>(Ge[it][NPL - 1], Qe[it][NPL - 1]);
+            if constexpr (sizeof(T) == 4) gin = enter_left<C::NEAR / NPL>(Ge[it][NPL - 1], Qe[it][NPL - 1]);
             else gin = fr_enter_left(Ge[it][NPL - 1], Qe[it][NPL - 1]);
             T x = T(0);
 #pragma unroll
@@ -426,7 +447,7 @@ __device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShar
         }
 #pragma unroll
         for (int it = 0; it < XR; ++it) {
-            if constexpr (sizeof(T) == 4) below[it] = enter_right<16 / NPL>(first[it], Qe[it][NPL - 1]);
+            if constexpr (sizeof(T) == 4) below[it] = enter_right<C::NEAR / NPL>(first[it], Qe[it][NPL - 1]);
             else below[it] = fr_enter_right(first[it], inwin ? Qe[it][NPL - 1] : T(1), lane);
         }
 #pragma unroll
@@ -638,7 +659,7 @@ __device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShar
         // the loads are issued on every path (rows past the strip's last band read
         // as zero or are never used), so the outstanding-load count is the same at
         // every point of the loop and each wait covers only the band it needs
-        FRIn<T> PA, PB;
+        FRIn<T, H> PA, PB;
         load_band(0, PA);
         load_band(1, PB);
         int sb = 0;
@@ -655,16 +676,16 @@ __device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShar
     }
 }
 
-template <typename T, bool KEEP = false>
-__global__ void __launch_bounds__(Fr<T>::THREADS) k_fusedr(FArgsT<T> A)
+template <typename T, bool KEEP = false, int H = 0>
+__global__ void __launch_bounds__((Fr<T, H>::THREADS)) k_fusedr(FArgsT<T> A)
 {
-    __shared__ FRShared<T> sh;
+    __shared__ FRShared<T, H> sh;
     rec_tap<T>(A.uc, A.rec_idx, A.rec_out, A.nrec, (long long)A.nx * A.ny);
     // neighbouring strips of a segment row run on one XCD (their halo columns meet
     // in that XCD's L2): the grid is a multiple of 8 and blocks past the tiles exit
     const int blk = xcd_band(blockIdx.x);
     if (blk >= A.tiles) return;
-    fusedr_strip<T, KEEP>(A, blk, sh);
+    fusedr_strip<T, KEEP, H>(A, blk, sh);
 }
 
 }  // namespace adw
