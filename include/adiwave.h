@@ -354,8 +354,8 @@ typedef struct {
     int kernels_per_step;     /* launches queued per ADI step (exact step: 2 with whole columns
                                  in one launch, 3 or 4 with the chunked y-solve); 1 with
                                  fused_step 0: a one-pass form for what fused_allowed leaves
-                                 out (FP32: r_max <= 0.81 on strips with a wider halo, or rows
-                                 of any length within r_max <= 0.18), which adi_wave_step
+                                 out (rows of any length within its r_max; FP32 with r_max <=
+                                 0.81 on strips with a wider halo), which adi_wave_step
                                  takes on grids where it is the faster one unless fused_step
                                  or a plan of the exact step is set */
     size_t workspace_bytes;   /* device bytes owned by the handle */

@@ -687,52 +687,69 @@ bool strip_plan(int nx, int ny, int ncu, int most, int kx, int hmin, int& wt, in
     return best >= 0;
 }
 
-// Where the handle's one-pass step (fused_ok) does not apply, adi_wave_step takes two more
-// forms of it (FP32, automatic choice only):
-//   kWideHalo   column strips with 16 halo columns and rows, for larger r: the bound
+// Where the handle's one-pass step (fused_ok) does not apply, adi_wave_step takes three
+// more forms of it (automatic choice only):
+//   kWideHalo   FP32 column strips with 16 halo columns and rows, for larger r: the bound
 //               4 qs^17 max|w| is below half an ulp up to r = 0.81.
-//   kWideTiles  four-node tiles on rows that are no multiple of 16 bytes (every access of
-//               that kernel goes through a row's own descriptor), within the plain bound.
-// Both lie on one line of time that the exact step has to be above.  A pass of either costs
-// a chain of its own, 13 and 10 us, however small the grid; the exact step's two launches
-// are below that until the grid is large, and far above it once its columns are too long
-// for a short chain in the column solve.  us a step, exact -> this:
+//   kWideTiles  FP32 four-node tiles on rows that are no multiple of 16 bytes (every access
+//               of that kernel goes through a row's own descriptor), within the plain bound.
+//   kWideRows   column strips with row descriptors on such rows, FP32 and FP64, likewise.
+// A pass of each costs a chain of its own, 13, 10 and 13 us, however small the grid; the
+// exact step's two launches are below that until the grid is large, and far above it once
+// its columns are too long for a short chain in the column solve.  us a step, exact -> this:
 //   kWideHalo   1024^2 14.2 -> 16.4, 4096x512 17.6 -> 21.4, 2048x1024 18.4 -> 20.2,
 //               4096x640 19.4 -> 20.6 | 2560x1000 26.4 -> 20.6, 8192x512 31.5 -> 24.2;
 //               512x1152 13.2 -> 16.4 | 1024x1280 19.2 -> 16.4, 1152^2 20.5 -> 16.3;
 //               256x1280 12.3 -> 13.8 | 64x1536 15.4 -> 13.0, 512x3072 22.6 -> 19.3;
-//               3072^2 70 -> 43, 4096^2 101 -> 67, 8192^2 393 -> 249
+//               3072^2 70 -> 43, 4096^2 101 -> 67, 8192^2 393 -> 249, 8191^2 448 -> 248
 //   kWideTiles  449^2 9.7 -> 10.4, 4097x65 10.2 -> 10.7 | 401x801 11.7 -> 10.7;
-//               65x1101 13.9 -> 10.3, 255x2049 19.8 -> 11.0;
-//               1501x997 17.4 -> 10.7, 2049x2047 48 -> 23, 8191^2 450 -> 257
-enum { kWideNone = 0, kWideHalo = 1, kWideTiles = 2 };
+//               65x1101 13.9 -> 10.3, 255x2049 19.8 -> 11.0; 1501x997 17.4 -> 10.8
+//   kWideRows   FP32 (tiles in the middle): 1501x997 17.4 | 10.8 | 13.4, 601^2 11.7 | 10.7 |
+//               13.4; 2049x2047 48 | 22.8 | 21.1, 4097x1025 49 | 22.6 | 20.9,
+//               8191^2 448 | 258 | 221;  FP64: 513x512 11.8 -> 17.2, 767x768 17.2 -> 17.3 |
+//               1023x1024 20.1 -> 18.4, 1501x997 29.5 -> 24.0, 4097x4095 327 -> 167;
+//               127x2001 21.7 -> 13.5, 65x4097 27.8 -> 16.8
+enum { kWideNone = 0, kWideHalo = 1, kWideTiles = 2, kWideRows = 3 };
+constexpr long long kWideRowsNodes = 4000000;   // FP32: strips instead of tiles
 
-// nodes from which the form is faster, by the rows of the grid
+// nodes from which a form (the tiles for FP32 rows of any length) is faster than the exact
+// step, by the rows of the grid
 long long wide_nodes(int form, int ny)
 {
     if (form == kWideTiles) return ny > 1024 ? 1LL << 16 : 300000;
+    if (form == kWideRows) return ny > 1024 ? 1LL << 16 : 800000;
     return ny >= 1536 ? 1LL << 16 : ny > 1024 ? 1250000 : ny >= 768 ? 2500000 : 3000000;
 }
 
 void fused_plan_wide(adi_wave_s* w)
 {
     const long long n = (long long)w->nx * w->ny;
+    const bool f64 = w->dtype == ADI_F64;
     w->fwide = kWideNone;
-    if (w->dtype != ADI_F32 || w->fused_ok || w->fused_mode != 0 || w->two_pass_user || w->f_ncu <= 0) return;
-    if (w->nx % 4 == 0) {
-        if (n >= wide_nodes(kWideHalo, w->ny) && fused_bound_holds(w->rmax, w->dtype, FrCfg<float, 1>::KY) &&
-            strip_plan(w->nx, w->ny, w->f_ncu, Fr<float, 1>::S, FrCfg<float, 1>::KX, 1, w->g_wt, w->g_tx, w->g_wide, w->g_hs)) {
-            w->fwide = kWideHalo;
-            w->g_tiles = w->g_tx * ((w->ny + w->g_hs - 1) / w->g_hs);
-        }
-    } else if (n >= wide_nodes(kWideTiles, w->ny) && fused_bound_holds(w->rmax, w->dtype)) {
+    if (w->fused_ok || w->fused_mode != 0 || w->two_pass_user || w->f_ncu <= 0) return;
+    int form = kWideNone;
+    if (fused_bound_holds(w->rmax, w->dtype)) form = f64 || n >= kWideRowsNodes ? kWideRows : kWideTiles;
+    else if (!f64 && fused_bound_holds(w->rmax, w->dtype, FrCfg<float, 1>::KY)) form = kWideHalo;
+    if (form == kWideNone || n < wide_nodes(form, w->ny)) return;
+    if (form == kWideHalo) {
+        if (!strip_plan(w->nx, w->ny, w->f_ncu, Fr<float, 1>::S, FrCfg<float, 1>::KX, 1, w->g_wt, w->g_tx, w->g_wide, w->g_hs))
+            return;
+    } else if (form == kWideTiles) {
         long long c = 0;
-        w->fwide = kWideTiles;
         w->g_wt = fused_width(w->nx, w->ny, w->f_ncu, kF4Wmax, kFuT4a, kFuT4b, &c);
         w->g_tx = w->g_wide = (w->nx + w->g_wt - 1) / w->g_wt;
         w->g_hs = 0;
-        w->g_tiles = w->g_tx * ((w->ny + kFuHt - 1) / kFuHt);
+    } else if (f64) {
+        w->g_wt = w->f_wt;
+        w->g_tx = w->f_tx;
+        w->g_wide = w->f_wide;
+        w->g_hs = w->f_hs;
+    } else if (!strip_plan(w->nx, w->ny, w->f_ncu, kF4Wmax, kFuKx, 1, w->g_wt, w->g_tx, w->g_wide, w->g_hs)) {
+        return;
     }
+    const int rows = w->g_hs > 0 ? w->g_hs : kFuHt;
+    w->g_tiles = w->g_tx * ((w->ny + rows - 1) / rows);
+    w->fwide = form;
 }
 
 void fused_plan(adi_wave_s* w)
@@ -743,6 +760,7 @@ void fused_plan(adi_wave_s* w)
     w->fstep = w->fused_ok && (w->fused_mode == 1 || (w->fused_mode == 0 && autoon)) ? 1 : 0;
     if (f64) {
         fused_plan_f64(w);
+        fused_plan_wide(w);
         return;
     }
     long long c8 = 0, c4 = 0;
@@ -872,6 +890,18 @@ FArgsT<T> make_fargs(const adi_wave_s* w, const void* u_curr, const void* u_prev
     return a;
 }
 
+// the plan of fused_plan_wide into the arguments; returns the grid
+template <typename T>
+dim3 wide_args(const adi_wave_s* w, FArgsT<T>& a)
+{
+    a.wt = w->g_wt;
+    a.tiles_x = w->g_tx;
+    a.wide = w->g_wide;
+    a.hs = w->g_hs;
+    a.tiles = w->g_tiles;
+    return dim3((w->g_tiles + 7) / 8 * 8);
+}
+
 // out: u_prev (in place) or another 16-byte aligned buffer
 adi_status queue_fused(adi_wave_s* w, const void* u_curr, const void* u_prev, void* out, const adi_source* f, int k)
 {
@@ -880,21 +910,19 @@ adi_status queue_fused(adi_wave_s* w, const void* u_curr, const void* u_prev, vo
         FArgsT<double> a = make_fargs<double>(w, u_curr, u_prev, out, f, k);
         a.qin = static_cast<const double*>(w->qin2);   // entry pivot of every 2-node lane
         const dim3 g(w->f_grid), b(kFrThreads64);
-        if (keep) hipLaunchKernelGGL((k_fusedr<double, true>), g, b, 0, w->stream, a);
+        if (w->fwide) hipLaunchKernelGGL((k_fusedr<double, false, 0, true>), wide_args(w, a), b, 0, w->stream, a);
+        else if (keep) hipLaunchKernelGGL((k_fusedr<double, true>), g, b, 0, w->stream, a);
         else hipLaunchKernelGGL((k_fusedr<double>), g, b, 0, w->stream, a);
         ADI_LAUNCHED("fused_step");
         return ADI_OK;
     }
     FArgs a = make_fargs<float>(w, u_curr, u_prev, out, f, k);
     if (w->fwide) {
-        a.wt = w->g_wt;
-        a.tiles_x = w->g_tx;
-        a.wide = w->g_wide;
-        a.hs = w->g_hs;
-        a.tiles = w->g_tiles;
-        const dim3 g((w->g_tiles + 7) / 8 * 8);
+        const dim3 g = wide_args(w, a);
         if (w->fwide == kWideHalo)
             hipLaunchKernelGGL((k_fusedr<float, false, 1>), g, dim3(Fr<float, 1>::THREADS), 0, w->stream, a);
+        else if (w->fwide == kWideRows)
+            hipLaunchKernelGGL((k_fusedr<float, false, 0, true>), g, dim3(kFrThreads), 0, w->stream, a);
         else
             hipLaunchKernelGGL(k_fused4, g, dim3(1024), 0, w->stream, a);
         ADI_LAUNCHED("fused_step");

@@ -238,7 +238,7 @@ __device__ __forceinline__ double fr_enter_right(double a, double b, int lane)
 // One strip segment (blk = segment row * tiles_x + strip) of the grid A
 // describes, by the whole workgroup.
 // KEEP: u^{n+1} goes to a buffer of its own (see fused_tile)
-template <typename T, bool KEEP = false, int H = 0>
+template <typename T, bool KEEP = false, int H = 0, bool ROWS = (H == 1)>
 __device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShared<T, H>& sh)
 {
     using C = FrCfg<T, H>;
@@ -301,29 +301,40 @@ __device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShar
     // whatever lies outside the grid (the lanes or edge values past a wall, whole rows
     // above or below it, the bands past the strip's last) through a vector offset past
     // every range, which the range check turns into zeros without a memory access.
+    // ROWS: one resource per row, whose range is the row (none for a row outside the
+    // grid), so that a row may end within a lane's vector.  Its scalar work made the step
+    // on 16-byte rows 1% slower (8192^2 212.4 -> 214.4 us), hence the two forms.
     const int ecol = (lane == 0) ? c0 - KX - 1 : (lane == nl - 1) ? c0 + wt + KX : -1;
     const int voff = (inwin && col0 >= 0 && col0 < nx) ? col0 * ES : kFuOOB;
     const int eoff = (ecol >= 0 && ecol < nx) ? ecol * ES : kFuOOB;
+    // FP64: A.qin holds the entry pivot of every 2-node lane, ceil(nx / 2) a row
+    const int nq = (nx + 1) / 2;
     const int plane = (int)(npts * ES);
     const rsrc_t ru_all = buf(A.uc, plane);
     const rsrc_t rr_all = buf(A.r, plane);
-    // FP64: A.qin holds the entry pivot of every 2-node lane, ceil(nx / 2) a row (nx is even)
     const rsrc_t rq_all = buf(A.qin, sizeof(T) == 8 ? (int)(npts / 2 * ES) : 0);
+    // the resource of row jj (ok: it is a row of the grid) of n values a row
+    auto row = [&](const T* p, rsrc_t all, int jj, bool ok, int n) {
+        return ROWS ? buf(p + (size_t)(ok ? jj : 0) * n, ok ? n * ES : 0) : all;
+    };
     const int qoff = voff == kFuOOB ? kFuOOB : voff / 2;
     // pieces of band k's inputs: u^n row j-1+i (with its window-edge values), and
     // r row j+i, j = the wavefront's first x-row of band k
     auto load_u = [&](int k, int i, FRIn<T, H>& P) {
         const int jj = xr_lo + kFrB * k + XR * xw - 1 + i;
         const bool ok = row_ok(jj) && k < nb;
-        const int so = ok ? jj * row_bytes : 0;
-        fr_load_vec<T>(ru_all, ok ? voff : kFuOOB, so, P.u[i]);
-        P.e[i] = fr_load1<T, 0>(ru_all, ok ? eoff : kFuOOB, so);
+        const int so = ok && !ROWS ? jj * row_bytes : 0;
+        const rsrc_t rs = row(A.uc, ru_all, jj, ok, nx);
+        fr_load_vec<T>(rs, ok || ROWS ? voff : kFuOOB, so, P.u[i]);
+        P.e[i] = fr_load1<T, 0>(rs, ok || ROWS ? eoff : kFuOOB, so);
     };
     auto load_r = [&](int k, int i, FRIn<T, H>& P) {
         const int jj = xr_lo + kFrB * k + XR * xw + i;
         const bool ok = row_ok(jj) && k < nb;
-        fr_load_vec<T>(rr_all, ok ? voff : kFuOOB, ok ? jj * row_bytes : 0, P.r[i]);
-        if constexpr (sizeof(T) == 8) P.q[i] = fr_load1<T, 0>(rq_all, ok ? qoff : kFuOOB, ok ? jj * (row_bytes / 2) : 0);
+        const int so = ok && !ROWS ? jj * row_bytes : 0;
+        fr_load_vec<T>(row(A.r, rr_all, jj, ok, nx), ok || ROWS ? voff : kFuOOB, so, P.r[i]);
+        if constexpr (sizeof(T) == 8)
+            P.q[i] = fr_load1<T, 0>(row(A.qin, rq_all, jj, ok, nq), ok || ROWS ? qoff : kFuOOB, so / 2);
     };
     auto load_band = [&](int k, FRIn<T, H>& P) {
 #pragma unroll
@@ -676,7 +687,7 @@ __device__ __forceinline__ void fusedr_strip(const FArgsT<T>& A, int blk, FRShar
     }
 }
 
-template <typename T, bool KEEP = false, int H = 0>
+template <typename T, bool KEEP = false, int H = 0, bool ROWS = (H == 1)>
 __global__ void __launch_bounds__((Fr<T, H>::THREADS)) k_fusedr(FArgsT<T> A)
 {
     __shared__ FRShared<T, H> sh;
@@ -685,7 +696,7 @@ __global__ void __launch_bounds__((Fr<T, H>::THREADS)) k_fusedr(FArgsT<T> A)
     // in that XCD's L2): the grid is a multiple of 8 and blocks past the tiles exit
     const int blk = xcd_band(blockIdx.x);
     if (blk >= A.tiles) return;
-    fusedr_strip<T, KEEP, H>(A, blk, sh);
+    fusedr_strip<T, KEEP, H, ROWS>(A, blk, sh);
 }
 
 }  // namespace adw
