@@ -311,7 +311,8 @@ adi_status adi_batch_destroy(adi_batch_t b);
  * the systems must be solvable by Gaussian elimination without pivoting
  * (e.g. strictly diagonally dominant), as the paper's line systems are.
  * Contiguous systems (elem_stride == 1, n <= 16384 / 8192 for f64) are solved
- * one per workgroup on chip.  Other layouts take a partition solve in three
+ * one per workgroup on chip, interleaved ones (sys_stride == 1) of up to 4096 unknowns
+ * several side by side likewise, where that is faster.  Other layouts take a partition solve in three
  * launches (chunks of 32 rows for f32, 16 for f64, eliminated onto their last
  * row; the chunk-boundary system, solved by a second partition level with up to
  * 64 threads per system, or by one thread per system when it has more than 1024

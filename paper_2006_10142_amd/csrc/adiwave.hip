@@ -1464,6 +1464,17 @@ adi_status tri_run_part(adi_dtype dtype, int n, int batch, const void* a, const 
     return ADI_OK;
 }
 
+// whole interleaved systems in one launch, without scratch: false where that does not apply
+bool tri_run_cols(adi_dtype dtype, int n, int batch, const void* a, const void* b, const void* c, void* d,
+                  long long sys_stride, long long elem_stride, hipStream_t st)
+{
+    if (dtype == ADI_F32)
+        return launch_tri_cols<float>({(const float*)a, (const float*)b, (const float*)c, (float*)d, n, batch,
+                                       sys_stride, elem_stride}, st);
+    return launch_tri_cols<double>({(const double*)a, (const double*)b, (const double*)c, (double*)d, n, batch,
+                                    sys_stride, elem_stride}, st);
+}
+
 // scratch of the partition solve, one per device, grown on demand
 std::mutex g_scr_mu;
 std::vector<std::pair<void*, size_t>> g_scr;
@@ -1509,6 +1520,10 @@ adi_status tridiag_solve_batched(adi_dtype dtype, int n, int batch, const void* 
     if (n == 0 || batch == 0) return ADI_OK;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (wg) return tri_run_wg(dtype, p, n, batch, a, b, c, d, sys_stride, elem_stride, st);
+    if (tri_run_cols(dtype, n, batch, a, b, c, d, sys_stride, elem_stride, st)) {
+        ADI_LAUNCHED("tridiag_cols");
+        return ADI_OK;
+    }
     int dev = 0;
     ADI_HIP(hipGetDevice(&dev));
     const size_t need = tri_part_bytes(dtype, n, batch);
@@ -1548,6 +1563,10 @@ adi_status tridiag_solve_batched_noalloc(adi_dtype dtype, int n, int batch, cons
         return fail(ADI_EINVAL, "the layout needs " + std::to_string(need) +
                                     " bytes of partition workspace, above the no-allocation scratch of " +
                                     std::to_string(kNoAllocScratchBytes) + " bytes");
+    if (tri_run_cols(dtype, n, batch, a, b, c, d, sys_stride, elem_stride, st)) {
+        ADI_LAUNCHED("tridiag_cols");
+        return ADI_OK;
+    }
     void* scr = nullptr;
     if (adi_status s = noalloc_scratch(&scr)) return s;
     return tri_run_part(dtype, n, batch, a, b, c, d, sys_stride, elem_stride, scr, st);

@@ -2,7 +2,8 @@
 // on-chip one-workgroup-per-system kernel does not take (strided elements,
 // interleaved systems, very long lines).  It is a partition method in three
 // launches, so that every unknown of every system keeps a thread busy instead
-// of one thread walking a whole system; included by adiwave.hip.
+// of one thread walking a whole system; included by adiwave.hip.  (k_tri_cols, at the
+// end: short interleaved systems whole, in one launch.)
 //
 // A system of n unknowns is cut into P = ceil(n/M) chunks of M rows.  The last
 // row of chunk p holds its interface unknown X_p; the rows before it (the
@@ -427,6 +428,86 @@ __global__ void __launch_bounds__(256) k_tri_part_expand(TriArgs<T> A, int P, co
             A.d[base + i * es] = x;
         }
     }
+}
+
+// Neighbouring systems one value apart, n <= S * P: whole systems in one launch.  A
+// workgroup owns CB systems side by side, P threads each with S consecutive rows in
+// registers (partition_solve), so that every value is read and written once; the launches
+// above read each twice.  The blocks that share 128-byte lines run on one XCD.
+// Rows past a thread's last and systems past the call's last load the one before again.
+// Bound by memory where the call is large (1024 rows, 32768 FP32 systems: 224 us, 3.0 TB/s,
+// 239 by the three launches; 200 rows, 200000 FP64 systems 609 -> 333 us), by one chain of
+// loads, elimination and cyclic reduction where it is small.
+template <typename T, int S, int P, int CB>
+__global__ void __launch_bounds__(P * CB) k_tri_cols(TriArgs<T> A)
+{
+    __shared__ T lds[partition_lds_slots<P>() * CB];
+    const int blk = (blockIdx.x & 7) * (int)(gridDim.x >> 3) + (blockIdx.x >> 3);
+    if ((long long)blk * CB >= A.batch) return;
+    const int col = threadIdx.x % CB;
+    const int t = threadIdx.x / CB;
+    const int sys = blk * CB + col;
+    const bool live = sys < A.batch;
+    const int n = A.n, lo = t * S;
+    const int L = live ? max(0, min(S, n - lo)) : 0;
+    const int nact = live ? (n + S - 1) / S : 0;
+    const long long es = A.elem_stride;
+    const long long base = min(sys, A.batch - 1) + (long long)min(lo, n - 1) * es;
+    T a[S], b[S], c[S], d[S];
+    long long o = base;
+#pragma unroll
+    for (int k = 0; k < S; ++k) {
+        a[k] = A.a[o];
+        b[k] = A.b[o];
+        c[k] = A.c[o];
+        d[k] = A.d[o];
+        o += lo + k < n - 1 ? es : 0;
+    }
+    if (t == 0) a[0] = T(0);            // outside the system
+#pragma unroll
+    for (int k = 0; k < S; ++k)
+        if (lo + k == n - 1) c[k] = T(0);
+    partition_solve<T, S, P>(d, CoefABC<T, S>{a, b, c}, L, t, nact, lds + col, CB);
+#pragma unroll
+    for (int k = 0; k < S; ++k)
+        if (k < L) A.d[base + k * es] = d[k];
+}
+
+template <typename T, int S, int P, int CB>
+void launch_tri_cols1(const TriArgs<T>& t, hipStream_t st)
+{
+    const int blocks = (t.batch + CB - 1) / CB;
+    hipLaunchKernelGGL((k_tri_cols<T, S, P, CB>), dim3((blocks + 7) / 8 * 8), dim3(P * CB), 0, st, t);
+}
+
+// One launch where it is faster than the three (us, three -> one):
+//   n <= 1024  always (512 x 512 FP32 29 -> 10.6, 1024 x 8192 77 -> 54), but for very short
+//              systems in great number (1 x 100000: 16.8 -> 19.1), where most threads idle;
+//   n <= 2048  four (FP64) to eight adjacent systems share a workgroup, each 128-byte line
+//              being read by several: up to 5000 systems (2048 x 2000 FP32 47 -> 23,
+//              2048 x 5500 103 -> 90, 1500 x 8192 98 -> 108; FP64 1200 x 5500 105 -> 107);
+//   n <= 4096  two (FP64) or four, one workgroup per compute unit (4096 x 1000 FP32 48 ->
+//              33, 4096 x 2000 81 -> 89; FP64 x 500 46 -> 32, x 1000 77 -> 85);
+//   beyond, the chain over 512 or more segments is the longer one (5000 x 16 26 -> 31).
+// Columns: half as many and shorter segments where that still leaves a compute unit idle
+// (1000 x 1000 FP32 15.9 -> 12.1, but x 8192 54 -> 70).
+template <typename T>
+bool launch_tri_cols(const TriArgs<T>& t, hipStream_t st)
+{
+    constexpr bool F = sizeof(T) == 4;
+    const int n = t.n, batch = t.batch;
+    const int most = n > 2048 ? (F ? 1024 : 512) : n > 1024 ? 5000 : n < 16 ? 32768 : batch;
+    if (t.sys_stride != 1 || n > 4096 || batch > most) return false;
+    const bool few = batch <= 255 * (F ? 16 : 8);
+    if (n <= 128) launch_tri_cols1<T, 4, 32, 16>(t, st);
+    else if (n <= 256) launch_tri_cols1<T, 8, 32, 16>(t, st);
+    else if (n <= 512) launch_tri_cols1<T, 8, 64, F ? 16 : 8>(t, st);
+    else if (n <= 1024 && few) launch_tri_cols1<T, 8, 128, F ? 8 : 4>(t, st);
+    else if (n <= 1024) launch_tri_cols1<T, F ? 16 : 8, F ? 64 : 128, F ? 16 : 8>(t, st);
+    else if (n <= 2048 && F && batch > 4 * 255) launch_tri_cols1<T, F ? 16 : 8, F ? 128 : 256, F ? 8 : 4>(t, st);
+    else if (n <= 2048) launch_tri_cols1<T, 8, 256, 4>(t, st);
+    else launch_tri_cols1<T, F ? 16 : 8, F ? 256 : 512, F ? 4 : 2>(t, st);
+    return true;
 }
 
 // Workspace values the partition solve needs for (n, batch).

@@ -142,6 +142,31 @@ def test_contiguous_lines_of_any_alignment(adw, oracle_lib, dtype, n, batch, pad
     assert np.array_equal(got[gap], d[gap])
 
 
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n,batch,pad", [(1, 70, 0), (2, 17, 3), (5, 33, 1), (15, 32769, 0), (128, 47, 0), (129, 16, 5),
+                                         (257, 9, 0), (513, 15, 1), (1024, 2041, 0), (1000, 4097, 0), (1025, 1021, 3),
+                                         (2048, 5, 0), (1030, 5001, 0), (2049, 3, 1), (4096, 6, 0), (2100, 513, 0),
+                                         (2100, 1025, 0), (4097, 5, 2)])
+def test_interleaved_lines(adw, oracle_lib, dtype, n, batch, pad):
+    """Interleaved systems around the lengths and counts where the kernel and its split
+    change, with gaps between the rows; what lies outside a system is not read (NaN)."""
+    print(f"interleaved lines {dtype} n={n} batch={batch} pad={pad}", flush=True)
+    nt = np.float32 if dtype == "f32" else np.float64
+    rng = np.random.default_rng(n)
+    es = batch + pad
+    a, c, d = (rng.uniform(-1, 1, (n, es)).astype(nt) for _ in range(3))
+    b = (np.abs(a) + np.abs(c) + 0.5).astype(nt)
+    ref = oracle_lib.tridiag_batched(a, b, c, d, n, batch, 1, es)
+    a[0] = c[-1] = np.nan
+    for v in (a, b, c):
+        v[:, batch:] = np.nan
+    A, B, C, D = (torch.from_numpy(v).cuda() for v in (a, b, c, d))
+    adw.tridiag_solve_batched(A, B, C, D, n, batch, 1, es)
+    got, ref = D.cpu().numpy(), np.asarray(ref).reshape(n, es)
+    assert rel_l2(got[:, :batch], ref[:, :batch]) <= (1e-13 if dtype == "f64" else 1e-5)
+    assert np.array_equal(got[:, batch:], d[:, batch:])
+
+
 def test_lines_past_the_caches(adw):
     """Line solves whose arrays exceed the last-level cache (their kernels read past it):
     the residual of 3500 systems of 8192 unknowns, contiguous and interleaved."""
