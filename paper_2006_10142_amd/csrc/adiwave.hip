@@ -222,7 +222,7 @@ int choose_ycol(int nx, int ny, adi_dtype dt)
 int ycol_threads(int ny, int S, int CB) { return (CB * ((ny + S - 1) / S) + 63) / 64 * 64; }
 
 template <typename T, int CB, bool DYN>
-bool launch_ycol_s(int S, const YArgs<T>& a, hipStream_t st)
+bool launch_ycol_s(int S, const YColArgs<T>& a, hipStream_t st)
 {
     constexpr bool kTop = CB < 16 || sizeof(T) == 4;      // 32-row segments fit the registers
     const int blocks = (a.nx + CB - 1) / CB;
@@ -245,7 +245,7 @@ bool launch_ycol_s(int S, const YArgs<T>& a, hipStream_t st)
 // 128 workgroups on; 1501 x 997: 17.6 us, 18.9 with 16, 21.2 with 4), else 4 (1024^2
 // FP64: 20.1 us, 21.6 with 8; 500 x 2040 FP32 19.9, 22.2 with 8).
 template <typename T, bool DYN = false>
-bool launch_ycol(int S, const YArgs<T>& a, hipStream_t st)
+bool launch_ycol(int S, const YColArgs<T>& a, hipStream_t st)
 {
     if constexpr (!DYN)                 // (the time-dependent step comes here with at most 2048 columns)
         if (a.nx > 16 * 255 && (sizeof(T) == 4 || S <= 16)) return launch_ycol_s<T, 16, DYN>(S, a, st);
@@ -458,13 +458,10 @@ XArgs<T> make_x(const adi_wave_s* w, const void* u, const adi_source* f, int k, 
     a.w = static_cast<T*>(w->w);
     a.nx = w->nx;
     a.ny = w->ny;
-    a.nseg = w->nseg;
     a.rows_per_strip = w->xp.fuse ? w->xp.frs : w->xp.rs;
-    a.xcd = a.rows_per_strip <= kXcdStripRows;
     a.sum = static_cast<T*>(w->sum);
     a.K = w->K;
     a.M = w->M;
-    a.nxp = w->nxp;
     a.rho_scale = rho_scale;
     a.tau2 = (T)(w->dt * w->dt);
     if (f && f->count > 0) {
@@ -490,7 +487,6 @@ YArgs<T> make_y(const adi_wave_s* w, const void* u, const void* v, void* out, T 
     a.K = w->K;
     a.nxp = w->nxp;
     a.tmp = static_cast<T*>(w->w);
-    a.qy = static_cast<T*>(w->qy);
     a.sum = static_cast<T*>(w->sum);
     a.X = static_cast<T*>(w->X);
     a.u = static_cast<const T*>(u);
@@ -498,6 +494,24 @@ YArgs<T> make_y(const adi_wave_s* w, const void* u, const void* v, void* out, T 
     a.out = static_cast<T*>(out);
     a.alpha = alpha;
     a.beta = beta;
+    return a;
+}
+
+template <typename T>
+YColArgs<T> make_ycol(const adi_wave_s* w, const YArgs<T>& y)
+{
+    YColArgs<T> a{};
+    a.w = y.w;
+    a.r = y.r;
+    a.qy = static_cast<T*>(w->qy);
+    a.nx = y.nx;
+    a.ny = y.ny;
+    a.u = y.u;
+    a.v = y.v;
+    a.out = y.out;
+    a.alpha = y.alpha;
+    a.beta = y.beta;
+    a.rhs_times_r = y.rhs_times_r;
     return a;
 }
 
@@ -519,7 +533,7 @@ adi_status queue_y(adi_wave_s* w, const YArgs<T>& ya, bool reduced, hipEvent_t* 
             ADI_HIP(hipEventRecord(ev[1], st));
             ADI_HIP(hipEventRecord(ev[2], st));
         }
-        if (!launch_ycol<T>(w->ycs, ya, st)) return fail(ADI_EUNSUPPORTED, "no column kernel for this plan");
+        if (!launch_ycol<T>(w->ycs, make_ycol<T>(w, ya), st)) return fail(ADI_EUNSUPPORTED, "no column kernel for this plan");
         ADI_LAUNCHED("y_solve_update");
         if (ev) ADI_HIP(hipEventRecord(ev[3], st));
         return ADI_OK;

@@ -220,7 +220,7 @@ __device__ __forceinline__ void xsolve_update_strip(const XArgs<T>& X, const Adj
     constexpr int E = kSeg;
     const int lane = t & 63;
     const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int nx = X.nx, ny = X.ny, nseg = X.nseg;
+    const int nx = X.nx, ny = X.ny, nseg = X.nseg();
     const int RS = X.rows_per_strip;
     const int j0 = strip * RS;
     const int j1 = min(j0 + RS, ny);              // output rows [j0, j1)
@@ -414,7 +414,7 @@ __global__ void __launch_bounds__(TR >= 256 ? TR : 256) k_xsolve_update(XArgs<T>
             const int id = A.sidx[k];
             if (id < 0 || id >= A.npts) A.gout[k] = T(0);
         }
-    const int blk = X.xcd ? (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) : (int)blockIdx.x;
+    const int blk = X.xcd() ? (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) : (int)blockIdx.x;
     const int strips = (X.ny + X.rows_per_strip - 1) / X.rows_per_strip;
     if (blk * G >= strips) return;
     const int g = __builtin_amdgcn_readfirstlane(threadIdx.x / TR);
@@ -574,7 +574,6 @@ adi_status queue_xsolve(adi_wave_s* w, const void* rhs, void* out)
     XArgs<T> a = make_x<T>(w, rhs, nullptr, 0, T(1));
     a.w = static_cast<T*>(out);
     a.rows_per_strip = w->xp.rs;
-    a.xcd = a.rows_per_strip <= kXcdStripRows;
     const int g = x_groups_per_wg(w->xp.tr);
     const int grid = xsweep_grid(w->ny, w->xp.rs, g);
     switch (w->xp.tr) {
@@ -597,7 +596,6 @@ bool queue_xsolve_update(adi_wave_s* w, const void* z, const AdjArgs<T>& ua)
 {
     XArgs<T> a = make_x<T>(w, z, nullptr, 0, T(1));
     a.rows_per_strip = w->xp.rs;
-    a.xcd = a.rows_per_strip <= kXcdStripRows;
     const int grid = xsweep_grid(w->ny, w->xp.rs, x_groups_per_wg(w->xp.tr));
     switch (w->xp.tr) {
         case 64: hipLaunchKernelGGL((k_xsolve_update<T, 64>), dim3(grid), dim3(256), 0, w->stream, a, ua); return true;

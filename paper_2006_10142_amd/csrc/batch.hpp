@@ -143,15 +143,12 @@ __global__ void __launch_bounds__(TR >= 256 ? TR : 256) k_xsweep_batch(BatchArgs
             A.w = S.w;
             A.nx = S.nx;
             A.ny = S.ny;
-            A.nseg = S.nseg;
             A.sum = S.sum;
             A.K = S.K;
-            A.nxp = S.nxp;
             strip = wi.y;
         } else {            // idle group: no rows, but the same barrier sequence
             A.nx = 1;
             A.ny = 0;
-            A.nseg = 1;
         }
         A.rows_per_strip = B.RS;
         A.M = B.M;

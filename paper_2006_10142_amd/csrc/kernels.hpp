@@ -129,10 +129,6 @@ struct YArgs {
     int nx, ny, M, K, nxp;
     T* sum;              // summary planes (blocked, see above)
     T* X;                // K*nx interface values, index c*nx + i
-    T* qy;               // entry pivots of the whole-column y-solve (ycol.hpp)
-    int nrec;            // receivers of the level written (time-dependent whole-column step)
-    const int* rec_idx;
-    T* rec_out;
     const T* u;          // update: out = alpha*u + beta*v + d
     const T* v;          // may be null when beta == 0
     T* out;

@@ -62,8 +62,8 @@ __global__ void __launch_bounds__(256) k_tdc_x(TdcArgs<T> B)
     constexpr int ES = (int)sizeof(T);
     __shared__ TdcShared<T, TR> shg[G];
     const XArgs<T>& A = B.x;
-    const int blk = A.xcd ? xcd_band(blockIdx.x) : (int)blockIdx.x;
-    const int RS = A.rows_per_strip, nx = A.nx, ny = A.ny, nseg = A.nseg;
+    const int blk = A.xcd() ? xcd_band(blockIdx.x) : (int)blockIdx.x;
+    const int RS = A.rows_per_strip, nx = A.nx, ny = A.ny, nseg = A.nseg();
     if (blk * G * RS >= ny) return;
     const int g = __builtin_amdgcn_readfirstlane(threadIdx.x / TR);
     const int t = threadIdx.x - g * TR, lane = t & 63;
@@ -166,7 +166,6 @@ adi_status step_tdc_rows(adi_wave_s* w, void** u_prev, void** u_curr, const void
     TdcArgs<T> a{};
     a.x = make_x<T>(w, *u_curr, f, 0, T(1));
     a.x.rows_per_strip = w->xp.rs;
-    a.x.xcd = w->xp.rs <= kXcdStripRows;
     a.up = static_cast<const T*>(*u_prev);
     a.kn = static_cast<const T*>(kappa_next ? kappa_next : w->r);
     a.sn = kappa_next ? (T)s : T(1);
@@ -176,7 +175,7 @@ adi_status step_tdc_rows(adi_wave_s* w, void** u_prev, void** u_curr, const void
     a.qout = static_cast<T*>(w->qin);
     launch_tdc_x<T>(w->xp.tr, xsweep_grid(w->ny, w->xp.rs, x_groups_per_wg(w->xp.tr)), a, w->stream);
     ADI_LAUNCHED("x_sweep (time-dependent coefficient)");
-    YArgs<T> ya = make_y<T>(w, *u_curr, *u_prev, *u_prev, T(2), T(-1));
+    YColArgs<T> ya = make_ycol<T>(w, make_y<T>(w, *u_curr, *u_prev, *u_prev, T(2), T(-1)));
     if (rec && rec->count > 0) {
         ya.nrec = rec->count;
         ya.rec_idx = rec->idx;

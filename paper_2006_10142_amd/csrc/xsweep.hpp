@@ -243,27 +243,34 @@ __device__ __forceinline__ void wave_scan_bwd3(T& a0, T& a1, T& b, int lane)
     b = b * cb;
 }
 
+// strips in XCD bands: strips of at most this many rows
+constexpr int kXcdStripRows = 4;
+
 template <typename T>
 struct XArgs {
+    // (120 bytes for FP64: the hidden launch arguments behind it, gridDim among them, start
+    // in the second 64-byte line, as for FArgsT in fused.hpp)
     const T* u;          // u^n, (ny, nx)
     const T* r;          // r, (ny, nx)
     const T* qin;        // pivot entering each 8-node segment, (ny, nseg)
     T* w;                // out, (ny, nx)
-    int nx, ny, nseg;    // nseg = ceil(nx / 8)
+    int nx, ny;
     int rows_per_strip;  // consecutive rows handled by one line group
-    int xcd;             // strips in XCD bands (short strips, see k_xsweep)
+    int nsrc;            // point sources of this step
     T rho_scale;         // 1 for a step, 1/2 for the ghost start
     T tau2;              // dt^2
-    int nsrc;            // point sources of this step
     const int* src_idx;
     const T* src_amp;    // nsrc values of f
     // fused y-chunk elimination: a strip is a whole number of y-chunks of M rows
     T* sum;              // summary planes (blocked by 16 columns, see kernels.hpp)
-    int K, M, nxp;
     // receivers of the previous step, sampled from u (see rec_tap)
-    int nrec;
     const int* rec_idx;
     T* rec_out;
+    int nrec;
+    int K, M;
+    __host__ __device__ int nseg() const { return (nx + 7) / 8; }
+    __host__ __device__ int nxp() const { return (nx + 15) / 16 * 16; }
+    __host__ __device__ bool xcd() const { return rows_per_strip <= kXcdStripRows; }   // strips in XCD bands
 };
 
 constexpr int kSeg = 8;   // nodes per x-line segment (one segment per thread)
@@ -629,7 +636,7 @@ __device__ __forceinline__ void xsweep_strip(const XArgs<T>& A, const int strip,
     auto& s_halo = sh.halo;
     const int lane = t & 63;
     const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int nx = A.nx, ny = A.ny, nseg = A.nseg;
+    const int nx = A.nx, ny = A.ny, nseg = A.nseg();
     const int RS = A.rows_per_strip;
     const int j0 = strip * RS;
     const int i0 = E * t;
@@ -788,7 +795,7 @@ __device__ __forceinline__ void xsweep_strip(const XArgs<T>& A, const int strip,
                 }
             } else if (act && kk == Lc - 1) {
                 // interface row of the chunk: E = wI + rI Pl and Pf, then restart
-                const size_t pl = (size_t)A.K * A.nxp;
+                const size_t pl = (size_t)A.K * A.nxp();
                 const size_t o = ((size_t)(i0 / kPB) * A.K + c) * kPB + (i0 % kPB);
 #pragma unroll
                 for (int e = 0; e < E; ++e)
@@ -838,15 +845,12 @@ __global__ void __launch_bounds__(TR >= 256 ? TR : 256) k_xsweep(XArgs<T> A)
     rec_tap<T>(A.u, A.rec_idx, A.rec_out, A.nrec, (long long)A.nx * A.ny);
     constexpr int G = (TR >= 256 ? TR : 256) / TR;
     __shared__ XShared<T, TR, FUSE> sh[G];
-    const int blk = A.xcd ? (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) : (int)blockIdx.x;
+    const int blk = A.xcd() ? (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) : (int)blockIdx.x;
     const int strips = (A.ny + A.rows_per_strip - 1) / A.rows_per_strip;
     if (blk * G >= strips) return;
     const int g = __builtin_amdgcn_readfirstlane(threadIdx.x / TR);   // one group per wavefront or more
     xsweep_strip<T, TR, FUSE, STENCIL>(A, blk * G + g, threadIdx.x - g * TR, sh[g]);
 }
-
-// strips in XCD bands: strips of at most this many rows
-constexpr int kXcdStripRows = 4;
 
 // x-sweep grid: workgroups for the strips (a multiple of 8 for XCD bands)
 inline int xsweep_grid(int ny, int rows_per_strip, int groups_per_wg)

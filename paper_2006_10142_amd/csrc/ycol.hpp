@@ -23,6 +23,23 @@ namespace adw {
 constexpr int kYcP = 64;          // segments per column (lanes of the scanning wavefront)
 constexpr int kYpCB = 16;         // columns per workgroup of the pivot kernel
 
+// (96 bytes for FP64: the hidden launch arguments behind it stay in the second 64-byte line)
+template <typename T>
+struct YColArgs {
+    const T* w;          // x-sweep result
+    const T* r;
+    T* qy;               // entry pivot of every segment (DYN: written here)
+    const T* u;          // update: out = alpha*u + beta*v + d
+    const T* v;          // may be null when beta == 0
+    T* out;
+    T alpha, beta;
+    int nx, ny;
+    int rhs_times_r;     // right-hand side is r * w (adjoint solves)
+    int nrec;            // DYN: receivers of the level written
+    const int* rec_idx;
+    T* rec_out;
+};
+
 template <typename T, int CB>
 struct YColShared {
     T m[4][kYcP][CB + 1];            // G (then g_in), Q, H (then x_below), E
@@ -68,7 +85,7 @@ __global__ void __launch_bounds__(kYcP * kYpCB) k_ycol_pivots(const T* __restric
 // DYN: r is new (the time-dependent step): the entry pivots are formed here and kept in
 // A.qy, and the receivers of the new level are recorded.
 template <typename T, int S, int CB, bool DYN = false>
-__global__ void __launch_bounds__(kYcP * CB) k_ycol(YArgs<T> A)
+__global__ void __launch_bounds__(kYcP * CB) k_ycol(YColArgs<T> A)
 {
     constexpr int ES = (int)sizeof(T);
     constexpr bool PRE = S * ES <= 64;
