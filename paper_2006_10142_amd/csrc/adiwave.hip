@@ -208,11 +208,15 @@ bool launch_ysolve(int M, dim3 grid, const YArgs<T>& a, hipStream_t st)
 // thread, one workgroup a compute unit) stay with it on grids above 2^23 nodes, where
 // both are bound by bytes and its many small workgroups hide the loads better (step of
 // 8192 x 2048: FP32 121 us chunked, 129 whole; FP64 259, 291); at or below, whole
-// columns win (4096 x 2048: FP32 76, 62; FP64 141, 138; 2048 x 1100 FP32 30.4, 22.0).
+// columns win (4096 x 2048: FP32 76, 62; FP64 141, 138; 2048 x 1100 FP32 30.4, 22.0), but
+// for narrow FP32 grids near 2048 rows in whole chunks, where both are one chain and the
+// chunks' is the shorter (100 x 2000: 17.1 chunked, 19.4 whole; 400 x 2000 19.4, 20.7;
+// 500 x 2000 20.7, 19.8; 33 x 2000 18.5, 18.2; 100 x 1900 19.0, 18.5).
 int choose_ycol(int nx, int ny, adi_dtype dt)
 {
     const long long n = (long long)nx * ny;
     if (n * (long long)esize(dt) > kFuOOB || (ny > kYcP * 16 && n > (1LL << 23))) return 0;
+    if (dt == ADI_F32 && ny > 1920 && ny <= 2048 && ny % 16 == 0 && nx >= 64 && nx <= 448) return 0;
     for (int s = 2; s <= 32; s *= 2)
         if (kYcP * s >= ny) return s;
     return 0;

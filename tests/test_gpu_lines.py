@@ -62,7 +62,7 @@ def test_entry_pivots_of_long_rows(adw, oracle_lib, dtype, nx):
 
 
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
-@pytest.mark.parametrize("nx,ny", [(1, 1), (2, 3), (5, 40), (66, 31), (515, 33), (1501, 97), (2051, 20), (8190, 6), (8191, 5)])
+@pytest.mark.parametrize("nx,ny", [(1, 1), (2, 3), (5, 40), (66, 31), (515, 33), (1501, 97), (2051, 20), (8190, 6), (8191, 5), (100, 2000)])
 def test_rows_of_any_length(adw, oracle_lib, dtype, nx, ny):
     """Rows that end inside a 16-byte vector and start off 16-byte boundaries, on the
     exact two-pass step of every line-group width."""
