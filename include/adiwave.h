@@ -276,7 +276,10 @@ typedef struct {
     int fused_step;           /* 1: one-pass step for every simulation (FP32, when each
                                  simulation's truncation bound holds; the default then),
                                  2 (set only): exact two-pass step, 0 (set): keep */
-    int fused_allowed;        /* read-only: the one-pass step is allowed for the batch */
+    int fused_allowed;        /* read-only: the one-pass step is allowed for the batch (where
+                                 rows that are no multiple of 4 values forbid it, FP32 within
+                                 r_max 0.18, adi_batch_step takes a form of it by itself unless
+                                 fused_step 2 is set) */
     int fused_items;          /* read-only: one-pass work items (tiles or strip segments)
                                  over all simulations */
     int fused_lane_nodes;     /* one-pass tiles: x-line nodes per lane, 8 (default) or 4

@@ -99,6 +99,8 @@ __global__ void __launch_bounds__(1024) k_fused4_batch(FBatchArgs B)
 // simulation's strips are of one width (the last one cut by the grid's edge),
 // so a plain handle tuned to the same width and segment rows runs the same
 // arithmetic
+// ROWS: rows of any length (fusedr.hpp)
+template <bool ROWS>
 __global__ void __launch_bounds__(Fr<float>::THREADS) k_fusedr_batch(FBatchArgs B)
 {
     __shared__ FRShared<float> sh;
@@ -120,7 +122,7 @@ __global__ void __launch_bounds__(Fr<float>::THREADS) k_fusedr_batch(FBatchArgs 
     A.wide = A.tiles_x;
     A.hs = __builtin_amdgcn_readfirstlane(S.s_hs);
     A.tiles = __builtin_amdgcn_readfirstlane(S.s_tiles);
-    fusedr_strip<float>(A, __builtin_amdgcn_readfirstlane(wi.y), sh);
+    fusedr_strip<float, false, 0, ROWS>(A, __builtin_amdgcn_readfirstlane(wi.y), sh);
 }
 
 template <typename T, int TR>
@@ -235,6 +237,9 @@ struct adi_batch_s {
     long long nodes = 0;
     // one-pass step: allowed when every simulation allows it (FP32, bound holds)
     int fused_ok = 0, fused = 0;
+    // where it is not, but its bound holds for all (FP32 rows that are no multiple of 16
+    // bytes): the form adi_batch_step takes by itself (batch_wide)
+    int wide = 0;
     int flane = 8;                  // nodes per lane of the one-pass tiles (8 or 4)
     int fstrips = 0;                // 1: the one-pass step on column strips instead of tiles
     int2* fitems = nullptr;         // (simulation, tile) of the eight-node tiles, then the four-node
@@ -245,6 +250,13 @@ struct adi_batch_s {
 };
 
 namespace {
+
+// FP32 batches whose rows are of any length, within the one-pass bound: the four-node tiles
+// (row descriptors), from 40 M nodes on the column strips with row descriptors.  us a step,
+// three exact launches | tiles | strips: 2 simulations of 64 to 100 64 | 10 | 19; 32 of 200
+// to 700 109 | 36 | 94; 64 of 200 to 900 (18 M nodes) 191 | 78 | 122; 128 of 256 to 1024
+// (53 M) 460 | 228 | 221; 256 of them (105 M) 857 | 438 | 405.
+int batch_wide(long long nodes) { return nodes < 40000000 ? kWideTiles : kWideRows; }
 
 void batch_free(adi_batch_s* b)
 {
@@ -375,14 +387,17 @@ adi_status queue_batch_solve(adi_batch_s* b, int u_slot, int v_slot, int out_slo
 adi_status batch_step_once(adi_batch_s* b, hipStream_t st, int parity)
 {
     const int p = parity;
-    if (b->fused && b->fstrips) {
+    const bool rows = !b->fused && b->wide == kWideRows, tiles = !b->fused && b->wide == kWideTiles;
+    if (rows || (b->fused && b->fstrips)) {
         FBatchArgs a{static_cast<const SimDesc<float>*>(b->desc), b->fitems + b->nf_items + b->nf4_items,
                      b->nfs_items, p ^ 1, p};
-        hipLaunchKernelGGL(k_fusedr_batch, dim3((b->nfs_items + 7) / 8 * 8), dim3(Fr<float>::THREADS), 0, st, a);
+        const dim3 g((b->nfs_items + 7) / 8 * 8), blk(Fr<float>::THREADS);
+        if (rows) hipLaunchKernelGGL(k_fusedr_batch<true>, g, blk, 0, st, a);
+        else hipLaunchKernelGGL(k_fusedr_batch<false>, g, blk, 0, st, a);
         ADI_LAUNCHED("fused_batch");
         return ADI_OK;
     }
-    if (b->fused && b->flane == 4) {
+    if (tiles || (b->fused && b->flane == 4)) {
         FBatchArgs a{static_cast<const SimDesc<float>*>(b->desc), b->fitems + b->nf_items, b->nf4_items, p ^ 1, p};
         hipLaunchKernelGGL(k_fused4_batch, dim3((b->nf4_items + 7) / 8 * 8), dim3(1024), 0, st, a);
         ADI_LAUNCHED("fused_batch");
@@ -559,18 +574,24 @@ adi_status adi_batch_create(adi_batch_t* out, int count, const int* nx, const in
     }
     if (st == ADI_OK) {
         // one-pass tiles of every simulation (each view's plan was set with its r)
+        bool bound = dtype == ADI_F32;
         b->fused_ok = dtype == ADI_F32 ? 1 : 0;
-        std::vector<int2> fi;
-        for (int s = 0; s < count && b->fused_ok; ++s) {
+        for (int s = 0; s < count; ++s) {
             if (!b->sims[s].fused_ok) b->fused_ok = 0;
+            bound = bound && fused_bound_holds(b->sims[s].rmax, dtype);
+        }
+        b->wide = bound && !b->fused_ok ? batch_wide(b->nodes) : kWideNone;
+        const bool lists = b->fused_ok || b->wide;
+        std::vector<int2> fi;
+        for (int s = 0; s < count && lists; ++s) {
             for (int tl = 0; tl < b->sims[s].f_tiles; ++tl) fi.push_back(make_int2(s, tl));
         }
         b->nf_items = (int)fi.size();
-        for (int s = 0; s < count && b->fused_ok; ++s)
+        for (int s = 0; s < count && lists; ++s)
             for (int tl = 0; tl < b->sims[s].f4_tiles; ++tl) fi.push_back(make_int2(s, tl));
         b->nf4_items = (int)fi.size() - b->nf_items;
         b->s_wt.assign(count, 0); b->s_tx.assign(count, 0); b->s_hs.assign(count, 0); b->s_tiles.assign(count, 0);
-        for (int s = 0; s < count && b->fused_ok; ++s) {
+        for (int s = 0; s < count && lists; ++s) {
             batch_strip_plan(nx[s], ny[s], b->s_wt[s], b->s_tx[s], b->s_hs[s], b->s_tiles[s]);
             for (int tl = 0; tl < b->s_tiles[s]; ++tl) fi.push_back(make_int2(s, tl));
         }
@@ -616,7 +637,7 @@ adi_status adi_batch_create(adi_batch_t* out, int count, const int* nx, const in
                 for (int x = 0; x < 8; ++x) fi.push_back(k < qs[x].size() ? qs[x][k] : make_int2(-1, -1));
             b->nfs_items = (int)(8 * len);
         }
-        if (b->fused_ok) {
+        if (lists) {
             if (hipMalloc(&b->fitems, fi.size() * sizeof(int2)) != hipSuccess) {
                 (void)hipGetLastError();
                 b->fitems = nullptr;
@@ -625,7 +646,7 @@ adi_status adi_batch_create(adi_batch_t* out, int count, const int* nx, const in
                                       b->stream) != hipSuccess) {
                 st = fail(ADI_EHIP, "upload of the one-pass work list failed");
             }
-            b->fused = st == ADI_OK ? 1 : 0;
+            b->fused = st == ADI_OK && b->fused_ok ? 1 : 0;
         }
     }
     if (st == ADI_OK) st = batch_upload(b);
@@ -753,6 +774,7 @@ adi_status adi_batch_set_plan(adi_batch_t b, const adi_batch_plan* p)
     if (p->fused_lane_nodes != 0 && p->fused_lane_nodes != 4 && p->fused_lane_nodes != 8)
         return fail(ADI_EINVAL, "fused_lane_nodes must be 0, 4 or 8");
     if (p->fused_strips < 0 || p->fused_strips > 2) return fail(ADI_EINVAL, "fused_strips must be 0, 1 or 2");
+    if (p->fused_step == 2) b->wide = kWideNone;
     if (p->fused_step > 0) b->fused = p->fused_step == 1 ? 1 : 0;
     if (p->fused_strips) b->fstrips = p->fused_strips == 1 ? 1 : 0;
     if (p->fused_lane_nodes) b->flane = p->fused_lane_nodes;
@@ -825,7 +847,19 @@ adi_status adi_batch_autotune(adi_batch_t b, int trial_steps, double* best_ms)
         b->flane = blane;
         b->fstrips = bstrips;
     } else if (st == ADI_OK) {
+        int wide = b->wide;
+        if (wide) {
+            for (int form : {kWideTiles, kWideRows}) {
+                b->wide = form;
+                double ms = 0;
+                if ((st = trial(ms)) != ADI_OK) break;
+                if (ms < best) { best = ms; wide = form; }
+            }
+        }
+        const double bwide = best;
+        b->wide = kWideNone;
         for (int tr : {128, 256, 1024}) {
+            if (st != ADI_OK) break;
             if (8LL * tr < b->max_nx || !batch_fits(tr, b->dtype)) continue;
             b->x_tr = tr; b->x_grid = 0; b->ys_grid = 0; b->yv_grid = 0;
             double ms = 0;
@@ -845,6 +879,7 @@ adi_status adi_batch_autotune(adi_batch_t b, int trial_steps, double* best_ms)
             }
             *knobs[q] = *bests[q];
         }
+        b->wide = best < bwide ? kWideNone : wide;
     }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);

@@ -101,3 +101,30 @@ def test_when_the_exact_step_runs(adw):
     w.set_kappa(k)
     assert w.info()["kernels_per_step"] == 1
     w.close()
+
+
+@pytest.mark.parametrize("sizes", [[(1, 9), (33, 70), (257, 64), (5, 300), (243, 65), (8, 8)],
+                                   [(3203, 3201), (3201, 3203), (3999, 2501), (6667, 1601)]])
+def test_batched_rows_of_any_length(adw, sizes):
+    """The batched forms on rows of any length (tiles; column strips from 40 M nodes) against
+    the batch's exact step, eager and replayed: five FP32 steps apart by rounding and half
+    an ulp of truncation each, 3e-6."""
+    print(f"batched rows of any length {sizes}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    h = [1.0 / (max(s) + 1) for s in sizes]
+    c = [1.0 + 2.0 * torch.rand(ny, nx, device="cuda", generator=g) for nx, ny in sizes]
+    u0 = [torch.randn(ny, nx, device="cuda", generator=g) for nx, ny in sizes]
+    out = []
+    for exact, graph in ((False, False), (False, True), (True, False)):
+        b = adw.Batch(sizes, h, [0.19 * x for x in h], c)      # r <= 0.163
+        assert b.plan()["fused_allowed"] == 0 and b.plan()["fused_step"] == 0
+        if exact:
+            b.set_plan(fused_step=False)
+        b.bind([u.clone() for u in u0], [u.clone() for u in u0])
+        if graph:
+            b.graph(True)
+        b.step(5)
+        out.append([x.clone() for x in b.levels()[1]])
+        b.close()
+    for a, r, e in zip(*out):
+        assert torch.equal(a, r) and ((a - e).norm() / e.norm()).item() <= 3e-6
