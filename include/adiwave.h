@@ -367,7 +367,9 @@ typedef struct {
     int fused_allowed;        /* 1: the one-pass step's truncation bound holds (FP32:
                                  r_max <= 0.18 and nx % 4 == 0; FP64: r_max <= 0.13 and nx
                                  even) */
-    double r_max;             /* largest r = dt^2 kappa / (2 h^2) */
+    double r_max;             /* largest r = dt^2 kappa / (2 h^2); negative after
+                                 adi_wave_step_tdc with a kappa_next, until the next
+                                 adi_wave_set_kappa: not measured */
     int line_solver;          /* 1: partition / scan solvers, 2: cyclic-reduction baseline */
     int fused_tile_cols;      /* one-pass step: output columns per tile (64 rows each) or per
                                  column strip; chosen for the device's compute units unless

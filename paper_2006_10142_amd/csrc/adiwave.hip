@@ -328,7 +328,9 @@ struct adi_wave_s {
     void* sum = nullptr;   // 8 * K * nx
     void* X = nullptr;     // K * nx
     void* qin = nullptr;   // ny * nseg entry pivots of the x-line segments
-    void* qin2 = nullptr;  // FP64: ny * ceil(nx / 2) entry pivots of every 2-node lane (one-pass strips)
+    // FP64: ny * ceil(nx / 2) entry pivots of every 2-node lane (one-pass strips); those of r
+    // only where r was measured (rmax >= 0): the time-dependent step does not write them
+    void* qin2 = nullptr;
     void* qy = nullptr;    // qy_n = ceil(ny / ycs) * nx entry pivots of the y-line segments (ycol.hpp)
     size_t qy_n = 0;
     int ycs = 0;           // rows per thread of the whole-column y-solve; 0: the chunked y-solve
@@ -345,7 +347,9 @@ struct adi_wave_s {
     unsigned long long gen = 0;
     // one-pass step (FP32): allowed when the truncation bound holds for the
     // largest r; mode 0 = automatic, 1 = on when allowed, 2 = off
-    double rmax = 0.0;   // largest r, measured on the device when the coefficient is set
+    // largest r, measured on the device when the coefficient is set; negative: r is newer
+    // than the last measurement (see coef_unmeasured)
+    double rmax = 0.0;
     int fused_ok = 0, fused_mode = 0, fstep = 0;
     int f_wt = 0, f_tx = 0, f_tiles = 0, f_grid = 0;
     int f_wide = 0;      // column strips: the first f_wide are f_wt wide, the others f_wt - 8
@@ -849,6 +853,16 @@ adi_status measure_rmax(adi_wave_s* w)
     w->rmax = (double)v;
     fused_plan(w);
     return ADI_OK;
+}
+
+// r was replaced without a measurement (the time-dependent step, which does not
+// synchronise): a negative rmax fails every bound, so no plan made from here on, by
+// whatever call, takes a one-pass form before measure_rmax has run again.
+void coef_unmeasured(adi_wave_s* w)
+{
+    if (w->rmax < 0.0) return;
+    w->rmax = -1.0;
+    fused_plan(w);
 }
 
 void adjoint_invalidate(adi_wave_s* w);   // adjoint.hpp

@@ -159,9 +159,7 @@ adi_status step_tdc_rows(adi_wave_s* w, void** u_prev, void** u_curr, const void
     if (kappa_next) {
         ++w->gen;
         adjoint_invalidate(w);
-        // r is not measured here: the one-pass step stays off until the next set_kappa
-        w->fused_ok = 0;
-        w->fstep = w->fwide = 0;
+        coef_unmeasured(w);      // the one-pass step stays off until the next set_kappa
     }
     TdcArgs<T> a{};
     a.x = make_x<T>(w, *u_curr, f, 0, T(1));
@@ -221,9 +219,7 @@ adi_status do_step_tdc(adi_wave_s* w, void** u_prev, void** u_curr, const void* 
     // r^{n+1} with its x-line pivots and y-chunk planes becomes the handle's coefficient
     if (kappa_next) {
         if (adi_status st = set_coef<T>(w, kappa_next, 0.0, 0, false)) return st;
-        // r is no longer measured: the one-pass step stays off until the next set_kappa
-        w->fused_ok = 0;
-        w->fstep = w->fwide = 0;
+        coef_unmeasured(w);      // the one-pass step stays off until the next set_kappa
     }
     hipLaunchKernelGGL((k_rhs_tdc<T>), dim3(cr_grid(n)), dim3(256), 0, w->stream, static_cast<const T*>(*u_curr),
                        static_cast<const T*>(*u_prev), static_cast<const T*>(w->r),

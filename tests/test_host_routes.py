@@ -1,0 +1,39 @@
+"""Which kernels the host code queues, on the recording HIP runtime (no GPU): the forms a
+handle takes after calls that change its state."""
+import pytest
+
+from tests import recorder
+
+ONE_PASS = ("k_fused", "k_fused4", "k_fusedr")
+
+
+@pytest.mark.parametrize("nx,ny,rmax,f64", [(256, 256, 0.1, 0), (256, 256, 0.1, 1), (64, 1600, 0.5, 0),
+                                            (65, 1600, 0.17, 0), (65, 1600, 0.13, 1),
+                                            (2056, 2100, 0.1, 0), (2056, 2100, 0.1, 1)])
+def test_no_one_pass_step_on_an_unmeasured_coefficient(nx, ny, rmax, f64):
+    """A time-dependent step leaves a coefficient whose largest r is unknown: no call but
+    set_kappa brings a one-pass form back.  (2056 columns: the time-dependent step of
+    separate launches.)"""
+    got = recorder.run(f'''
+out = []
+for kw in (dict(x_rows_per_strip=4), dict(y_chunk_rows=16), dict(fused_lane_nodes=-1), dict(fused_tile_cols=-1),
+           dict(fused_segment_rows=-1), dict(fused_tile_cols=64), dict(fused_step=1), dict()):
+    w = wave({nx}, {ny}, {rmax}, {f64})
+    before = short(step(w))
+    a, b = ct.c_void_p(A), ct.c_void_p(B)
+    _lib.check(lib.adi_wave_step_tdc(w, ct.byref(a), ct.byref(b), C, D, None, None))
+    st = tune(w, **kw)
+    i = info(w)
+    after = short(step(w))
+    rid = ct.c_ulonglong()
+    _lib.check(lib.adi_adjoint_forward(w, A, B, None, None, 2, 1, ct.byref(rid)))
+    forward = short(names())
+    _lib.check(lib.adi_wave_set_kappa(w, C, 1.0))
+    out.append([kw, before, st, i["fused_step"] + i["fused_allowed"], i["r_max"], after, forward, short(step(w))])
+''')
+    for kw, before, st, flags, rmax_got, after, forward, restored in got:
+        assert before[0] in ONE_PASS and flags == 0 and rmax_got < 0
+        assert (st == -4) == ("fused_step" in kw)                  # asked for by name: refused
+        assert not set(after + forward) & set(ONE_PASS), (kw, after, forward)
+        plan = {"x_rows_per_strip", "y_chunk_rows"} & set(kw)
+        assert restored[0] in ONE_PASS or (plan and before[0] != restored[0])
