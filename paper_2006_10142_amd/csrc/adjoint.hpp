@@ -758,6 +758,9 @@ adi_status adj_backward(adi_wave_s* w, const adi_source* f, const adi_receivers*
     const int last = a->ncheck - 1;
     auto recompute = [&](int c) -> adi_status {
         if (a->kept && c + 1 >= last) return ADI_OK;
+        // from here on the storage holds other levels than the kept ones (cleared before
+        // they are queued: a reverse pass that fails half way must not leave it set)
+        if (c + 1 < last) a->kept = false;
         const int k0 = 1 + c * K;
         const int n = std::min(K, S - c * K);
         hipStream_t s1 = w->stream;
@@ -829,7 +832,6 @@ adi_status adj_backward(adi_wave_s* w, const adi_source* f, const adi_receivers*
         }
         ADI_HIP(hipEventRecord(a->ev_rev[c & 1], w->stream));
     }
-    if (last > 1) a->kept = false;       // the storage was used for earlier segments
     return ADI_OK;
 }
 

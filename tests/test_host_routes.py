@@ -37,3 +37,43 @@ for kw in (dict(x_rows_per_strip=4), dict(y_chunk_rows=16), dict(fused_lane_node
         assert not set(after + forward) & set(ONE_PASS), (kw, after, forward)
         plan = {"x_rows_per_strip", "y_chunk_rows"} & set(kw)
         assert restored[0] in ONE_PASS or (plan and before[0] != restored[0])
+
+
+ADJOINT = '''
+def forward(w, nsteps, every, s=0):
+    rid = ct.c_ulonglong()
+    names()
+    _lib.check(lib.adi_adjoint_forward(w, A, B, None, None, nsteps, every, ct.byref(rid)))
+    return short(names())
+
+def backward(w):
+    """status, steps of the forward run's kind queued again, exact steps queued"""
+    names()
+    st = lib.adi_adjoint_backward(w, 0, None, None, None, D, None)
+    k = short(names())
+    return st, k.count("k_fused4") + k.count("k_fusedr"), k.count("k_xsweep")
+'''
+
+
+@pytest.mark.parametrize("rmax,f64", [(0.1, 0), (0.1, 1)])
+def test_reverse_pass_after_one_that_failed(rmax, f64):
+    """Four segments of two steps whose last two are in the segment storage; a reverse pass
+    that fails at each of its event records in turn.  The next one may take the kept levels
+    only if no earlier segment was recomputed over them."""
+    got = recorder.run(ADJOINT + f'''
+out = []
+for n in range(9):
+    w = wave(256, 256, {rmax}, {f64})
+    forward(w, 8, 2)
+    first = backward(w)
+    forward(w, 8, 2)
+    rec.rec_fail_event(n)
+    failed = backward(w)
+    rec.rec_fail_event(-1)
+    out.append([first, failed, backward(w)])
+    _lib.check(lib.adi_wave_destroy(w))
+''')
+    for first, failed, again in got:
+        assert first == [0, 4, 4] and failed[0] == -3 and again[0] == 0
+        assert again[1:] == ([4, 4] if failed[2] else [0, 4])
+    assert {f[2] for _, f, _ in got} >= {0, 2, 4}
