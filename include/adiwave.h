@@ -123,7 +123,10 @@ adi_status adi_wave_start(adi_wave_t w, const void* u0, const void* psi,
  * On entry *u_prev, *u_curr point to u^{n-1}, u^n.  Each step writes u^{n+1}
  * over u^{n-1} and swaps the two pointers, so on return *u_curr points to
  * u^{n+nsteps} and *u_prev to u^{n+nsteps-1} (the roles rotate as the
- * paper's swap of level matrices).  f, rec: may be NULL.  nsteps >= 0. */
+ * paper's swap of level matrices).  f, rec: may be NULL.  nsteps >= 0.
+ * Under stream capture the replayed kernels are those of the call: the one-pass
+ * step where the handle's fused_step is 1 (its coefficients have to stay within the
+ * bound of fused_allowed then, also those set between replays), else the exact step. */
 adi_status adi_wave_step(adi_wave_t w, void** u_prev, void** u_curr,
                          const adi_source* f, const adi_receivers* rec, int nsteps);
 

@@ -429,6 +429,18 @@ adi_status alloc_chunks(adi_wave_s* w)
     return ADI_OK;
 }
 
+// Work queued now is recorded for replay (the legacy default stream cannot capture).
+bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (!st) return false;
+    if (hipStreamIsCapturing(st, &c) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return c == hipStreamCaptureStatusActive;
+}
+
 bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
 
 adi_status check_handle(adi_wave_t w)
@@ -1052,7 +1064,11 @@ adi_status do_step(adi_wave_s* w, void** u_prev, void** u_curr, const adi_source
                    const adi_receivers* rec, int nsteps, int kind = kStepDefault, T* keep = nullptr)
 {
     const bool cr = kind == kStepDefault && w->cr;
-    const bool one_pass = kind != kStepExact && (w->fstep || (w->fwide && kind == kStepDefault));
+    // A captured step is replayed as it is after set_kappa has measured another coefficient,
+    // so the forms beside the tuned one-pass step, which their grids took silently, are
+    // not captured: such a graph holds the exact step, right for any coefficient.
+    const bool one_pass = kind != kStepExact &&
+                          (w->fstep || (w->fwide && kind == kStepDefault && !capturing(w->stream)));
     const bool fused = !cr && one_pass && aligned16(*u_prev) && aligned16(*u_curr) && aligned16(keep);
     const bool recs = rec && rec->count > 0;
     auto record = [&](int k, const void* level) -> adi_status {

@@ -77,3 +77,23 @@ for n in range(9):
         assert first == [0, 4, 4] and failed[0] == -3 and again[0] == 0
         assert again[1:] == ([4, 4] if failed[2] else [0, 4])
     assert {f[2] for _, f, _ in got} >= {0, 2, 4}
+
+
+@pytest.mark.parametrize("nx,ny,rmax,f64", [(64, 1600, 0.5, 0), (65, 1600, 0.17, 0), (2051, 1953, 0.17, 0),
+                                            (65, 1600, 0.13, 1)])
+def test_captured_steps_take_any_coefficient(nx, ny, rmax, f64):
+    """A graph of steps replays the kernels it was captured with after set_kappa has given
+    the handle another coefficient: where the exact step was captured before these forms
+    were there, it still is.  The forms come back outside the capture."""
+    got = recorder.run(f'''
+w = wave({nx}, {ny}, {rmax}, {f64})
+eager = short(step(w, 2))
+_lib.check(lib.adi_wave_set_stream(w, 5))
+rec.rec_capturing(1)
+captured = short(step(w, 2))
+rec.rec_capturing(0)
+out = [eager, captured, short(step(w, 2))]
+''')
+    eager, captured, after = got
+    assert len(eager) == 2 and set(eager) <= set(ONE_PASS) and after == eager
+    assert captured.count("k_xsweep") == 2 and not set(captured) & set(ONE_PASS)
