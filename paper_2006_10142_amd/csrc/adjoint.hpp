@@ -497,6 +497,8 @@ struct adi_adjoint_s {
     void* seg = nullptr;         // 2 x K fields, one half per segment parity: levels
                                  // u^{k0+1..k0+K}
     bool kept = false;           // seg holds the forward run's own levels of its last two segments
+    bool captured = false;       // a forward run was captured: its replays, of which nothing is known
+                                 // here, renew the checkpoints only, so no run keeps levels any more
     void* work = nullptr;        // 6 fields: forward levels (2; during the reverse pass the
                                  // recomputation's x-sweep output), lambda (2), t, z
     void* rmap = nullptr;        // nx*ny + receiver count + ny ints: receiver map of the reverse pass
@@ -644,7 +646,8 @@ adi_status adj_forward(adi_wave_s* w, const void* u_prev, const void* u_curr, co
     // its segment storage, this run writes their levels there and they need no
     // recomputation (at 1024^2 FP32, 18 us a step with nothing to run beside it for the
     // last one).  Without it the reverse pass runs them again with the same step.
-    a->kept = a->seg_cap >= 2 * (size_t)K * F;
+    if (capturing(w->stream)) a->captured = true;
+    a->kept = !a->captured && a->seg_cap >= 2 * (size_t)K * F;
     ADI_HIP(hipMemcpyAsync(p, u_prev, F, hipMemcpyDeviceToDevice, w->stream));
     ADI_HIP(hipMemcpyAsync(q, u_curr, F, hipMemcpyDeviceToDevice, w->stream));
     // the handle's step without cyclic reduction: the one-pass step where it is
@@ -675,6 +678,7 @@ adi_status adj_backward(adi_wave_s* w, const adi_source* f, const adi_receivers*
     const size_t F = a->field;
     const int S = a->nsteps, K = a->K;
     const long long npts = (long long)w->nx * w->ny;
+    if (capturing(w->stream)) a->kept = false;   // a second replay finds other levels there
     if (adi_status s = grow(&a->seg, &a->seg_cap, 2 * (size_t)K * F)) return s;
     if (adi_status s = adjoint_streams(a)) return s;
     // the recomputation's y-chunk workspace: the handle's planes (the static interface

@@ -97,3 +97,26 @@ out = [eager, captured, short(step(w, 2))]
     eager, captured, after = got
     assert len(eager) == 2 and set(eager) <= set(ONE_PASS) and after == eager
     assert captured.count("k_xsweep") == 2 and not set(captured) & set(ONE_PASS)
+
+
+def test_captured_forward_run_keeps_no_levels():
+    """A captured forward run may be replayed between an eager one and its reverse pass, and
+    after the segment storage has been replaced: it writes checkpoints only, and from then
+    on every reverse pass recomputes.  A captured reverse pass may be replayed twice."""
+    got = recorder.run(ADJOINT + '''
+w = wave(256, 256, 0.1)
+_lib.check(lib.adi_wave_set_stream(w, 5))
+forward(w, 8, 2)
+out = [backward(w)]
+forward(w, 8, 2)
+out.append(backward(w))                 # levels kept by the eager run
+forward(w, 8, 2)
+rec.rec_capturing(1)
+out.append(backward(w))
+forward(w, 8, 2)
+rec.rec_capturing(0)
+out.append(backward(w))
+forward(w, 8, 2)                        # the graph of the run above may be replayed after this one
+out.append(backward(w))
+''')
+    assert got == [[0, 4, 4], [0, 0, 4], [0, 4, 4], [0, 4, 4], [0, 4, 4]]
