@@ -6,8 +6,8 @@
 // (I - beta K^{n+1} Lxx)(I - beta K^{n+1} Lyy): the x-lines, then the y-lines and
 // the update, with exact line solves on the coefficient r^{n+1}.  For a coefficient
 // constant in time it is the plain step.  Two launches where a row fits 256 threads and
-// a column one workgroup (k_tdc_x and the whole-column y-solve: 1024^2 FP32 22 us a
-// step, 203 before), else the separate kernels.  Included at the end of
+// a column one workgroup (k_tdc_x and the whole-column y-solve: 1024^2 FP32 23 us a
+// step, 203 by the separate kernels), else the separate kernels.  Included at the end of
 // adiwave.hip.
 
 namespace adw {
@@ -35,9 +35,12 @@ __global__ void __launch_bounds__(256) k_rhs_tdc(const T* __restrict__ uc, const
 // r^{n+1} = sn * kn and r^{n-1} = sp * kp formed where they are used, the right-hand side
 // above with the point sources, the row's entry pivots from r^{n+1} (one scan of pivot
 // maps, xsweep.hpp), and the line solve.  r^{n+1} and the entry pivots are written as the
-// handle's (rout NULL: the coefficient is unchanged).  Bound by latency at 1024^2; as
-// launches of their own the same work took 27 us a step there, this kernel 12.7 (FP32;
-// 3 us of it the write of r).
+// handle's (rout NULL: the coefficient is unchanged).  The maps are formed and composed in
+// FP64, as in k_xpivots: composed in FP32 the step at 1024^2 takes 22.2 us instead of 23.2,
+// but at r = 2 the pivots are further from 64 bits than a sequential FP32 sweep's (rms
+// 5.7e-8 on 4-node segments and 5.52e-8 on 8, against 5.5e-8 and 5.47e-8; in FP64 4.9e-8
+// and 5.2e-8).  Bound by latency at 1024^2; as launches of their own the same work took
+// 27 us a step there.
 template <typename T>
 struct TdcArgs {
     XArgs<T> x;          // u = u^n, qin and w written; sources
@@ -52,7 +55,7 @@ struct TdcArgs {
 template <typename T, int TR>
 struct TdcShared {
     XShared<T, TR, false> x;
-    PivotMap<T> tot[2][TR / 64];
+    PivotMap<double> tot[2][TR / 64];
 };
 
 template <typename T, int TR>
@@ -108,9 +111,9 @@ __global__ void __launch_bounds__(256) k_tdc_x(TdcArgs<T> B)
             rho[e] = fma_rn(B.sp * rp[e] - rc[e], sp[e], T(2) * rc[e] * su[e]);
         }
         if (it == 0) stage_sources<T, TR, false>(A, j0, RS, t, sh.x);   // (seen after entry_pivot's barrier)
-        PivotMap<T> m{T(0), T(1), T(0)};
-        if (act) m = pivot_map(rc);
-        const T q = entry_pivot(m, sh.tot[it & 1], lane, wv);
+        PivotMap<double> m{0.0, 1.0, 0.0};
+        if (act) m = pivot_map<double>(rc);
+        const T q = (T)entry_pivot(m, sh.tot[it & 1], lane, wv);
         const int ns = sh.x.src_n;
         for (int k = 0; live && k < (ns >= 0 ? ns : A.nsrc); ++k) {
             int i = -1;

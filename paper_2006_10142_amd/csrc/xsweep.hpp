@@ -374,14 +374,15 @@ __device__ __forceinline__ M pivot_after(const PivotMap<M>& a, M q)
 {
     return a.al + a.be * (q * nr_rcp(M(1) - a.ga * q));
 }
-// the map of the run of nodes r[0 .. N), and of every run of lanes 0 .. l of a wavefront
-template <typename M, int N>
-__device__ __forceinline__ PivotMap<M> pivot_map(const M (&r)[N])
+// the map of the run of nodes r[0 .. N), formed in M; and of every run of lanes 0 .. l of
+// a wavefront
+template <typename M, typename R, int N>
+__device__ __forceinline__ PivotMap<M> pivot_map(const R (&r)[N])
 {
     M q = M(0), pi = M(1), ga = M(0);
 #pragma unroll
     for (int e = 0; e < N; ++e) {
-        (void)pivot_step<M>(r[e], q);
+        (void)pivot_step<M>((M)r[e], q);
         const M p = pi * q;
         ga = fma_rn(pi, p, ga);
         pi = p;
@@ -434,7 +435,7 @@ __global__ void __launch_bounds__(TR >= 256 ? TR : 256)
 #pragma unroll
     for (int e = 0; e < kSeg; ++e) rr[e] = (double)rv[e];   // 0 past the row's end
     PivotMap<double> m{0.0, 1.0, 0.0};
-    if (act) m = pivot_map(rr);
+    if (act) m = pivot_map<double>(rr);
     double q = entry_pivot(m, tot[g], t & 63, t >> 6);
     if (!act) return;
     qin[(size_t)j * nseg + t] = (T)q;

@@ -40,9 +40,12 @@ struct YColArgs {
     T* rec_out;
 };
 
-template <typename T, int CB>
+template <typename T, int CB, bool DYN>
 struct YColShared {
-    T m[4][kYcP][CB + 1];            // G (then g_in), Q, H (then x_below), E
+    union {
+        T m[4][kYcP][CB + 1];                    // G (then g_in), Q, H (then x_below), E
+        double v[DYN ? 3 : 1][kYcP][CB + 1];     // DYN: the pivot maps al (then al of the run so far), be, ga
+    };
 };
 struct YPivShared {
     double m[3][kYcP][kYpCB + 1];    // al (then the entry pivot), be, ga
@@ -89,7 +92,7 @@ __global__ void __launch_bounds__(kYcP * CB) k_ycol(YColArgs<T> A)
 {
     constexpr int ES = (int)sizeof(T);
     constexpr bool PRE = S * ES <= 64;
-    __shared__ YColShared<T, CB> sh;
+    __shared__ YColShared<T, CB, DYN> sh;
     const int blk = xcd_band(blockIdx.x);                 // neighbouring columns on one XCD
     if (blk * CB >= A.nx) return;
     const int t = threadIdx.x, lane = t & 63;
@@ -122,21 +125,21 @@ __global__ void __launch_bounds__(kYcP * CB) k_ycol(YColArgs<T> A)
         }
     }
     if constexpr (DYN) {
-        const PivotMap<T> own = pivot_map(q);
-        sh.m[0][p][col] = own.al;
-        sh.m[1][p][col] = own.be;
-        sh.m[2][p][col] = own.ga;
+        const PivotMap<double> own = pivot_map<double>(q);  // (in FP64: the pivots of k_ycol_pivots)
+        sh.v[0][p][col] = own.al;
+        sh.v[1][p][col] = own.be;
+        sh.v[2][p][col] = own.ga;
         __syncthreads();
         for (int c = wv; c < CB; c += nw) {
-            PivotMap<T> m{T(0), T(1), T(0)};
-            if (lane < P) m = {sh.m[0][lane][c], sh.m[1][lane][c], sh.m[2][lane][c]};
+            PivotMap<double> m{0.0, 1.0, 0.0};
+            if (lane < P) m = {sh.v[0][lane][c], sh.v[1][lane][c], sh.v[2][lane][c]};
             m = pivot_scan(m, lane);
-            if (lane < P) sh.m[3][lane][c] = m.al;          // the run's last pivot from 0
+            if (lane < P) sh.v[0][lane][c] = m.al;          // the run's last pivot from 0
         }
         __syncthreads();
-        if (p > 0) qq = sh.m[3][p - 1][col];
+        if (p > 0) qq = (T)sh.v[0][p - 1][col];
         fr_store1<T, 0>(qq, rq, qoff, 0);
-        __syncthreads();                                    // m[0 .. 3] are written again
+        __syncthreads();                                    // the maps' place is written again
     }
     const bool sc = A.rhs_times_r != 0;
     {

@@ -44,3 +44,29 @@ def test_step_on_an_unmeasured_coefficient(adw, oracle_lib, nx, ny, r0, dtype, p
     _, ref, _ = oracle_lib.run(k1.astype(np.float64), up.astype(np.float64), uc.astype(np.float64), h, dt, 1)
     assert rel_l2(b.cpu().numpy(), ref) <= tol
     wave.close()
+
+
+@pytest.mark.parametrize("nx,ny", [(60, 200), (301, 211), (1000, 1000), (1999, 2040), (2048, 130)])
+def test_pivots_are_those_of_set_kappa(adw, nx, ny):
+    """The FP32 pivots a time-dependent step leaves are those set_kappa builds (composed in
+    FP64, rounded once): the plain exact step after either has the same bits.  r up to 2,
+    where maps composed in FP32 are further off than a sequential sweep."""
+    print(f"pivots after tdc {nx}x{ny}", flush=True)
+    tt = torch.float32
+    g = torch.Generator(device="cuda").manual_seed(nx + ny)
+    h = 1.0 / (max(nx, ny) + 1)
+    k = (1.0 / 9.0 + 8.0 / 9.0 * torch.rand(ny, nx, device="cuda", generator=g)).to(tt)
+    u = torch.randn(ny, nx, device="cuda", generator=g).to(tt)
+    v = torch.randn(ny, nx, device="cuda", generator=g).to(tt)
+    out = []
+    for by_step in (True, False):
+        w = adw.Wave(nx, ny, h, 2.0 * h, c=1.0, dtype=tt)      # r = 2 kappa
+        w.set_tuning(fused_step=False)
+        if by_step:
+            w.step_tdc(u.clone(), v.clone(), kappa_prev=k, kappa_next=k)
+        else:
+            w.set_kappa(k)
+        _, b = w.step(u.clone(), v.clone(), 1)
+        out.append(b.clone())
+        w.close()
+    assert torch.equal(*out)
