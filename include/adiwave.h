@@ -396,7 +396,7 @@ adi_status adi_wave_get_info(adi_wave_t w, adi_wave_info* info);
  * Any field <= 0 keeps the current value.  Reallocates chunk workspace if the
  * chunk size changes (synchronises the stream). */
 typedef struct {
-    int x_threads_per_line;   /* 64, 128, 256 or 1024, with 8 * threads >= nx */
+    int x_threads_per_line;   /* 64, 128, 256, 512 or 1024, with 8 * threads >= nx */
     int x_rows_per_strip;     /* >= 1 (unfused plans; a fused strip is one y-chunk) */
     int y_fused;              /* 1 = fuse the y-chunk elimination into the x-sweep, 2 = separate
                                  (either, like y_chunk_rows, takes the chunked y-solve instead

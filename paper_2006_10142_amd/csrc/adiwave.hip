@@ -1288,8 +1288,8 @@ adi_status adi_wave_set_tuning(adi_wave_t w, const adi_tuning* t)
     if (t->x_rows_per_strip > 0) xp.rs = t->x_rows_per_strip;
     if (t->y_fused == 1) xp.fuse = 1;
     if (t->y_fused == 2) xp.fuse = 0;
-    if (t->x_threads_per_line > 0 && xp.tr != 64 && xp.tr != 128 && xp.tr != 256 && xp.tr != 1024)
-        return fail(ADI_EINVAL, "x_threads_per_line must be 64, 128, 256 or 1024");
+    if (xp.tr != 64 && xp.tr != 128 && xp.tr != 256 && xp.tr != 512 && xp.tr != 1024)
+        return fail(ADI_EINVAL, "x_threads_per_line must be 64, 128, 256, 512 or 1024");
     if (8LL * xp.tr < w->nx) return fail(ADI_EINVAL, "8 * x_threads_per_line must cover nx");
     if (xp.fuse && !fuse_fits(xp.tr, w->dtype))
         return fail(ADI_EUNSUPPORTED, "fused y-reduction does not fit in LDS for this plan");

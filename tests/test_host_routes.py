@@ -120,3 +120,21 @@ forward(w, 8, 2)                        # the graph of the run above may be repl
 out.append(backward(w))
 ''')
     assert got == [[0, 4, 4], [0, 0, 4], [0, 4, 4], [0, 4, 4], [0, 4, 4]]
+
+
+@pytest.mark.parametrize("f64", [0, 1])
+def test_reported_line_groups_are_accepted(f64):
+    """x_threads_per_line as adi_wave_get_info reports it can be set again, also after other
+    widths, on rows of every width."""
+    got = recorder.run(f'''
+out = []
+for nx in (8, 512, 513, 1025, 2048, 2049, 3000, 4096, 4097, 8192):
+    w = wave(nx, 64, 2.0, {f64})
+    tr = info(w)["x_threads_per_line"]
+    sts = [tune(w, x_threads_per_line=tr), tune(w, x_threads_per_line=1024), tune(w, x_threads_per_line=tr)]
+    out.append([nx, tr, sts, info(w)["x_threads_per_line"], step(w)[0]])
+    _lib.check(lib.adi_wave_destroy(w))
+''')
+    for nx, tr, sts, again, kernel in got:
+        assert sts == [0, 0, 0] and again == tr and f"Li{tr}E" in kernel, (nx, tr, sts)
+    assert {tr for _, tr, *_ in got} == {64, 128, 256, 512, 1024}
