@@ -393,7 +393,7 @@ typedef struct {
 adi_status adi_wave_get_info(adi_wave_t w, adi_wave_info* info);
 
 /* Override the launch configuration chosen at create (for the autotuner).
- * Any field <= 0 keeps the current value.  Reallocates chunk workspace if the
+ * Any field <= 0 keeps the current value.  A refused call changes nothing.  Reallocates chunk workspace if the
  * chunk size changes (synchronises the stream). */
 typedef struct {
     int x_threads_per_line;   /* 64, 128, 256, 512 or 1024, with 8 * threads >= nx */

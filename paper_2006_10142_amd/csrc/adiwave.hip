@@ -1321,16 +1321,6 @@ adi_status adi_wave_set_tuning(adi_wave_t w, const adi_tuning* t)
         return fail(ADI_EINVAL, "column strips take four nodes per lane");
     if (t->fused_segment_rows > 0 && wt_req > kF4Wmax)
         return fail(ADI_EINVAL, "column strips are at most 240 columns wide");
-    const bool two_pass = t->x_threads_per_line > 0 || t->x_rows_per_strip > 0 || t->y_fused > 0 || t->y_chunk_rows > 0;
-    if (two_pass) w->two_pass_user = 1;
-    if (t->fused_step > 0) w->fused_mode = t->fused_step;
-    if (t->fused_segment_rows) w->f_hs_user = t->fused_segment_rows == -1 ? 0 : t->fused_segment_rows;
-    if (t->fused_tile_cols > 0) w->f_wt_user = t->fused_tile_cols;
-    if (t->fused_tile_cols == -1) w->f_wt_user = 0;
-    if (t->fused_lane_nodes) w->f_lane_user = t->fused_lane_nodes > 0 ? t->fused_lane_nodes : 0;
-    if (t->fused_step > 0 || t->fused_tile_cols > 0 || t->fused_tile_cols == -1 || t->fused_lane_nodes ||
-        t->fused_segment_rows || two_pass)
-        fused_plan(w);
     if (t->line_solver < 0 || t->line_solver > 2) return fail(ADI_EINVAL, "line_solver must be 0, 1 or 2");
     if (t->line_solver == 2 && !w->cr_abc) {
         const size_t bytes = 3 * (size_t)w->nx * w->ny * esize(w->dtype);
@@ -1341,6 +1331,17 @@ adi_status adi_wave_set_tuning(adi_wave_t w, const adi_tuning* t)
         }
         w->bytes += bytes;
     }
+    // every setting is valid: from here on the plan changes
+    const bool two_pass = t->x_threads_per_line > 0 || t->x_rows_per_strip > 0 || t->y_fused > 0 || t->y_chunk_rows > 0;
+    if (two_pass) w->two_pass_user = 1;
+    if (t->fused_step > 0) w->fused_mode = t->fused_step;
+    if (t->fused_segment_rows) w->f_hs_user = t->fused_segment_rows == -1 ? 0 : t->fused_segment_rows;
+    if (t->fused_tile_cols > 0) w->f_wt_user = t->fused_tile_cols;
+    if (t->fused_tile_cols == -1) w->f_wt_user = 0;
+    if (t->fused_lane_nodes) w->f_lane_user = t->fused_lane_nodes > 0 ? t->fused_lane_nodes : 0;
+    if (t->fused_step > 0 || t->fused_tile_cols > 0 || t->fused_tile_cols == -1 || t->fused_lane_nodes ||
+        t->fused_segment_rows || two_pass)
+        fused_plan(w);
     if (t->line_solver > 0) w->cr = t->line_solver == 2 ? 1 : 0;
     if (xp.fuse && (M != w->M || !w->xp.fuse)) xp.frs = fused_rows(M);
     w->xp = xp;

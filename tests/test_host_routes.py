@@ -138,3 +138,21 @@ for nx in (8, 512, 513, 1025, 2048, 2049, 3000, 4096, 4097, 8192):
     for nx, tr, sts, again, kernel in got:
         assert sts == [0, 0, 0] and again == tr and f"Li{tr}E" in kernel, (nx, tr, sts)
     assert {tr for _, tr, *_ in got} == {64, 128, 256, 512, 1024}
+
+
+def test_a_refused_tuning_changes_nothing():
+    """Every refused call of adi_wave_set_tuning, with valid settings beside the bad one,
+    leaves the plan and the step as they were."""
+    got = recorder.run('''
+out = []
+good = dict(x_rows_per_strip=4, y_chunk_rows=32, fused_step=2, fused_tile_cols=64, fused_segment_rows=64)
+for nx, ny, r in ((64, 1600, 0.5), (256, 256, 0.1), (65, 1600, 0.17), (128, 128, 2.0)):
+    w = wave(nx, ny, r)
+    before = [info(w), step(w)]
+    for bad in (dict(line_solver=3), dict(line_solver=-1), dict(x_threads_per_line=96), dict(y_chunk_rows=8),
+                dict(fused_step=3), dict(fused_lane_nodes=5), dict(fused_tile_cols=12), dict(fused_segment_rows=4)):
+        st = tune(w, **{**good, **bad})
+        out.append([nx, ny, bad, st, [info(w), step(w)] == before])
+''')
+    for nx, ny, bad, st, same in got:
+        assert st == -1 and same, (nx, ny, bad)
