@@ -393,8 +393,12 @@ typedef struct {
 adi_status adi_wave_get_info(adi_wave_t w, adi_wave_info* info);
 
 /* Override the launch configuration chosen at create (for the autotuner).
- * Any field <= 0 keeps the current value.  A refused call changes nothing.  Reallocates chunk workspace if the
- * chunk size changes (synchronises the stream). */
+ * Any field <= 0 keeps the current value, unless its comment gives a negative one a
+ * meaning.  A refused call changes nothing.  Reallocates chunk workspace if the
+ * chunk size changes (synchronises the stream).
+ * The first four fields are a plan of the exact step.  Where the tuned one-pass step is
+ * allowed they do not decide which step runs (fused_step does); where one of its other
+ * forms would run, setting any of them takes the exact step instead. */
 typedef struct {
     int x_threads_per_line;   /* 64, 128, 256, 512 or 1024, with 8 * threads >= nx */
     int x_rows_per_strip;     /* >= 1 (unfused plans; a fused strip is one y-chunk) */
@@ -403,7 +407,9 @@ typedef struct {
                                  of the whole-column one of short columns) */
     int y_chunk_rows;         /* 16 or 32 */
     int fused_step;           /* 1 = one-pass step when allowed (else ADI_EUNSUPPORTED),
-                                 2 = exact two-pass step, 0 = keep */
+                                 2 = exact two-pass step, 0 = keep, -1 = back to the
+                                 automatic choice of the step and of the exact step's plan
+                                 (the first four fields), as after create */
     int line_solver;          /* 1 = partition / scan line solvers (default),
                                  2 = cyclic reduction, one launch per level for all lines
                                  of a sweep (the paper's Sec. 3.1 solver, as a same-GPU

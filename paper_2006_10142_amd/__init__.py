@@ -295,8 +295,10 @@ class Wave:
                    fused_lane_nodes=0, fused_segment_rows=0):
         """Override the launch plan (0 / None keeps the current value).  fused_step:
         True = one-pass step (when its truncation bound holds: FP32 r <= 0.18 and nx % 4
-        == 0, FP64 r <= 0.13 and nx even), False = exact two-pass step.  cyclic_reduction: True = the paper's cyclic-reduction line
-        solver (one launch per level, for comparison), False = the default solvers.
+        == 0, FP64 r <= 0.13 and nx even), False = exact two-pass step, "auto" = the automatic
+        choice of the step and of the exact step's plan, as in a new handle.
+        cyclic_reduction: True = the paper's cyclic-reduction line solver (one launch per
+        level, for comparison), False = the default solvers.
         fused_tile_cols: one-pass tile width (multiple of 8, <= 496; FP64 strips <= 64;
         -1 = automatic).
         fused_lane_nodes: one-pass x-line nodes per lane, 8 or 4 (4: tiles of at most
@@ -305,7 +307,7 @@ class Wave:
         -2 = 64-row tiles, -1 = automatic."""
         self._sync_stream()
         f = 0 if y_fused is None else (1 if y_fused else 2)
-        fs = 0 if fused_step is None else (1 if fused_step else 2)
+        fs = 0 if fused_step is None else -1 if fused_step == "auto" else (1 if fused_step else 2)
         ls = 0 if cyclic_reduction is None else (2 if cyclic_reduction else 1)
         t = _lib.AdiTuning(x_threads_per_line, x_rows_per_strip, f, y_chunk_rows, fs, ls,
                            fused_tile_cols, fused_lane_nodes, fused_segment_rows)

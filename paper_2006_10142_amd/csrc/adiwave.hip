@@ -334,6 +334,8 @@ struct adi_wave_s {
     void* qy = nullptr;    // qy_n = ceil(ny / ycs) * nx entry pivots of the y-line segments (ycol.hpp)
     size_t qy_n = 0;
     int ycs = 0;           // rows per thread of the whole-column y-solve; 0: the chunked y-solve
+    XPlan xp0{};           // the exact step's plan as chosen at create: x-sweep,
+    int M0 = 32, ycs0 = 0; //   chunk rows, rows per thread of the whole-column y-solve
     int nseg = 0;
     int nxp = 0;           // nx rounded up to the summary-plane column block
     size_t w_cap = 0;      // elements of w (also create-time scratch of 5*K*nx)
@@ -877,6 +879,17 @@ void coef_unmeasured(adi_wave_s* w)
     fused_plan(w);
 }
 
+// what the y-lines of the handle's plan need of r: the column pivots or the chunk planes
+template <typename T>
+adi_status y_coef(adi_wave_s* w)
+{
+    if (!w->ycs) return static_planes<T>(w);
+    if (!launch_ycol_pivots<T>(w->ycs, static_cast<const T*>(w->r), static_cast<T*>(w->qy), w->nx, w->ny, w->stream))
+        return fail(ADI_EUNSUPPORTED, "no column pivot kernel for this plan");
+    ADI_LAUNCHED("y_pivots");
+    return ADI_OK;
+}
+
 void adjoint_invalidate(adi_wave_s* w);   // adjoint.hpp
 
 template <typename T>
@@ -896,13 +909,7 @@ adi_status set_coef(adi_wave_s* w, const void* field, double scalar, int squared
     ADI_LAUNCHED("x_pivots");
     if (measure)
         if (adi_status s = measure_rmax<T>(w)) return s;
-    if (w->ycs) {
-        if (!launch_ycol_pivots<T>(w->ycs, static_cast<const T*>(w->r), static_cast<T*>(w->qy), w->nx, w->ny, w->stream))
-            return fail(ADI_EUNSUPPORTED, "no column pivot kernel for this plan");
-        ADI_LAUNCHED("y_pivots");
-        return ADI_OK;
-    }
-    return static_planes<T>(w);
+    return y_coef<T>(w);
 }
 
 template <typename T>
@@ -1177,6 +1184,9 @@ adi_status adi_wave_create(adi_wave_t* out, int nx, int ny, double h, double dt,
     w->nseg = (nx + kSeg - 1) / kSeg;
     if (!xp.fuse) w->ycs = choose_ycol(nx, ny, dtype);
     if (w->ycs) w->qy_n = (size_t)((ny + w->ycs - 1) / w->ycs) * nx;
+    w->xp0 = w->xp;
+    w->M0 = M;
+    w->ycs0 = w->ycs;
     if (hipMalloc(&w->r, npts * es) != hipSuccess ||
         hipMalloc(&w->qin, (size_t)ny * w->nseg * es) != hipSuccess ||
         (w->ycs && hipMalloc(&w->qy, w->qy_n * es) != hipSuccess) ||
@@ -1283,7 +1293,9 @@ adi_status adi_wave_set_tuning(adi_wave_t w, const adi_tuning* t)
 {
     if (adi_status s = check_handle(w)) return s;
     if (!t) return fail(ADI_EINVAL, "tuning is null");
-    XPlan xp = w->xp;
+    // fused_step -1: everything from the automatic choice again, then what else is set here
+    const bool reset = t->fused_step == -1;
+    XPlan xp = reset ? w->xp0 : w->xp;
     if (t->x_threads_per_line > 0) xp.tr = t->x_threads_per_line;
     if (t->x_rows_per_strip > 0) xp.rs = t->x_rows_per_strip;
     if (t->y_fused == 1) xp.fuse = 1;
@@ -1293,9 +1305,9 @@ adi_status adi_wave_set_tuning(adi_wave_t w, const adi_tuning* t)
     if (8LL * xp.tr < w->nx) return fail(ADI_EINVAL, "8 * x_threads_per_line must cover nx");
     if (xp.fuse && !fuse_fits(xp.tr, w->dtype))
         return fail(ADI_EUNSUPPORTED, "fused y-reduction does not fit in LDS for this plan");
-    const int M = t->y_chunk_rows > 0 ? t->y_chunk_rows : w->M;
+    const int M = t->y_chunk_rows > 0 ? t->y_chunk_rows : reset ? w->M0 : w->M;
     if (M != 16 && M != 32) return fail(ADI_EINVAL, "y_chunk_rows must be 16 or 32");
-    if (t->fused_step < 0 || t->fused_step > 2) return fail(ADI_EINVAL, "fused_step must be 0, 1 or 2");
+    if (t->fused_step < -1 || t->fused_step > 2) return fail(ADI_EINVAL, "fused_step must be -1, 0, 1 or 2");
     if (t->fused_step == 1 && !w->fused_ok)
         return fail(ADI_EUNSUPPORTED, w->dtype == ADI_F64
                                           ? "the FP64 one-pass step needs nx % 2 == 0 and r <= 0.13 everywhere"
@@ -1333,29 +1345,31 @@ adi_status adi_wave_set_tuning(adi_wave_t w, const adi_tuning* t)
     }
     // every setting is valid: from here on the plan changes
     const bool two_pass = t->x_threads_per_line > 0 || t->x_rows_per_strip > 0 || t->y_fused > 0 || t->y_chunk_rows > 0;
+    if (reset) w->fused_mode = w->two_pass_user = 0;
     if (two_pass) w->two_pass_user = 1;
     if (t->fused_step > 0) w->fused_mode = t->fused_step;
     if (t->fused_segment_rows) w->f_hs_user = t->fused_segment_rows == -1 ? 0 : t->fused_segment_rows;
     if (t->fused_tile_cols > 0) w->f_wt_user = t->fused_tile_cols;
     if (t->fused_tile_cols == -1) w->f_wt_user = 0;
     if (t->fused_lane_nodes) w->f_lane_user = t->fused_lane_nodes > 0 ? t->fused_lane_nodes : 0;
-    if (t->fused_step > 0 || t->fused_tile_cols > 0 || t->fused_tile_cols == -1 || t->fused_lane_nodes ||
+    if (t->fused_step || t->fused_tile_cols > 0 || t->fused_tile_cols == -1 || t->fused_lane_nodes ||
         t->fused_segment_rows || two_pass)
         fused_plan(w);
     if (t->line_solver > 0) w->cr = t->line_solver == 2 ? 1 : 0;
-    if (xp.fuse && (M != w->M || !w->xp.fuse)) xp.frs = fused_rows(M);
+    const bool y_plan = t->y_fused > 0 || t->y_chunk_rows > 0;
+    if (xp.fuse && (M != w->M || !w->xp.fuse) && !(reset && !y_plan)) xp.frs = fused_rows(M);
     w->xp = xp;
     // a y plan set by the caller is one of the chunked solve
-    const bool M_changed = M != w->M;
-    const bool chunked = w->ycs && (t->y_fused > 0 || t->y_chunk_rows > 0);
-    if (chunked) w->ycs = 0;
+    const int ycs = y_plan ? 0 : reset ? w->ycs0 : w->ycs;
+    const bool y_changed = M != w->M || ycs != w->ycs;
+    w->ycs = ycs;
     if (M != w->M) {
         if (hipStreamSynchronize(w->stream) != hipSuccess)
             return fail(ADI_EHIP, "stream synchronise failed");
         w->M = M;
         if (adi_status s = alloc_chunks(w)) return s;
     }
-    if (chunked || M_changed) return w->dtype == ADI_F32 ? static_planes<float>(w) : static_planes<double>(w);
+    if (y_changed) return w->dtype == ADI_F32 ? y_coef<float>(w) : y_coef<double>(w);
     return ADI_OK;
 }
 

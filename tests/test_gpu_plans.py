@@ -42,3 +42,30 @@ def test_line_groups_of_512_threads(adw, oracle_lib, dtype, nx, ny, fused, m):
     _, ref, _ = oracle_lib.run(kap, u0, u1, h, dt, 10)
     assert rel_l2(b.cpu().numpy(), ref) <= tol
     wave.close()
+
+
+@pytest.mark.parametrize("nx,ny,rmax,dtype", [(64, 1600, 0.5, "f32"), (300, 211, 2.0, "f32"), (300, 211, 2.0, "f64"),
+                                              (65, 1600, 0.13, "f64")])
+def test_undone_plans_step_as_a_new_handle(adw, nx, ny, rmax, dtype):
+    """A chunked y plan, a new coefficient while it holds, then fused_step "auto": steps of
+    both kinds (the automatic one and the exact one) have the bits of a new handle's."""
+    print(f"undone plans {nx}x{ny} {dtype}", flush=True)
+    tt = torch.float32 if dtype == "f32" else torch.float64
+    g = torch.Generator(device="cuda").manual_seed(3)
+    h = 1.0 / (max(nx, ny) + 1)
+    k = (0.5 + 0.5 * torch.rand(ny, nx, device="cuda", generator=g)).to(tt)
+    u = torch.randn(ny, nx, device="cuda", generator=g).to(tt)
+    v = torch.randn(ny, nx, device="cuda", generator=g).to(tt)
+    got = []
+    for undo in (True, False):
+        w = adw.Wave(nx, ny, h, np.sqrt(2 * rmax) * h, c=1.0, dtype=tt)
+        if undo:
+            w.set_tuning(x_rows_per_strip=5, y_chunk_rows=32)
+        w.set_kappa(k)
+        if undo:
+            w.set_tuning(fused_step="auto")
+        _, a = w.step(u.clone(), v.clone(), 1)
+        b = w.start(u)                                        # the exact line solves
+        got.append((w.info(), a.clone(), b.clone()))
+        w.close()
+    assert got[0][0] == got[1][0] and torch.equal(got[0][1], got[1][1]) and torch.equal(got[0][2], got[1][2])

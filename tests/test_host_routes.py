@@ -156,3 +156,30 @@ for nx, ny, r in ((64, 1600, 0.5), (256, 256, 0.1), (65, 1600, 0.17), (128, 128,
 ''')
     for nx, ny, bad, st, same in got:
         assert st == -1 and same, (nx, ny, bad)
+
+
+@pytest.mark.parametrize("nx,ny,rmax,f64", [(64, 1600, 0.5, 0), (65, 1600, 0.17, 0), (65, 1600, 0.13, 1),
+                                            (256, 256, 0.1, 0), (128, 128, 2.0, 0), (128, 128, 2.0, 1),
+                                            (3000, 300, 2.0, 0), (3000, 4100, 2.0, 0), (300, 5000, 2.0, 1)])
+def test_plans_can_be_undone(nx, ny, rmax, f64):
+    """fused_step -1 brings the automatic choice back after any plan: the kernels of a new
+    handle, with the pivots or planes they read built again."""
+    got = recorder.run(f'''
+out = []
+for kw in (dict(x_rows_per_strip=5), dict(x_threads_per_line=1024), dict(y_fused=2), dict(y_chunk_rows=16),
+           dict(y_chunk_rows=32), dict(fused_step=2), dict(x_rows_per_strip=5, y_chunk_rows=32, fused_step=2)):
+    w = wave({nx}, {ny}, {rmax}, {f64})
+    first = [info(w), step(w)]
+    st = [tune(w, **kw)]
+    names()
+    st.append(tune(w, fused_step=-1))
+    built = short(names())
+    again = [info(w), step(w)]
+    _lib.check(lib.adi_wave_set_kappa(w, C, 1.0))
+    whole = first[0]["kernels_per_step"] == 2
+    out.append([kw, st, again == first, [info(w), step(w)] == first, whole, built])
+''')
+    for kw, st, same, after_kappa, whole, built in got:
+        assert st == [0, 0] and same and after_kappa, kw
+        if whole and ("y_fused" in kw or "y_chunk_rows" in kw):
+            assert "k_ycol_pivots" in built, (kw, built)
