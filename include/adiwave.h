@@ -281,8 +281,7 @@ typedef struct {
                                  2 (set only): exact two-pass step, 0 (set): keep */
     int fused_allowed;        /* read-only: the one-pass step is allowed for the batch (where
                                  rows that are no multiple of 4 values forbid it, FP32 within
-                                 r_max 0.18, adi_batch_step takes a form of it by itself unless
-                                 fused_step 2 is set) */
+                                 r_max 0.18, fused_form says what adi_batch_step takes) */
     int fused_items;          /* read-only: one-pass work items (tiles or strip segments)
                                  over all simulations */
     int fused_lane_nodes;     /* one-pass tiles: x-line nodes per lane, 8 (default) or 4
@@ -292,12 +291,20 @@ typedef struct {
                                  one width, in segments of at most 1024 rows), 0 (get): on
                                  tiles; set: 1 = strips, 2 = tiles, 0 = keep.  The
                                  autotuner times both tile kinds and the strips */
+    int fused_form;           /* batches of FP32 rows of any length within r_max 0.18, where
+                                 fused_allowed is 0: what adi_batch_step takes by itself.
+                                 1: one-pass step on four-node tiles, 2: on column strips,
+                                 3: exact step, 0 (get): no such batch; set: 0 = keep, -1 =
+                                 the automatic choice, others as get (ADI_EUNSUPPORTED for
+                                 other batches).  fused_step 2 sets 3, and the autotuner, which
+                                 else times all three, then keeps to the exact step */
 } adi_batch_plan;
 adi_status adi_batch_get_plan(adi_batch_t b, adi_batch_plan* p);
 adi_status adi_batch_set_plan(adi_batch_t b, const adi_batch_plan* p);
 
-/* Autotuner: times candidate plans (line-group width, then each launch's
- * persistent grid size) for trial_steps steps on scratch levels it allocates
+/* Autotuner: times candidate plans (the one-pass kinds or forms that apply; for the
+ * exact step the line-group width, then each launch's persistent grid size) for
+ * trial_steps steps on scratch levels it allocates
  * and frees, keeps the fastest plan and returns its milliseconds per step.
  * The bound levels are not touched.  Synchronises the stream. */
 adi_status adi_batch_autotune(adi_batch_t b, int trial_steps, double* best_ms_per_step);

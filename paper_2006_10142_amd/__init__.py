@@ -400,13 +400,16 @@ class Batch:
         _lib.check(_lib.load().adi_batch_get_plan(self._h, ctypes.byref(p)))
         return {f: getattr(p, f) for f, _ in _lib.AdiBatchPlan._fields_}
 
+    FORMS = {"auto": -1, None: 0, "tiles": 1, "strips": 2, "exact": 3}
+
     def set_plan(self, x_threads_per_line=0, x_grid=0, yscan_grid=0, ysolve_grid=0, fused_step=None,
-                 fused_lane_nodes=0, fused_strips=None):
+                 fused_lane_nodes=0, fused_strips=None, fused_form=None):
         """Launch plan of the two-pass step; fused_step: True = one-pass step for every
         simulation (FP32, when allowed), False = exact two-pass step, None = keep;
         fused_lane_nodes: 8 or 4 nodes per lane of the one-pass tiles (0 = keep);
         fused_strips: True = the one-pass step on column strips, False = on tiles,
-        None = keep."""
+        None = keep; fused_form: what FP32 batches on rows of any length take, "tiles",
+        "strips", "exact" or "auto" (adi_batch_plan in adiwave.h), None = keep."""
         p = _lib.AdiBatchPlan()
         _lib.check(_lib.load().adi_batch_get_plan(self._h, ctypes.byref(p)))
         if x_threads_per_line:
@@ -415,6 +418,7 @@ class Batch:
         p.fused_step = 0 if fused_step is None else (1 if fused_step else 2)
         p.fused_lane_nodes = fused_lane_nodes
         p.fused_strips = 0 if fused_strips is None else (1 if fused_strips else 2)
+        p.fused_form = self.FORMS[fused_form]
         _lib.check(_lib.load().adi_batch_set_plan(self._h, ctypes.byref(p)))
 
     def autotune(self, trial_steps: int = 10, cache: Optional[str] = None) -> float:
@@ -432,9 +436,12 @@ class Batch:
                     ent = None
                 if ent:
                     strips = ent.get("fused_strips")
+                    # (the file does not know the coefficient: a form is taken where it applies)
+                    form = ent.get("fused_form") if self.plan()["fused_form"] else None
                     self.set_plan(ent["x_threads_per_line"], ent["x_grid"], ent["yscan_grid"],
                                   ent["ysolve_grid"], fused_lane_nodes=ent.get("fused_lane_nodes", 0),
-                                  fused_strips=None if strips is None else bool(strips))
+                                  fused_strips=None if strips is None else bool(strips),
+                                  fused_form=form)
                     return float(ent["ms_per_step"])
         best = ctypes.c_double(0.0)
         _lib.check(_lib.load().adi_batch_autotune(self._h, int(trial_steps), ctypes.byref(best)))
@@ -448,6 +455,7 @@ class Batch:
                     data = {}
             data[key] = {k: p[k] for k in ("x_threads_per_line", "x_grid", "yscan_grid",
                                            "ysolve_grid", "fused_lane_nodes", "fused_strips")}
+            data[key]["fused_form"] = {v: k for k, v in self.FORMS.items()}[p["fused_form"]]
             data[key]["ms_per_step"] = best.value
             os.makedirs(os.path.dirname(os.path.abspath(cache)), exist_ok=True)
             json.dump(data, open(cache, "w"), indent=1)

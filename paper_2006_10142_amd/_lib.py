@@ -57,7 +57,7 @@ class AdiBatchPlan(ctypes.Structure):
                 ("yscan_items", ctypes.c_int), ("ysolve_items", ctypes.c_int),
                 ("fused_step", ctypes.c_int), ("fused_allowed", ctypes.c_int),
                 ("fused_items", ctypes.c_int), ("fused_lane_nodes", ctypes.c_int),
-                ("fused_strips", ctypes.c_int)]
+                ("fused_strips", ctypes.c_int), ("fused_form", ctypes.c_int)]
 
 
 _SIGNATURES = {

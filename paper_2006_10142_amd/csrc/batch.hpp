@@ -238,8 +238,9 @@ struct adi_batch_s {
     // one-pass step: allowed when every simulation allows it (FP32, bound holds)
     int fused_ok = 0, fused = 0;
     // where it is not, but its bound holds for all (FP32 rows that are no multiple of 16
-    // bytes): the form adi_batch_step takes by itself (batch_wide)
-    int wide = 0;
+    // bytes, wide_ok): the form adi_batch_step takes by itself (batch_wide, the autotuner or
+    // the plan; kWideNone: the exact step, with exact_user asked for by fused_step 2)
+    int wide_ok = 0, wide = 0, exact_user = 0;
     int flane = 8;                  // nodes per lane of the one-pass tiles (8 or 4)
     int fstrips = 0;                // 1: the one-pass step on column strips instead of tiles
     int2* fitems = nullptr;         // (simulation, tile) of the eight-node tiles, then the four-node
@@ -580,8 +581,9 @@ adi_status adi_batch_create(adi_batch_t* out, int count, const int* nx, const in
             if (!b->sims[s].fused_ok) b->fused_ok = 0;
             bound = bound && fused_bound_holds(b->sims[s].rmax, dtype);
         }
-        b->wide = bound && !b->fused_ok ? batch_wide(b->nodes) : kWideNone;
-        const bool lists = b->fused_ok || b->wide;
+        b->wide_ok = bound && !b->fused_ok;
+        b->wide = b->wide_ok ? batch_wide(b->nodes) : kWideNone;
+        const bool lists = b->fused_ok || b->wide_ok;
         std::vector<int2> fi;
         for (int s = 0; s < count && lists; ++s) {
             for (int tl = 0; tl < b->sims[s].f_tiles; ++tl) fi.push_back(make_int2(s, tl));
@@ -752,9 +754,11 @@ adi_status adi_batch_get_plan(adi_batch_t b, adi_batch_plan* p)
     p->ysolve_items = b->nyv_items;
     p->fused_step = b->fused;
     p->fused_allowed = b->fused_ok;
-    p->fused_items = b->fstrips ? b->nfs_segments : b->flane == 4 ? b->nf4_items : b->nf_items;
+    const bool strips = b->wide_ok ? b->wide == kWideRows : b->fstrips != 0;
+    p->fused_items = strips ? b->nfs_segments : b->wide_ok || b->flane == 4 ? b->nf4_items : b->nf_items;
     p->fused_lane_nodes = b->flane;
     p->fused_strips = b->fstrips;
+    p->fused_form = !b->wide_ok ? 0 : b->wide == kWideTiles ? 1 : b->wide == kWideRows ? 2 : 3;
     return ADI_OK;
 }
 
@@ -774,7 +778,19 @@ adi_status adi_batch_set_plan(adi_batch_t b, const adi_batch_plan* p)
     if (p->fused_lane_nodes != 0 && p->fused_lane_nodes != 4 && p->fused_lane_nodes != 8)
         return fail(ADI_EINVAL, "fused_lane_nodes must be 0, 4 or 8");
     if (p->fused_strips < 0 || p->fused_strips > 2) return fail(ADI_EINVAL, "fused_strips must be 0, 1 or 2");
-    if (p->fused_step == 2) b->wide = kWideNone;
+    if (p->fused_form < -1 || p->fused_form > 3) return fail(ADI_EINVAL, "fused_form must be -1, 0, 1, 2 or 3");
+    if (p->fused_form != 0 && !b->wide_ok)
+        return fail(ADI_EUNSUPPORTED, "fused_form is for FP32 batches with r <= 0.18 whose rows are of any length");
+    if (p->fused_step == 2) {
+        b->wide = kWideNone;
+        b->exact_user = 1;
+    } else if (p->fused_form) {
+        b->wide = p->fused_form == 1   ? kWideTiles
+                  : p->fused_form == 2 ? kWideRows
+                  : p->fused_form == 3 ? kWideNone
+                                       : batch_wide(b->nodes);
+        if (p->fused_form != 3) b->exact_user = 0;
+    }
     if (p->fused_step > 0) b->fused = p->fused_step == 1 ? 1 : 0;
     if (p->fused_strips) b->fstrips = p->fused_strips == 1 ? 1 : 0;
     if (p->fused_lane_nodes) b->flane = p->fused_lane_nodes;
@@ -847,16 +863,17 @@ adi_status adi_batch_autotune(adi_batch_t b, int trial_steps, double* best_ms)
         b->flane = blane;
         b->fstrips = bstrips;
     } else if (st == ADI_OK) {
+        // the forms that apply, then the exact step's plans among themselves
         int wide = b->wide;
-        if (wide) {
+        double bwide = 1e30;
+        if (b->wide_ok && !b->exact_user) {
             for (int form : {kWideTiles, kWideRows}) {
                 b->wide = form;
                 double ms = 0;
                 if ((st = trial(ms)) != ADI_OK) break;
-                if (ms < best) { best = ms; wide = form; }
+                if (ms < bwide) { bwide = ms; wide = form; }
             }
         }
-        const double bwide = best;
         b->wide = kWideNone;
         for (int tr : {128, 256, 1024}) {
             if (st != ADI_OK) break;
@@ -879,7 +896,8 @@ adi_status adi_batch_autotune(adi_batch_t b, int trial_steps, double* best_ms)
             }
             *knobs[q] = *bests[q];
         }
-        b->wide = best < bwide ? kWideNone : wide;
+        b->wide = st == ADI_OK && best < bwide ? kWideNone : wide;
+        best = std::min(best, bwide);
     }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);

@@ -183,3 +183,101 @@ for kw in (dict(x_rows_per_strip=5), dict(x_threads_per_line=1024), dict(y_fused
         assert st == [0, 0] and same and after_kappa, kw
         if whole and ("y_fused" in kw or "y_chunk_rows" in kw):
             assert "k_ycol_pivots" in built, (kw, built)
+
+
+BATCH = '''
+import paper_2006_10142_amd as adw
+
+def batch(sizes, rmax=0.1):
+    rec.rec_set_rmax(rmax)
+    n = len(sizes)
+    h = ct.c_void_p()
+    _lib.check(lib.adi_batch_create(ct.byref(h), n, (ct.c_int * n)(*[s[0] for s in sizes]),
+                                    (ct.c_int * n)(*[s[1] for s in sizes]), (ct.c_double * n)(*[0.1] * n),
+                                    (ct.c_double * n)(*[0.1] * n), None, (ct.c_double * n)(*[1.0] * n), 0, None))
+    b = adw.Batch.__new__(adw.Batch)
+    b._h, b.count, b.sizes, b._code = h, n, sizes, 0
+    lev = [(ct.c_void_p * n)(*[base + (k << 32) for k in range(n)]) for base in (A, B)]
+    _lib.check(lib.adi_batch_bind(h, *lev))
+    return b
+
+def runs(b):
+    names()
+    b.step(1)
+    got = names()
+    return "exact" if len(got) == 3 else "strips" if "k_fusedr" in got[0] else "tiles"
+
+def times(*ms):
+    rec.rec_times((ct.c_float * len(ms))(*ms), len(ms))
+
+RAGGED = [(33, 70), (257, 64), (243, 65)]
+'''
+
+
+@pytest.mark.parametrize("ms,form", [((1, 5, 9), "tiles"), ((5, 1, 9), "strips"), ((5, 5, 1), "exact")])
+def test_batch_autotune_cache_keeps_the_form(ms, form, tmp_path):
+    """The form the autotuner chose is in the plan and in the cache file, a second tuning
+    times all of them again, and a file made for another coefficient is no error."""
+    cache = str(tmp_path / "plans.json")
+    got = recorder.run(BATCH + f'''
+a = batch(RAGGED)
+times(*{ms})
+a.autotune(2, cache={cache!r})
+b = batch(RAGGED)
+b.autotune(2, cache={cache!r})
+names()
+times(5, 1, 9)                             # strips are the fastest now
+a.autotune(2)
+again = runs(a)
+c = batch(RAGGED, 0.5)                     # no form applies
+c.autotune(2, cache={cache!r})
+out = [runs(b), b.plan()["fused_items"], again, runs(c), c.plan()["fused_form"]]
+''')
+    assert got[0] == form and got[2:] == ["strips", "exact", 0]
+    # tiles of at most 240 columns by 64 rows: 1 x 2 + 2 x 1 + 2 x 2; strips: 1 + 2 + 2
+    assert form == "exact" or got[1] == (8 if form == "tiles" else 5)
+
+
+def test_batch_form_plans():
+    """Forms set by name, the exact step asked for and given up again, plans read and set
+    again, and what is refused."""
+    got = recorder.run(BATCH + '''
+out = []
+b = batch(RAGGED)
+out.append([runs(b), b.plan()["fused_form"]])
+for kw in (dict(fused_form="strips"), dict(fused_form="tiles"), dict(fused_form="exact"), dict(fused_form="auto"),
+           dict(fused_step=False), dict(x_threads_per_line=128), dict(fused_form="auto")):
+    b.set_plan(**kw)
+    p = _lib.AdiBatchPlan()
+    _lib.check(lib.adi_batch_get_plan(b._h, ct.byref(p)))
+    _lib.check(lib.adi_batch_set_plan(b._h, ct.byref(p)))
+    out.append([runs(b), b.plan()["fused_form"]])
+c = batch([(64, 64), (128, 64)])           # the tuned one-pass step
+out.append([runs(c) != "exact", c.plan()["fused_form"]])
+for d in (c, batch(RAGGED, 0.5)):
+    for form in (1, 2, 3, -1, 4, -2):
+        p = _lib.AdiBatchPlan()
+        _lib.check(lib.adi_batch_get_plan(d._h, ct.byref(p)))
+        p.fused_form = form
+        out.append(lib.adi_batch_set_plan(d._h, ct.byref(p)))
+b.set_plan(fused_step=False)
+times(1, 1, 9)
+b.autotune(2)
+out.append(runs(b))                        # the exact step as asked for: only its plans are timed
+''')
+    assert got[:8] == [["tiles", 1], ["strips", 2], ["tiles", 1], ["exact", 3], ["tiles", 1], ["exact", 3],
+                       ["exact", 3], ["tiles", 1]]
+    assert got[8] == [True, 0] and got[9:21] == 2 * [-4, -4, -4, -4, -1, -1] and got[21] == "exact"
+
+
+def test_batch_autotune_tunes_the_exact_step_too():
+    """Where a form is the fastest, the exact step that fused_step 2 takes has the fastest of
+    its own plans, as it had before there were forms."""
+    got = recorder.run(BATCH + '''
+b = batch(RAGGED)
+times(1, 1, 9, 4, 9, 9, 9, 3, 9)          # tiles, strips, 128, 256, 1024 threads, then x grids 0, 256, 512 ...
+b.autotune(2)
+p = b.plan()
+out = [runs(b), p["x_threads_per_line"], p["x_grid"]]
+''')
+    assert got == ["tiles", 256, 512]
