@@ -152,9 +152,10 @@ adi_status adi_wave_destroy(adi_wave_t w);
  * at that level; after exact steps it does not at all. */
 
 /* Forward run of nsteps steps from (u_prev, u_curr) (not modified) with
- * sources and receivers exactly as adi_wave_step (the handle's step: the
- * one-pass step where it is allowed, else the exact two-pass step; never cyclic
- * reduction), keeping the level pair every checkpoint_every steps in
+ * sources and receivers as adi_wave_step (the tuned one-pass step where the handle's
+ * fused_step is 1, else the exact two-pass step, also on handles whose adi_wave_step
+ * takes another form of the one-pass step: the two differ by at most its bound, half
+ * an ulp per step, there; never cyclic reduction), keeping the level pair every checkpoint_every steps in
  * handle-owned device memory (allocated here on first use or growth:
  * 2 * ceil(nsteps / checkpoint_every) + 6 fields).
  * The handle keeps ONE forward record: this call replaces the previous one,
@@ -373,7 +374,8 @@ typedef struct {
                                  takes on grids where it is the faster one unless fused_step
                                  or a plan of the exact step is set */
     size_t workspace_bytes;   /* device bytes owned by the handle */
-    int fused_step;           /* 1: adi_wave_step runs the one-pass step */
+    int fused_step;           /* 1: adi_wave_step runs the tuned one-pass step (0 with
+                                 kernels_per_step 1: another form of it, see there) */
     int fused_allowed;        /* 1: the one-pass step's truncation bound holds (FP32:
                                  r_max <= 0.18 and nx % 4 == 0; FP64: r_max <= 0.13 and nx
                                  even) */

@@ -1281,11 +1281,13 @@ adi_status adi_wave_get_info(adi_wave_t w, adi_wave_info* info)
     info->fused_allowed = w->fused_ok;
     info->r_max = w->rmax;
     info->line_solver = w->cr ? 2 : 1;
-    info->fused_tile_cols = w->f_wt;
-    info->fused_tiles = w->f_tiles;
-    info->fused_lane_nodes = w->f_lane;
-    info->fused_segment_rows = w->f_hs;
-    info->fused_strips_wide = w->f_wide;
+    // the plan of the form that runs, else of the tuned one-pass step
+    const bool wide = w->fwide != kWideNone;
+    info->fused_tile_cols = wide ? w->g_wt : w->f_wt;
+    info->fused_tiles = wide ? w->g_tiles : w->f_tiles;
+    info->fused_lane_nodes = !wide ? w->f_lane : w->dtype == ADI_F64 ? FrCfg<double>::NPL : kF4Seg;
+    info->fused_segment_rows = wide ? w->g_hs : w->f_hs;
+    info->fused_strips_wide = wide ? w->g_wide : w->f_wide;
     return ADI_OK;
 }
 

@@ -281,3 +281,32 @@ p = b.plan()
 out = [runs(b), p["x_threads_per_line"], p["x_grid"]]
 ''')
     assert got == ["tiles", 256, 512]
+
+
+@pytest.mark.parametrize("nx,ny,rmax,f64", [(64, 1600, 0.5, 0), (3000, 2999, 0.8, 0), (65, 1600, 0.17, 0),
+                                            (723, 417, 0.17, 0), (2051, 1953, 0.17, 0), (65, 1600, 0.13, 1),
+                                            (1001, 801, 0.13, 1), (256, 256, 0.1, 0), (2048, 2048, 0.1, 0),
+                                            (4096, 4096, 0.1, 0), (2048, 2048, 0.1, 1)])
+def test_reported_tiles_are_those_launched(nx, ny, rmax, f64):
+    """The tile plan in adi_wave_get_info is the one of the step that runs: its tiles cover
+    the grid, its count is the launch's (rounded up to whole XCD bands)."""
+    got = recorder.run(f'''
+w = wave({nx}, {ny}, {rmax}, {f64})
+i = info(w)
+rec.rec_clear()
+a, b = ct.c_void_p(A), ct.c_void_p(B)
+_lib.check(lib.adi_wave_step(w, ct.byref(a), ct.byref(b), None, None, 1))
+k = rec.rec_log().decode().splitlines()[0].split()
+out = [i, short(k[:1])[0], int(k[1])]
+''')
+    i, kernel, grid = got
+    assert i["kernels_per_step"] == 1 and kernel in ONE_PASS
+    assert grid == (i["fused_tiles"] + 7) // 8 * 8
+    assert (i["fused_segment_rows"] > 0) == (kernel == "k_fusedr")
+    assert i["fused_lane_nodes"] == (2 if f64 else 8 if kernel == "k_fused" else 4)
+    rows = i["fused_segment_rows"] or 64
+    across = i["fused_tiles"] // -(-ny // rows)
+    assert across * -(-ny // rows) == i["fused_tiles"]
+    wide = min(i["fused_strips_wide"], across)
+    cols = wide * i["fused_tile_cols"] + (across - wide) * (i["fused_tile_cols"] - 8)
+    assert nx <= cols < nx + 8 * across + i["fused_tile_cols"]
