@@ -204,22 +204,35 @@ bool launch_ysolve(int M, dim3 grid, const YArgs<T>& a, hipStream_t st)
 }
 
 // whole-column y-lines (ycol.hpp): rows per thread, the fewest of 2 .. 32 whose 64
-// segments cover ny; 0: the chunked y-solve.  Columns of more than 1024 rows (32 a
-// thread, one workgroup a compute unit) stay with it on grids above 2^23 nodes, where
-// both are bound by bytes and its many small workgroups hide the loads better (step of
-// 8192 x 2048: FP32 121 us chunked, 129 whole; FP64 259, 291); at or below, whole
-// columns win (4096 x 2048: FP32 76, 62; FP64 141, 138; 2048 x 1100 FP32 30.4, 22.0), but
-// for narrow FP32 grids near 2048 rows in whole chunks, where both are one chain and the
-// chunks' is the shorter (100 x 2000: 17.1 chunked, 19.4 whole; 400 x 2000 19.4, 20.7;
-// 500 x 2000 20.7, 19.8; 33 x 2000 18.5, 18.2; 100 x 1900 19.0, 18.5).
-int choose_ycol(int nx, int ny, adi_dtype dt)
+// segments cover ny; 0: too long or too large for them
+int ycol_rows(int nx, int ny, adi_dtype dt)
 {
-    const long long n = (long long)nx * ny;
-    if (n * (long long)esize(dt) > kFuOOB || (ny > kYcP * 16 && n > (1LL << 23))) return 0;
-    if (dt == ADI_F32 && ny > 1920 && ny <= 2048 && ny % 16 == 0 && nx >= 64 && nx <= 448) return 0;
+    if ((long long)nx * ny * (long long)esize(dt) > kFuOOB) return 0;
     for (int s = 2; s <= 32; s *= 2)
         if (kYcP * s >= ny) return s;
     return 0;
+}
+
+// ... for the exact step; 0: the chunked y-solve.  Up to 1024 rows always (chunked times
+// below, 1024^2 FP32 18.4 us, whole 14.8).  Columns of 32-row segments:
+//   above 2^23 nodes both are bound by bytes, and the chunks' many small workgroups hide
+//   the loads better (step of 8192 x 2048: FP32 121 us chunked, 129 whole; FP64 259, 291);
+//   at or below, whole columns win (4096 x 2048: FP32 76, 62; FP64 141, 138);
+//   narrow FP32 grids, 9 to 120 workgroups of 4 columns, are bound by one chain either
+//   way: that of whole columns grows by 5.5 us per 1000 rows, the chunks' does not, but for
+//   its last chunk, read row by row where it is not full, which costs 0.25 us a row past
+//   the fourth.  They meet near 1650 rows (100 columns: 1600 rows 16.7 chunked, 16.6 whole;
+//   1700 16.4, 17.1; 1900 (12 in the last chunk) 18.5, 18.2; 2000 16.4, 18.8; 400 columns:
+//   1600 18.4, 17.4; 2000 18.9, 20.3).  Not for rows of whole 512 bytes, whose columns are
+//   read faster (256 x 2000: 17.8, 14.6), nor in FP64 (100 x 2000: 21.6, 21.0).
+int choose_ycol(int nx, int ny, adi_dtype dt)
+{
+    const int s = ycol_rows(nx, ny, dt);
+    if (ny <= kYcP * 16) return s;
+    if ((long long)nx * ny > (1LL << 23)) return 0;
+    const int tail = std::max(0, ny % 16 - 4);
+    if (dt == ADI_F32 && nx > 32 && nx <= 480 && nx % 128 != 0 && ny - 60 * tail > 1650) return 0;
+    return s;
 }
 
 // threads of a block of CB columns: whole wavefronts holding ceil(ny / S) segments
@@ -331,11 +344,13 @@ struct adi_wave_s {
     // FP64: ny * ceil(nx / 2) entry pivots of every 2-node lane (one-pass strips); those of r
     // only where r was measured (rmax >= 0): the time-dependent step does not write them
     void* qin2 = nullptr;
-    void* qy = nullptr;    // qy_n = ceil(ny / ycs) * nx entry pivots of the y-line segments (ycol.hpp)
+    void* qy = nullptr;    // qy_n = ceil(ny / yct) * nx entry pivots of the y-line segments (ycol.hpp)
     size_t qy_n = 0;
-    int ycs = 0;           // rows per thread of the whole-column y-solve; 0: the chunked y-solve
+    int yct = 0;           // rows per thread of the whole-column y-solve where columns fit it: what
+                           // the time-dependent step takes; 0: they do not, or a y plan was set
+    int ycs = 0;           // of the exact step's y-solve: yct, or 0: the chunked y-solve
     XPlan xp0{};           // the exact step's plan as chosen at create: x-sweep,
-    int M0 = 32, ycs0 = 0; //   chunk rows, rows per thread of the whole-column y-solve
+    int M0 = 32, ycs0 = 0, yct0 = 0;   // chunk rows, rows per thread of the two column solves
     int nseg = 0;
     int nxp = 0;           // nx rounded up to the summary-plane column block
     size_t w_cap = 0;      // elements of w (also create-time scratch of 5*K*nx)
@@ -1182,14 +1197,18 @@ adi_status adi_wave_create(adi_wave_t* out, int nx, int ny, double h, double dt,
     const size_t es = esize(dtype);
     const size_t npts = (size_t)nx * ny;
     w->nseg = (nx + kSeg - 1) / kSeg;
-    if (!xp.fuse) w->ycs = choose_ycol(nx, ny, dtype);
-    if (w->ycs) w->qy_n = (size_t)((ny + w->ycs - 1) / w->ycs) * nx;
+    if (!xp.fuse) {
+        w->ycs = choose_ycol(nx, ny, dtype);
+        w->yct = w->ycs ? w->ycs : (long long)nx * ny <= (1LL << 23) ? ycol_rows(nx, ny, dtype) : 0;
+    }
+    if (w->yct) w->qy_n = (size_t)((ny + w->yct - 1) / w->yct) * nx;
     w->xp0 = w->xp;
     w->M0 = M;
     w->ycs0 = w->ycs;
+    w->yct0 = w->yct;
     if (hipMalloc(&w->r, npts * es) != hipSuccess ||
         hipMalloc(&w->qin, (size_t)ny * w->nseg * es) != hipSuccess ||
-        (w->ycs && hipMalloc(&w->qy, w->qy_n * es) != hipSuccess) ||
+        (w->yct && hipMalloc(&w->qy, w->qy_n * es) != hipSuccess) ||
         (dtype == ADI_F64 && hipMalloc(&w->qin2, (size_t)ny * ((nx + 1) / 2) * es) != hipSuccess)) {
         (void)hipGetLastError();
         free_ws(w);
@@ -1365,6 +1384,7 @@ adi_status adi_wave_set_tuning(adi_wave_t w, const adi_tuning* t)
     const int ycs = y_plan ? 0 : reset ? w->ycs0 : w->ycs;
     const bool y_changed = M != w->M || ycs != w->ycs;
     w->ycs = ycs;
+    w->yct = y_plan ? 0 : reset ? w->yct0 : w->yct;
     if (M != w->M) {
         if (hipStreamSynchronize(w->stream) != hipSuccess)
             return fail(ADI_EHIP, "stream synchronise failed");

@@ -182,8 +182,10 @@ adi_status step_tdc_rows(adi_wave_s* w, void** u_prev, void** u_curr, const void
         ya.rec_idx = rec->idx;
         ya.rec_out = static_cast<T*>(rec->traces);
     }
-    if (!launch_ycol<T, true>(w->ycs, ya, w->stream)) return fail(ADI_EUNSUPPORTED, "no column kernel for this plan");
+    if (!launch_ycol<T, true>(w->yct, ya, w->stream)) return fail(ADI_EUNSUPPORTED, "no column kernel for this plan");
     ADI_LAUNCHED("y_solve_update");
+    if (kappa_next && !w->ycs)           // the exact step's y-lines are chunked: their planes of the new r
+        if (adi_status e = static_planes<T>(w)) return e;
     std::swap(*u_prev, *u_curr);
     return ADI_OK;
 }
@@ -194,7 +196,7 @@ adi_status do_step_tdc(adi_wave_s* w, void** u_prev, void** u_curr, const void* 
 {
     // (line groups of 1024 threads have no registers for the two stencils; columns too
     // long for one workgroup need the chunked y-solve's planes of the new coefficient)
-    if (w->xp.tr <= 256 && w->ycs) return step_tdc_rows<T>(w, u_prev, u_curr, kappa_prev, kappa_next, f, rec);
+    if (w->xp.tr <= 256 && w->yct) return step_tdc_rows<T>(w, u_prev, u_curr, kappa_prev, kappa_next, f, rec);
     const long long n = (long long)w->nx * w->ny;
     const size_t bytes = (size_t)n * sizeof(T);
     if (!w->r_prev || !w->rho_buf) {

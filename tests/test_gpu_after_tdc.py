@@ -70,3 +70,31 @@ def test_pivots_are_those_of_set_kappa(adw, nx, ny):
         out.append(b.clone())
         w.close()
     assert torch.equal(*out)
+
+
+@pytest.mark.parametrize("nx,ny", [(100, 1700), (100, 2000), (33, 1999), (33, 2000), (480, 1652), (128, 2000), (40, 2048)])
+def test_narrow_columns(adw, oracle_lib, nx, ny):
+    """Exact FP32 steps on both sides of the rule between whole columns and the chunked
+    y-solve, before and after a time-dependent step (which takes whole columns), r up to 2;
+    the step's own tolerance (see above)."""
+    print(f"narrow columns {nx}x{ny}", flush=True)
+    rng = np.random.default_rng(nx + ny)
+    h = 1.0 / (max(nx, ny) + 1)
+    dt = 2.0 * h                                              # r = 2 kappa
+    ka, kb = (rng.uniform(1 / 9, 1.0, (ny, nx)).astype(np.float32) for _ in range(2))
+    up, uc = (rng.standard_normal((ny, nx)).astype(np.float32) for _ in range(2))
+
+    def cu(a):
+        return torch.from_numpy(a).cuda()
+    wave = adw.Wave(nx, ny, h, dt, kappa=cu(ka), dtype=torch.float32)
+    _, b = wave.step(cu(up), cu(uc), 1)
+    _, ref, _ = oracle_lib.run(ka.astype(np.float64), up.astype(np.float64), uc.astype(np.float64), h, dt, 1)
+    assert rel_l2(b.cpu().numpy(), ref) <= 1e-5
+    a, b = wave.step_tdc(cu(up), cu(uc), kappa_prev=cu(ka), kappa_next=cu(kb))
+    u1 = oracle_lib.step_tdc(ka.astype(np.float64), kb.astype(np.float64), up.astype(np.float64), uc.astype(np.float64), h, dt)
+    assert rel_l2(b.cpu().numpy(), u1) <= 1e-5
+    got = b.cpu().numpy()
+    _, b = wave.step(a, b, 1)
+    _, ref, _ = oracle_lib.run(kb.astype(np.float64), uc.astype(np.float64), got.astype(np.float64), h, dt, 1)
+    assert rel_l2(b.cpu().numpy(), ref) <= 1e-5
+    wave.close()
