@@ -481,8 +481,13 @@ void launch_tri_cols1(const TriArgs<T>& t, hipStream_t st)
 }
 
 // One launch where it is faster than the three (us, three -> one):
-//   n <= 1024  always (512 x 512 FP32 29 -> 10.6, 1024 x 8192 77 -> 54), but for very short
-//              systems in great number (1 x 100000: 16.8 -> 19.1), where most threads idle;
+//   n <= 32 (FP64 16)  the systems that one chunk of the three launches holds, eliminated
+//              from the top by one thread there and here: systems that are not dominant need
+//              that (cut into segments they can divide by zero).  FP32 16 rows x 1000
+//              14.9 -> 10.0, x 1000000 136 -> 69; 32 x 1000 19 -> 14.8, x 100000 35 -> 30,
+//              but x 400000 104 -> 105 and 17 x 400000 59 -> 66, hence the limit above 16 rows;
+//   n <= 1024  always (512 x 512 FP32 29 -> 10.6, 1024 x 8192 77 -> 54; FP64 17 x 1000000
+//              291 -> 143 in eight segments of four rows, 380 where 32 are provided for);
 //   n <= 2048  four (FP64) to eight adjacent systems share a workgroup, each 128-byte line
 //              being read by several: up to 5000 systems (2048 x 2000 FP32 47 -> 23,
 //              2048 x 5500 103 -> 90, 1500 x 8192 98 -> 108; FP64 1200 x 5500 105 -> 107);
@@ -496,10 +501,16 @@ bool launch_tri_cols(const TriArgs<T>& t, hipStream_t st)
 {
     constexpr bool F = sizeof(T) == 4;
     const int n = t.n, batch = t.batch;
-    const int most = n > 2048 ? (F ? 1024 : 512) : n > 1024 ? 5000 : n < 16 ? 32768 : batch;
+    constexpr int M = F ? kTpM32 : kTpM64;
+    const int most = n > 2048 ? (F ? 1024 : 512) : n > 1024 ? 5000 : F && n > 16 && n <= M ? 100000 : batch;
     if (t.sys_stride != 1 || n > 4096 || batch > most) return false;
     const bool few = batch <= 255 * (F ? 16 : 8);
-    if (n <= 128) launch_tri_cols1<T, 4, 32, 16>(t, st);
+    if (n <= 8) launch_tri_cols1<T, 8, 1, 64>(t, st);
+    else if (n <= 16) launch_tri_cols1<T, 16, 1, 64>(t, st);
+    else if (F && n <= 24) launch_tri_cols1<T, F ? 24 : 16, 1, 64>(t, st);
+    else if (F && n <= M) launch_tri_cols1<T, F ? M : 16, 1, 64>(t, st);
+    else if (!F && n <= 32) launch_tri_cols1<T, 4, F ? 32 : 8, F ? 16 : 32>(t, st);
+    else if (n <= 128) launch_tri_cols1<T, 4, 32, 16>(t, st);
     else if (n <= 256) launch_tri_cols1<T, 8, 32, 16>(t, st);
     else if (n <= 512) launch_tri_cols1<T, 8, 64, F ? 16 : 8>(t, st);
     else if (n <= 1024 && few) launch_tri_cols1<T, 8, 128, F ? 8 : 4>(t, st);
