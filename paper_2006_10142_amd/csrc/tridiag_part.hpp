@@ -388,12 +388,14 @@ __global__ void __launch_bounds__(256) k_tri_part_iface2(TriArgs<T> A, int P, in
 
 // Blocks run from the last to the first: the reduction's last reads are still in the
 // last-level cache (8192 interleaved FP32 systems of 8192: 474 -> 467 us for the three
-// launches; with both reading past the caches 455).
+// launches; with both reading past the caches 455).  Each on the XCD that reduced it, whose
+// L2 holds a small call whole (300 systems of 5008: 29.1 us, on another XCD 31.7).
 template <typename T, int M, bool NT>
 __global__ void __launch_bounds__(256) k_tri_part_expand(TriArgs<T> A, int P, const T* __restrict__ red)
 {
     const long long nb = A.batch;
-    const long long gid = (long long)(gridDim.x - 1 - blockIdx.x) * 256 + threadIdx.x;
+    const unsigned blk = ((gridDim.x >> 3) - 1 - (blockIdx.x >> 3)) * 8 + (blockIdx.x & 7);
+    const long long gid = (long long)blk * 256 + threadIdx.x;
     if (gid >= (long long)P * nb) return;
     const int p = (int)(gid / nb);
     const long long s = gid - (long long)p * nb;
@@ -552,8 +554,9 @@ void launch_tri_part(const TriArgs<T>& t, T* red, hipStream_t st)
         const unsigned g2 = (unsigned)((t.batch + kTpIfaceThreads - 1) / kTpIfaceThreads);
         hipLaunchKernelGGL((k_tri_part_iface<T>), dim3(g2), dim3(kTpIfaceThreads), 0, st, t, P, M, red);
     }
-    if (nt) hipLaunchKernelGGL((k_tri_part_expand<T, M, true>), dim3(g1), dim3(256), 0, st, t, P, (const T*)red);
-    else hipLaunchKernelGGL((k_tri_part_expand<T, M, false>), dim3(g1), dim3(256), 0, st, t, P, (const T*)red);
+    const dim3 g3((g1 + 7) / 8 * 8);
+    if (nt) hipLaunchKernelGGL((k_tri_part_expand<T, M, true>), g3, dim3(256), 0, st, t, P, (const T*)red);
+    else hipLaunchKernelGGL((k_tri_part_expand<T, M, false>), g3, dim3(256), 0, st, t, P, (const T*)red);
 }
 
 }  // namespace adw
