@@ -398,13 +398,15 @@ struct TriArgs {
 // and written once.  NT: the reads bypass the caches, for calls whose arrays exceed them
 // (8192 FP32 systems of 8192: 245 us, 5.5 TB/s; 258 without; 222 on the same arrays
 // again).  By buffer accesses of any alignment: 8192 systems of 8191, value by value
-// behind bounds tests, 580 us; so, 245.
+// behind bounds tests, 580 us; so, 245.  (The system of a wavefront is made uniform by name:
+// a resource that the compiler takes for one of each lane costs a loop at every access,
+// 30000 systems of 33 15.6 us, 14.5 without.)
 template <typename T, int S, int TR, bool NT>
 __global__ void __launch_bounds__(TR >= 256 ? TR : 256) k_tridiag_wg(TriArgs<T> A)
 {
     constexpr int G = (TR >= 256 ? TR : 256) / TR;
     __shared__ T lds_all[G * partition_lds_slots<TR>()];
-    const int g = threadIdx.x / TR;
+    const int g = __builtin_amdgcn_readfirstlane(threadIdx.x / TR);   // whole wavefronts a system
     const int t = threadIdx.x - g * TR;
     const long long sys = (long long)blockIdx.x * G + g;
     const bool live = sys < A.batch;
