@@ -389,12 +389,13 @@ __global__ void __launch_bounds__(256) k_tri_part_iface2(TriArgs<T> A, int P, in
 // Blocks run from the last to the first: the reduction's last reads are still in the
 // last-level cache (8192 interleaved FP32 systems of 8192: 474 -> 467 us for the three
 // launches; with both reading past the caches 455).  Each on the XCD that reduced it, whose
-// L2 holds a small call whole (300 systems of 5008: 29.1 us, on another XCD 31.7).
+// L2 holds a small call whole (300 systems of 5008: 29.1 us, on another XCD 31.7); in
+// plain reverse where the reads go past the caches (8192 x 8192: 451 us, 453 by XCD).
 template <typename T, int M, bool NT>
 __global__ void __launch_bounds__(256) k_tri_part_expand(TriArgs<T> A, int P, const T* __restrict__ red)
 {
     const long long nb = A.batch;
-    const unsigned blk = ((gridDim.x >> 3) - 1 - (blockIdx.x >> 3)) * 8 + (blockIdx.x & 7);
+    const unsigned blk = NT ? gridDim.x - 1 - blockIdx.x : ((gridDim.x >> 3) - 1 - (blockIdx.x >> 3)) * 8 + (blockIdx.x & 7);
     const long long gid = (long long)blk * 256 + threadIdx.x;
     if (gid >= (long long)P * nb) return;
     const int p = (int)(gid / nb);
