@@ -506,7 +506,8 @@ bool launch_tri_cols(const TriArgs<T>& t, hipStream_t st)
     const int n = t.n, batch = t.batch;
     constexpr int M = F ? kTpM32 : kTpM64;
     const int most = n > 2048 ? (F ? 1024 : 512) : n > 1024 ? 5000 : F && n > 16 && n <= M ? 100000 : batch;
-    if (t.sys_stride != 1 || n > 4096 || batch > most) return false;
+    // (2^24 systems of 128 threads: 2^31 threads; a launch takes less than 2^32)
+    if (t.sys_stride != 1 || n > 4096 || batch > most || batch > (1 << 24)) return false;
     const bool few = batch <= 255 * (F ? 16 : 8);
     if (n <= 8) launch_tri_cols1<T, 8, 1, 64>(t, st);
     else if (n <= 16) launch_tri_cols1<T, 16, 1, 64>(t, st);

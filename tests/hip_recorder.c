@@ -5,9 +5,11 @@
  * the reduction of the largest r, whose result rec_set_rmax gives.  Copies and fills of
  * at most 64 bytes and uploads are done, the others (between levels, which may be any
  * addresses) only logged. */
+#define _GNU_SOURCE
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <sys/mman.h>
 
 typedef struct { unsigned x, y, z; } dim3_t;
 
@@ -95,8 +97,20 @@ int hipLaunchKernel(const void* fn, dim3_t grid, dim3_t block, void** args, size
 }
 
 /* ------------------------------------------------------------------- memory ---- */
-int hipMalloc(void** p, size_t n) { *p = aligned_alloc(256, (n + 255) / 256 * 256); return *p ? kOk : kFailed; }
-int hipFree(void* p) { free(p); return kOk; }
+/* (address space only, no memory until it is touched: nothing here reads whole fields) */
+int hipMalloc(void** p, size_t n)
+{
+    size_t* q = mmap(NULL, n + 4096, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+    if (q == MAP_FAILED) return kFailed;
+    q[0] = n + 4096;
+    *p = (char*)q + 4096;
+    return kOk;
+}
+int hipFree(void* p)
+{
+    if (p) munmap((char*)p - 4096, *(size_t*)((char*)p - 4096));
+    return kOk;
+}
 int hipGetSymbolAddress(void** p, const void* sym) { (void)sym; return hipMalloc(p, (size_t)1 << 26); }
 int hipMemsetAsync(void* p, int v, size_t n, void* s)
 {

@@ -336,3 +336,22 @@ for nx, ny, f64, want in ((100, 1650, 0, 2), (100, 1651, 0, 4), (100, 1700, 0, 4
         if ny > 2048:
             continue
         assert tdc == ["k_tdc_x", "k_ycol"] + (["k_ystatic1", "k_ystatic2"] if want == 4 else []), (nx, ny, tdc)
+
+
+def test_interleaved_systems_in_very_great_number():
+    """Up to 2^31 - 1 interleaved systems: one launch as far as a launch's threads and the
+    kernel's 32-bit system numbers reach, the three of the partition solve beyond."""
+    got = recorder.run('''
+out = []
+for n, batch in ((1, (1 << 24) - 3), (1, (1 << 24) + 1), (1, (1 << 31) - 1), (16, 1 << 30), (33, 140000000), (200, 1 << 24),
+                 (1000, (1 << 24) + 1)):
+    for f64 in (0, 1):
+        rec.rec_clear()
+        st = lib.tridiag_solve_batched(f64, n, batch, A, B, C, D, 1, batch, None)
+        log = [l.split() for l in rec.rec_log().decode().splitlines()]
+        out.append([n, batch, f64, st, short([l[0] for l in log]), [int(l[1]) * int(l[2]) for l in log]])
+''')
+    for n, batch, f64, st, kernels, threads in got:
+        assert st == 0 and all(0 < t < 1 << 32 for t in threads), (n, batch, threads)
+        assert (kernels == ["k_tri_cols"]) == (batch <= 1 << 24), (n, batch, kernels)
+        assert threads[0] >= batch
