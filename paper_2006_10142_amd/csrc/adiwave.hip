@@ -289,14 +289,23 @@ void launch_tri1(long long batch, const TriArgs<T>& a, hipStream_t st)
 {
     constexpr int NT = TR >= 256 ? TR : 256;
     constexpr int G = NT / TR;
-    // (a lane's segment must be read whole before its lines leave the first-level
-    // cache: 64-byte FP64 segments bypassing, 5000 systems of 4000, 206 us, else 161)
-    constexpr bool kShort = S * sizeof(T) <= 32;
+    // Plain reads of FP32 rows on 16-byte boundaries where most of 1024 lanes hold whole
+    // vectors and the call is far larger than the last-level cache (256 MB); else buffer
+    // reads.  us, buffer | plain: 8192 systems of 8192 256 | 242, of 7600 239 | 231, of 7000
+    // 219 | 213, 5000 of 8192 157 | 151; 4000 of 8000 123 | 125, 1000 of 8000 35 | 38, 8192 of
+    // 6000 186 | 185, of 5000 153 | 159; FP64 4000 of 8000 302 | 370.  (Buffer reads past the
+    // caches, the form of these calls before, took 245 at 8192 of 8192, but 248 at 7600: a
+    // line of 128 bytes that two rows share was read twice.)
+    constexpr bool kPlain = sizeof(T) == 4 && TR == 1024 && S == 8;
     const dim3 grid((unsigned)((batch + G - 1) / G));
-    if (kShort && tri_streams<T>(a.n, batch))
-        hipLaunchKernelGGL((k_tridiag_wg<T, S, TR, kShort>), grid, dim3(NT), 0, st, a);
-    else
-        hipLaunchKernelGGL((k_tridiag_wg<T, S, TR, false>), grid, dim3(NT), 0, st, a);
+    if constexpr (kPlain) {
+        const bool rows16 = a.sys_stride % 4 == 0 && aligned16(a.a) && aligned16(a.b) && aligned16(a.c) && aligned16(a.d);
+        if (rows16 && a.n > 6144 && 16.0 * a.n * (double)batch > 5.5e8) {
+            hipLaunchKernelGGL((k_tridiag_wg<T, S, TR, true>), grid, dim3(NT), 0, st, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_tridiag_wg<T, S, TR, false>), grid, dim3(NT), 0, st, a);
 }
 
 template <typename T, int TR>

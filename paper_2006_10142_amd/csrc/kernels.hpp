@@ -36,18 +36,10 @@ template <> struct Vec16<double> {
     __device__ static double2 pack(const double* o) { return make_double2(o[0], o[1]); }
 };
 
-// The batched line solves read past the caches where their four arrays are far larger
-// than the last-level cache (256 MB); below, what one call or kernel leaves there serves
-// the next (4000 FP32 contiguous systems of 4000, 256 MB: 49 us, 87 bypassing; 4000 of
-// 5000, 320 MB: 75, 81; 4096 of 8192, 537 MB: 128, 113;
-// on other arrays each time 3500 of 8192: 111, 107).
-template <typename T>
-inline bool tri_streams(int n, long long batch) { return 4.0 * sizeof(T) * n * (double)batch > 4.5e8; }
-
 // S consecutive values at byte offset voff of a line, through a buffer resource of the
 // line's length, which needs no 16-byte alignment and drops what lies past the line's
-// end value by value (see bload8).  AUX: the buffer cache policy bits.
-template <typename T, int S, int AUX>
+// end value by value (see bload8).
+template <typename T, int S>
 __device__ __forceinline__ void load_seg(rsrc_t rs, int voff, T (&v)[S])
 {
     using V = Vec16<T>;
@@ -57,10 +49,26 @@ __device__ __forceinline__ void load_seg(rsrc_t rs, int voff, T (&v)[S])
     } else {
 #pragma unroll
         for (int k = 0; k < S / V::N; ++k) {
-            const auto x = __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 16 * k, 0, AUX);
+            const auto x = __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 16 * k, 0, 0);
             V::unpack(__builtin_bit_cast(typename V::type, x), &v[k * V::N]);
         }
     }
+}
+
+// the L <= S values at p by plain loads: whole vectors where `vec` says that p is 16-byte
+// aligned, else value by value
+template <typename T, int S>
+__device__ __forceinline__ void load_plain(const T* __restrict__ p, int L, bool vec, T (&v)[S])
+{
+    using V = Vec16<T>;
+    if (vec && L == S) {
+        const typename V::type* q = reinterpret_cast<const typename V::type*>(p);
+#pragma unroll
+        for (int k = 0; k < S / V::N; ++k) V::unpack(q[k], &v[k * V::N]);
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < S; ++k) v[k] = (k < L) ? p[k] : T(0);
 }
 
 template <typename T, int S>
@@ -395,18 +403,17 @@ struct TriArgs {
 };
 
 // One workgroup (TR threads) per contiguous system, nodes in registers: everything read
-// and written once.  NT: the reads bypass the caches, for calls whose arrays exceed them
-// (8192 FP32 systems of 8192: 245 us, 5.5 TB/s; 258 without; 222 on the same arrays
-// again).  By buffer accesses of any alignment: 8192 systems of 8191, value by value
-// behind bounds tests, 580 us; so, 245.  (The system of a wavefront is made uniform by name:
-// a resource that the compiler takes for one of each lane costs a loop at every access,
-// 30000 systems of 33 15.6 us, 14.5 without.)
-template <typename T, int S, int TR, bool NT>
+// and written once, by buffer accesses of any alignment (8192 systems of 8191, value by
+// value behind bounds tests, 580 us; so, 245).  (The system of a wavefront is made uniform
+// by name: a resource that the compiler takes for one of each lane costs a loop at every
+// access, 30000 systems of 33 15.6 us, 14.5 without.)  PLAIN: the reads as plain loads (see
+// launch_tri1).
+template <typename T, int S, int TR, bool PLAIN>
 __global__ void __launch_bounds__(TR >= 256 ? TR : 256) k_tridiag_wg(TriArgs<T> A)
 {
     constexpr int G = (TR >= 256 ? TR : 256) / TR;
     __shared__ T lds_all[G * partition_lds_slots<TR>()];
-    const int g = __builtin_amdgcn_readfirstlane(threadIdx.x / TR);   // whole wavefronts a system
+    const int g = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / TR);   // whole wavefronts a system
     const int t = threadIdx.x - g * TR;
     const long long sys = (long long)blockIdx.x * G + g;
     const bool live = sys < A.batch;
@@ -416,10 +423,15 @@ __global__ void __launch_bounds__(TR >= 256 ? TR : 256) k_tridiag_wg(TriArgs<T> 
     const long long off = (live ? sys : 0) * A.sys_stride;
     const int bytes = live ? A.n * (int)sizeof(T) : 0, voff = lo * (int)sizeof(T);
     T a[S], b[S], c[S], d[S];
-    load_seg<T, S, NT ? 2 : 0>(buf(A.a + off, bytes), voff, a);
-    load_seg<T, S, NT ? 2 : 0>(buf(A.b + off, bytes), voff, b);
-    load_seg<T, S, NT ? 2 : 0>(buf(A.c + off, bytes), voff, c);
-    load_seg<T, S, NT ? 2 : 0>(buf(A.d + off, bytes), voff, d);
+    const bool vec = A.sys_stride * sizeof(T) % 16 == 0;
+    auto load = [&](const T* p, T (&v)[S]) {
+        if constexpr (PLAIN) load_plain<T, S>(p + off + lo, L, vec, v);
+        else load_seg<T, S>(buf(p + off, bytes), voff, v);
+    };
+    load(A.a, a);
+    load(A.b, b);
+    load(A.c, c);
+    load(A.d, d);
 #pragma unroll
     for (int k = 0; k < S; ++k) if (k >= L) b[k] = T(1);
     partition_solve<T, S, TR>(d, CoefABC<T, S>{a, b, c}, L, t, nact, lds_all + g * partition_lds_slots<TR>(), 1);

@@ -38,7 +38,7 @@ namespace adw {
 constexpr int kTpM32 = 32;   // chunk rows, FP32 (4 (M-1) register values per thread)
 constexpr int kTpM64 = 16;   // chunk rows, FP64
 
-// NT: reads past the caches (tri_streams)
+// NT: reads past the caches (see launch_tri_part)
 template <bool NT, typename T, int M>
 __device__ __forceinline__ int tp_load(const TriArgs<T>& A, long long s, int p, T (&ca)[M - 1], T (&cb)[M - 1],
                                        T (&cc)[M - 1], T (&cd)[M - 1], long long& base)
@@ -540,7 +540,13 @@ void launch_tri_part(const TriArgs<T>& t, T* red, hipStream_t st)
     const int P = (t.n + M - 1) / M;
     const long long work = (long long)P * t.batch;
     const unsigned g1 = (unsigned)((work + 255) / 256);
-    const bool nt = tri_streams<T>(t.n, t.batch);
+    // Reads past the caches where the four arrays are far larger than the last-level cache
+    // (256 MB) and every row of an interleaved call is whole 128-byte lines: a line that two
+    // wavefronts share is read twice then (us, past | not: 8192 x 8192 448 | 459, x 8000 458 |
+    // 466, but x 7501 538 | 461, x 5000 347 | 312; 6000 x 4096 (393 MB) 188 | 189).
+    auto lines = [](const void* p) { return (reinterpret_cast<size_t>(p) & 127) == 0; };
+    const bool nt = t.sys_stride == 1 && t.elem_stride * (long long)sizeof(T) % 128 == 0 && lines(t.a) && lines(t.b) &&
+                    lines(t.c) && lines(t.d) && 4.0 * sizeof(T) * t.n * (double)t.batch > 4.5e8;
     if (nt) hipLaunchKernelGGL((k_tri_part_reduce<T, M, true>), dim3(g1), dim3(256), 0, st, t, P, red);
     else hipLaunchKernelGGL((k_tri_part_reduce<T, M, false>), dim3(g1), dim3(256), 0, st, t, P, red);
     // threads per system for the parallel interface solve: the least power of two

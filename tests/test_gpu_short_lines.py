@@ -70,3 +70,26 @@ def test_dominant_systems(adw, oracle_lib, n, dtype, batch, pad):
     got = D.cpu().numpy()
     assert np.isfinite(got[:, :batch]).all() and np.array_equal(got[:, batch:], d[:, batch:])
     assert rel_l2(got[:, pick], ref) <= (1e-13 if dtype == "f64" else 1e-5)
+
+
+@pytest.mark.parametrize("n,pad,shift", [(8192, 0, 0), (6148, 0, 0), (7001, 3, 0), (7260, 0, 1)])
+def test_large_contiguous_calls(adw, n, pad, shift):
+    """Calls past 550 MB with rows on 16-byte boundaries (whole and partial vectors at their
+    end) and off them: the residual of every system, 1e-6 as for the other large calls."""
+    print(f"large contiguous lines n={n} pad={pad} shift={shift}", flush=True)
+    batch, pitch = int(5.6e8 / 16 / n) + 1, n + pad
+    g = torch.Generator(device="cuda").manual_seed(n)
+    size = batch * pitch + 4
+    a, c, d = (torch.rand(size, device="cuda", generator=g)[shift:] - 0.5 for _ in range(3))
+    b = a.abs() + c.abs() + 0.5
+    x = d.clone()
+    if shift:                                          # (an expression's result starts its own storage)
+        a, b, c, x = (torch.cat([t.new_zeros(shift), t])[shift:] for t in (a, b, c, x))
+    adw.tridiag_solve_batched(a, b, c, x, n, batch, pitch, 1)
+    v = lambda t: t[:batch * pitch].view(batch, pitch)[:, :n]
+    res = v(b) * v(x) - v(d)
+    res[:, 1:] += v(a)[:, 1:] * v(x)[:, :-1]
+    res[:, :-1] += v(c)[:, :-1] * v(x)[:, 1:]
+    assert (res.norm() / v(d).norm()).item() <= 1e-6
+    if pad:
+        assert torch.equal(x[:batch * pitch].view(batch, pitch)[:, n:], d[:batch * pitch].view(batch, pitch)[:, n:])
