@@ -218,12 +218,12 @@ int ycol_rows(int nx, int ny, adi_dtype dt)
 //   above 2^23 nodes both are bound by bytes, and the chunks' many small workgroups hide
 //   the loads better (step of 8192 x 2048: FP32 121 us chunked, 129 whole; FP64 259, 291);
 //   at or below, whole columns win (4096 x 2048: FP32 76, 62; FP64 141, 138);
-//   narrow FP32 grids, 9 to 120 workgroups of 4 columns, are bound by one chain either
+//   narrow FP32 grids, 7 to 120 workgroups of 4 columns, are bound by one chain either
 //   way: that of whole columns grows by 5.5 us per 1000 rows, the chunks' does not, but for
 //   its last chunk, read row by row where it is not full, which costs 0.25 us a row past
 //   the fourth.  They meet near 1650 rows (100 columns: 1600 rows 16.7 chunked, 16.6 whole;
 //   1700 16.4, 17.1; 1900 (12 in the last chunk) 18.5, 18.2; 2000 16.4, 18.8; 400 columns:
-//   1600 18.4, 17.4; 2000 18.9, 20.3).  Not for rows of whole 512 bytes, whose columns are
+//   1600 18.4, 17.4; 2000 18.9, 20.3; 32 columns: 2040 17.1, 18.5; 16: 16.4, 13.9).  Not for rows of whole 512 bytes, whose columns are
 //   read faster (256 x 2000: 17.8, 14.6), nor in FP64 (100 x 2000: 21.6, 21.0).
 int choose_ycol(int nx, int ny, adi_dtype dt)
 {
@@ -231,7 +231,7 @@ int choose_ycol(int nx, int ny, adi_dtype dt)
     if (ny <= kYcP * 16) return s;
     if ((long long)nx * ny > (1LL << 23)) return 0;
     const int tail = std::max(0, ny % 16 - 4);
-    if (dt == ADI_F32 && nx > 32 && nx <= 480 && nx % 128 != 0 && ny - 60 * tail > 1650) return 0;
+    if (dt == ADI_F32 && nx > 24 && nx <= 480 && nx % 128 != 0 && ny - 60 * tail > 1650) return 0;
     return s;
 }
 
