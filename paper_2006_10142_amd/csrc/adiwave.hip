@@ -270,18 +270,27 @@ bool launch_ycol(int S, const YColArgs<T>& a, hipStream_t st)
     return launch_ycol_s<T, 4, DYN>(S, a, st);
 }
 
+template <typename T, int CB>
+bool launch_ycol_pivots_s(int S, const T* r, T* qy, int nx, int ny, hipStream_t st)
+{
+    const dim3 grid((nx + CB - 1) / CB), blk(ycol_threads(ny, S, CB));
+    switch (S) {
+        case 2: hipLaunchKernelGGL((k_ycol_pivots<T, 2, CB>), grid, blk, 0, st, r, qy, nx, ny); return true;
+        case 4: hipLaunchKernelGGL((k_ycol_pivots<T, 4, CB>), grid, blk, 0, st, r, qy, nx, ny); return true;
+        case 8: hipLaunchKernelGGL((k_ycol_pivots<T, 8, CB>), grid, blk, 0, st, r, qy, nx, ny); return true;
+        case 16: hipLaunchKernelGGL((k_ycol_pivots<T, 16, CB>), grid, blk, 0, st, r, qy, nx, ny); return true;
+        case 32: hipLaunchKernelGGL((k_ycol_pivots<T, 32, CB>), grid, blk, 0, st, r, qy, nx, ny); return true;
+    }
+    return false;
+}
+
+// 16 columns a workgroup, on narrow grids 4: the sweep is FP64 arithmetic, and four
+// wavefronts of a SIMD take turns at it with 16 (FP32 9 x 1960 13.8 us, 8.0 with 4; 2048 x
+// 2000 18.1, 28)
 template <typename T>
 bool launch_ycol_pivots(int S, const T* r, T* qy, int nx, int ny, hipStream_t st)
 {
-    const dim3 grid((nx + kYpCB - 1) / kYpCB), blk(ycol_threads(ny, S, kYpCB));
-    switch (S) {
-        case 2: hipLaunchKernelGGL((k_ycol_pivots<T, 2>), grid, blk, 0, st, r, qy, nx, ny); return true;
-        case 4: hipLaunchKernelGGL((k_ycol_pivots<T, 4>), grid, blk, 0, st, r, qy, nx, ny); return true;
-        case 8: hipLaunchKernelGGL((k_ycol_pivots<T, 8>), grid, blk, 0, st, r, qy, nx, ny); return true;
-        case 16: hipLaunchKernelGGL((k_ycol_pivots<T, 16>), grid, blk, 0, st, r, qy, nx, ny); return true;
-        case 32: hipLaunchKernelGGL((k_ycol_pivots<T, 32>), grid, blk, 0, st, r, qy, nx, ny); return true;
-    }
-    return false;
+    return nx > 256 ? launch_ycol_pivots_s<T, 16>(S, r, qy, nx, ny, st) : launch_ycol_pivots_s<T, 4>(S, r, qy, nx, ny, st);
 }
 
 template <typename T, int S, int TR>
@@ -353,7 +362,8 @@ struct adi_wave_s {
     // FP64: ny * ceil(nx / 2) entry pivots of every 2-node lane (one-pass strips); those of r
     // only where r was measured (rmax >= 0): the time-dependent step does not write them
     void* qin2 = nullptr;
-    void* qy = nullptr;    // qy_n = ceil(ny / yct) * nx entry pivots of the y-line segments (ycol.hpp)
+    void* qy = nullptr;    // qy_n = ceil(ny / yct) * nx entry pivots of the y-line segments (ycol.hpp);
+                           // part of qin's allocation
     size_t qy_n = 0;
     int yct = 0;           // rows per thread of the whole-column y-solve where columns fit it: what
                            // the time-dependent step takes; 0: they do not, or a y plan was set
@@ -414,7 +424,6 @@ void free_ws(adi_wave_s* w)
     if (w->X) (void)hipFree(w->X);
     if (w->qin) (void)hipFree(w->qin);
     if (w->qin2) (void)hipFree(w->qin2);
-    if (w->qy) (void)hipFree(w->qy);
     if (w->cr_abc) (void)hipFree(w->cr_abc);
     if (w->r_prev) (void)hipFree(w->r_prev);
     if (w->rho_buf) (void)hipFree(w->rho_buf);
@@ -1215,15 +1224,15 @@ adi_status adi_wave_create(adi_wave_t* out, int nx, int ny, double h, double dt,
     w->M0 = M;
     w->ycs0 = w->ycs;
     w->yct0 = w->yct;
-    if (hipMalloc(&w->r, npts * es) != hipSuccess ||
-        hipMalloc(&w->qin, (size_t)ny * w->nseg * es) != hipSuccess ||
-        (w->yct && hipMalloc(&w->qy, w->qy_n * es) != hipSuccess) ||
+    const size_t nq = ((size_t)ny * w->nseg + 63) / 64 * 64;        // the column pivots behind the rows'
+    if (hipMalloc(&w->r, npts * es) != hipSuccess || hipMalloc(&w->qin, (nq + w->qy_n) * es) != hipSuccess ||
         (dtype == ADI_F64 && hipMalloc(&w->qin2, (size_t)ny * ((nx + 1) / 2) * es) != hipSuccess)) {
         (void)hipGetLastError();
         free_ws(w);
         delete w;
         return fail(ADI_ENOMEM, "hipMalloc of the coefficient/x-sweep fields failed");
     }
+    if (w->yct) w->qy = static_cast<char*>(w->qin) + nq * es;
     adi_status s = alloc_chunks(w);
     if (s == ADI_OK)
         s = (dtype == ADI_F32) ? set_coef<float>(w, speed, speed_scalar, 1)

@@ -21,7 +21,6 @@
 namespace adw {
 
 constexpr int kYcP = 64;          // segments per column (lanes of the scanning wavefront)
-constexpr int kYpCB = 16;         // columns per workgroup of the pivot kernel
 
 // (96 bytes for FP64: the hidden launch arguments behind it stay in the second 64-byte line)
 template <typename T>
@@ -47,29 +46,32 @@ struct YColShared {
         double v[DYN ? 3 : 1][kYcP][CB + 1];     // DYN: the pivot maps al (then al of the run so far), be, ga
     };
 };
+template <int CB>
 struct YPivShared {
-    double m[3][kYcP][kYpCB + 1];    // al (then the entry pivot), be, ga
+    double m[3][kYcP][CB + 1];       // al (then the entry pivot), be, ga
 };
 
 // pivot entering every S-row segment of every column: qy[p * nx + i]
-template <typename T, int S>
-__global__ void __launch_bounds__(kYcP * kYpCB) k_ycol_pivots(const T* __restrict__ r, T* __restrict__ qy, int nx,
-                                                                 int ny)
+template <typename T, int S, int CB>
+__global__ void __launch_bounds__(kYcP * CB) k_ycol_pivots(const T* __restrict__ r, T* __restrict__ qy, int nx, int ny)
 {
-    constexpr int CB = kYpCB;
-    __shared__ YPivShared sh;
+    __shared__ YPivShared<CB> sh;
     const int t = threadIdx.x, lane = t & 63;
     const int wv = __builtin_amdgcn_readfirstlane(t >> 6), nw = blockDim.x >> 6;
     const int col = t % CB, p = t / CB, P = blockDim.x / CB;
     const int i = blockIdx.x * CB + col;
+    // (all requested before the sweep)
+    T rv[S];
+#pragma unroll
+    for (int k = 0; k < S; ++k) rv[k] = i < nx && p * S + k < ny ? r[(size_t)(p * S + k) * nx + i] : T(0);
     double q = 0.0, pi = 1.0, ga = 0.0;
-    if (i < nx)
-        for (int k = 0; k < S && p * S + k < ny; ++k) {
-            (void)pivot_step<double>((double)r[(size_t)(p * S + k) * nx + i], q);
-            const double x = pi * q;
-            ga = fma_rn(pi, x, ga);
-            pi = x;
-        }
+#pragma unroll
+    for (int k = 0; k < S; ++k) {
+        (void)pivot_step<double>((double)rv[k], q);
+        const double x = pi * q;
+        ga = fma_rn(pi, x, ga);
+        pi = x;
+    }
     sh.m[0][p][col] = q;
     sh.m[1][p][col] = pi * pi;
     sh.m[2][p][col] = ga;
