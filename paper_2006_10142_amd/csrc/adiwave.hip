@@ -298,23 +298,27 @@ void launch_tri1(long long batch, const TriArgs<T>& a, hipStream_t st)
 {
     constexpr int NT = TR >= 256 ? TR : 256;
     constexpr int G = NT / TR;
-    // Plain reads of FP32 rows on 16-byte boundaries where most of 1024 lanes hold whole
-    // vectors and the call is far larger than the last-level cache (256 MB); else buffer
-    // reads.  us, buffer | plain: 8192 systems of 8192 256 | 242, of 7600 239 | 231, of 7000
-    // 219 | 213, 5000 of 8192 157 | 151; 4000 of 8000 123 | 125, 1000 of 8000 35 | 38, 8192 of
-    // 6000 186 | 185, of 5000 153 | 159; FP64 4000 of 8000 302 | 370.  (Buffer reads past the
-    // caches, the form of these calls before, took 245 at 8192 of 8192, but 248 at 7600: a
-    // line of 128 bytes that two rows share was read twice.)
-    constexpr bool kPlain = sizeof(T) == 4 && TR == 1024 && S == 8;
+    // FP32 rows on 16-byte boundaries that fill most of 1024 lanes, in calls far larger than
+    // the last-level cache (256 MB): plain loads, or, where rows are whole 4 KiB, buffer reads
+    // past the caches; else buffer reads.  us, buffer | past | plain, on other arrays each
+    // time: 8192 systems of 8192 256 | 245 | 242, of 7600 239 | 248 | 231, of 7000 219 | 231 |
+    // 213; 4000 of 8000 123 | - | 125, 1000 of 8000 35 | - | 38, 8192 of 6000 186 | 199 | 185,
+    // of 5000 153 | 171 | 159 (a line of 128 bytes that two rows share is read twice past the
+    // caches).  Called again on the same arrays, 8192 of 8192: 251 | 219 | 251; of 8000 - | 222 |
+    // 248.
+    constexpr bool kLong = sizeof(T) == 4 && TR == 1024 && S == 8;
     const dim3 grid((unsigned)((batch + G - 1) / G));
-    if constexpr (kPlain) {
+    if constexpr (kLong) {
         const bool rows16 = a.sys_stride % 4 == 0 && aligned16(a.a) && aligned16(a.b) && aligned16(a.c) && aligned16(a.d);
         if (rows16 && a.n > 6144 && 16.0 * a.n * (double)batch > 5.5e8) {
-            hipLaunchKernelGGL((k_tridiag_wg<T, S, TR, true>), grid, dim3(NT), 0, st, a);
+            if (a.sys_stride % 1024 == 0)
+                hipLaunchKernelGGL((k_tridiag_wg<T, S, TR, kTriPast>), grid, dim3(NT), 0, st, a);
+            else
+                hipLaunchKernelGGL((k_tridiag_wg<T, S, TR, kTriPlain>), grid, dim3(NT), 0, st, a);
             return;
         }
     }
-    hipLaunchKernelGGL((k_tridiag_wg<T, S, TR, false>), grid, dim3(NT), 0, st, a);
+    hipLaunchKernelGGL((k_tridiag_wg<T, S, TR, kTriBuffer>), grid, dim3(NT), 0, st, a);
 }
 
 template <typename T, int TR>

@@ -36,10 +36,12 @@ template <> struct Vec16<double> {
     __device__ static double2 pack(const double* o) { return make_double2(o[0], o[1]); }
 };
 
+constexpr int kBufNT = 2;   // buffer cache policy: non-temporal
+
 // S consecutive values at byte offset voff of a line, through a buffer resource of the
 // line's length, which needs no 16-byte alignment and drops what lies past the line's
-// end value by value (see bload8).
-template <typename T, int S>
+// end value by value (see bload8).  AUX: the buffer cache policy bits.
+template <typename T, int S, int AUX>
 __device__ __forceinline__ void load_seg(rsrc_t rs, int voff, T (&v)[S])
 {
     using V = Vec16<T>;
@@ -49,7 +51,7 @@ __device__ __forceinline__ void load_seg(rsrc_t rs, int voff, T (&v)[S])
     } else {
 #pragma unroll
         for (int k = 0; k < S / V::N; ++k) {
-            const auto x = __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 16 * k, 0, 0);
+            const auto x = __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 16 * k, 0, AUX);
             V::unpack(__builtin_bit_cast(typename V::type, x), &v[k * V::N]);
         }
     }
@@ -406,9 +408,10 @@ struct TriArgs {
 // and written once, by buffer accesses of any alignment (8192 systems of 8191, value by
 // value behind bounds tests, 580 us; so, 245).  (The system of a wavefront is made uniform
 // by name: a resource that the compiler takes for one of each lane costs a loop at every
-// access, 30000 systems of 33 15.6 us, 14.5 without.)  PLAIN: the reads as plain loads (see
+// access, 30000 systems of 33 15.6 us, 14.5 without.)  LOAD: how the arrays are read (see
 // launch_tri1).
-template <typename T, int S, int TR, bool PLAIN>
+enum { kTriBuffer, kTriPast, kTriPlain };   // buffer reads; the same past the caches; plain loads
+template <typename T, int S, int TR, int LOAD>
 __global__ void __launch_bounds__(TR >= 256 ? TR : 256) k_tridiag_wg(TriArgs<T> A)
 {
     constexpr int G = (TR >= 256 ? TR : 256) / TR;
@@ -425,8 +428,8 @@ __global__ void __launch_bounds__(TR >= 256 ? TR : 256) k_tridiag_wg(TriArgs<T> 
     T a[S], b[S], c[S], d[S];
     const bool vec = A.sys_stride * sizeof(T) % 16 == 0;
     auto load = [&](const T* p, T (&v)[S]) {
-        if constexpr (PLAIN) load_plain<T, S>(p + off + lo, L, vec, v);
-        else load_seg<T, S>(buf(p + off, bytes), voff, v);
+        if constexpr (LOAD == kTriPlain) load_plain<T, S>(p + off + lo, L, vec, v);
+        else load_seg<T, S, LOAD == kTriPast ? kBufNT : 0>(buf(p + off, bytes), voff, v);
     };
     load(A.a, a);
     load(A.b, b);
